@@ -701,6 +701,8 @@ def image_clean(residual, psf, gain, threshold, max_iter):
     _check(lib().qc_image_clean(_ptr(residual), _ptr(psf), n, float(gain), float(threshold), max_iter,
                                 _ptr(pix), _ptr(flux), _ptr(nc), _stream()), "qc_image_clean")
     k = int(nc.item())
+    if k < 0:
+        raise QCError(-3, "qc_image_clean", "the launch's workgroups could not run together")
     return pix[:k], flux[:k]
 
 

@@ -15,14 +15,14 @@
 //     engine), so I = (-1)^(il+im) Re FFT2(conj X) / W.  The 2-D transform
 //     is rows, a tiled transpose, rows again; the final step reads the
 //     transposed result back.
-//   * Hogbom CLEAN on one workgroup, float32: each iteration subtracts the
+//   * Hogbom CLEAN in one launch, float32: each iteration subtracts the
 //     previous component's beam g * psf[(p - peak + (n/2, n/2)) mod n]
 //     (product and difference rounded separately: no contraction) and,
 //     in the same sweep, finds the next peak: largest |residual|, ties to
 //     the smallest flat index il * n + im.  g = gain * peak (rounded).
 //     Stops when |peak| < threshold or after max_iter components.  Every
 //     thread owns the same pixels in every sweep, so the only cross-thread
-//     step is the block reduction of the peak.
+//     step is the reduction of the peak.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
@@ -34,32 +34,107 @@ namespace qc {
 
 namespace {
 
-__global__ void image_grid_kernel(const float* __restrict__ u, const float* __restrict__ v,
-                                  const float2* __restrict__ vis, const float* __restrict__ weight,
-                                  int64_t n_vis, int n, double inv_du, float2* __restrict__ grid,
-                                  double* __restrict__ wsum) {
+// Gridding takes four consecutive samples per thread.  Neighbouring samples
+// (channels of one baseline) mostly share a cell, so runs of equal cells are
+// summed first, in the thread and then over the wave, and one atomic per run
+// and component reaches memory.  Only the cell itself is added to here; the
+// conjugates follow from the finished sums (image_mirror_kernel).  Bound: the
+// atomics: 8.1 M samples of 32 antennas onto 1024 x 1024 took 2.3 ms with four
+// per sample (14 G/s); runs leave about one sample in nine and the conjugates
+// none, 62 us and 6 us for the mirror pass (2.1 TB/s of samples).
+constexpr int GRID_PER = 4;
+
+template <bool VEC>
+__global__ void __launch_bounds__(256)
+image_grid_kernel(const float* __restrict__ u, const float* __restrict__ v, const float2* __restrict__ vis,
+                  const float* __restrict__ weight, int64_t n_vis, int n, double inv_du,
+                  float2* __restrict__ grid, double* __restrict__ wsum) {
   __shared__ double red[4];
+  const int lane = threadIdx.x & 63;
   double wacc = 0.0;
-  for (int64_t k = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; k < n_vis;
-       k += (int64_t)gridDim.x * blockDim.x) {
-    const int64_t iu = (int64_t)floor((double)u[k] * inv_du + 0.5) + n / 2;
-    const int64_t iv = (int64_t)floor((double)v[k] * inv_du + 0.5) + n / 2;
-    const int64_t ju = n - iu, jv = n - iv;
-    if (iu < 0 || iu >= n || iv < 0 || iv >= n || ju < 0 || ju >= n || jv < 0 || jv >= n) continue;
-    const float w = weight ? weight[k] : 1.f;
-    const float2 z = vis[k];
-    float* a = reinterpret_cast<float*>(grid + iu * n + iv);
-    float* b = reinterpret_cast<float*>(grid + ju * n + jv);
-    atomicAdd(a, w * z.x);
-    atomicAdd(a + 1, w * z.y);
-    atomicAdd(b, w * z.x);
-    atomicAdd(b + 1, -w * z.y);
-    wacc += 2.0 * (double)w;
+  auto add = [&](int cell, float2 z) {
+    if (cell < 0) return;
+    float* const a = reinterpret_cast<float*>(grid + cell);
+    atomicAdd(a, z.x);
+    atomicAdd(a + 1, z.y);
+  };
+  // whole waves run each step: the scan needs every lane
+  const int64_t wave_step = (int64_t)gridDim.x * blockDim.x * GRID_PER;
+  for (int64_t w0 = ((int64_t)blockIdx.x * blockDim.x + (threadIdx.x & ~63)) * GRID_PER; w0 < n_vis;
+       w0 += wave_step) {
+    const int64_t k0 = w0 + lane * GRID_PER;
+    float uu[GRID_PER], vv[GRID_PER], ww[GRID_PER];
+    float2 zz[GRID_PER];
+    if (VEC && k0 + GRID_PER <= n_vis) {
+      const float4 a = *reinterpret_cast<const float4*>(u + k0), b = *reinterpret_cast<const float4*>(v + k0);
+      const float4 c = *reinterpret_cast<const float4*>(vis + k0), d = *reinterpret_cast<const float4*>(vis + k0 + 2);
+      const float4 f = weight ? *reinterpret_cast<const float4*>(weight + k0) : make_float4(1.f, 1.f, 1.f, 1.f);
+      uu[0] = a.x, uu[1] = a.y, uu[2] = a.z, uu[3] = a.w;
+      vv[0] = b.x, vv[1] = b.y, vv[2] = b.z, vv[3] = b.w;
+      ww[0] = f.x, ww[1] = f.y, ww[2] = f.z, ww[3] = f.w;
+      zz[0] = make_float2(c.x, c.y), zz[1] = make_float2(c.z, c.w);
+      zz[2] = make_float2(d.x, d.y), zz[3] = make_float2(d.z, d.w);
+    } else {
+#pragma unroll
+      for (int j = 0; j < GRID_PER; ++j) {
+        const int64_t k = k0 + j < n_vis ? k0 + j : n_vis - 1;
+        uu[j] = u[k], vv[j] = v[k], zz[j] = vis[k];
+        ww[j] = weight ? weight[k] : 1.f;
+      }
+    }
+    int cell[GRID_PER];
+#pragma unroll
+    for (int j = 0; j < GRID_PER; ++j) {
+      const int64_t iu = (int64_t)floor((double)uu[j] * inv_du + 0.5) + n / 2;
+      const int64_t iv = (int64_t)floor((double)vv[j] * inv_du + 0.5) + n / 2;
+      // the mirrored cell n - i lies in [0, n) for i in [1, n]
+      const bool in = k0 + j < n_vis && iu >= 1 && iu < n && iv >= 1 && iv < n;
+      cell[j] = in ? (int)(iu * n + iv) : -1;
+      zz[j] = in ? make_float2(ww[j] * zz[j].x, ww[j] * zz[j].y) : make_float2(0.f, 0.f);
+      if (in) wacc += 2.0 * (double)ww[j];
+    }
+    // runs inside the thread; the last one goes on to the wave
+    int run = cell[0];
+    float2 sum = zz[0];
+    bool whole = true;
+#pragma unroll
+    for (int j = 1; j < GRID_PER; ++j) {
+      const bool same = cell[j] == run;
+      if (!same) {
+        add(run, sum);
+        whole = false;
+      }
+      sum = make_float2(same ? sum.x + zz[j].x : zz[j].x, same ? sum.y + zz[j].y : zz[j].y);
+      run = cell[j];
+    }
+    // segmented sum over lanes: a lane of one run continues its predecessor's
+    // segment if the cells agree
+    const int before = __shfl_up(run, 1);
+    const uint64_t heads = __ballot(lane == 0 || !whole || before != run);
+    const int start = 63 - __clzll((long long)(heads & (~0ull >> (63 - lane))));
+    for (int d = 1; d < 64; d <<= 1) {
+      const float x = __shfl_up(sum.x, d), y = __shfl_up(sum.y, d);
+      if (lane - d >= start) sum.x += x, sum.y += y;
+    }
+    if (lane == 63 || (heads >> (lane + 1)) & 1) add(run, sum);
   }
   for (int d = 32; d >= 1; d >>= 1) wacc += __shfl_down(wacc, d);
-  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = wacc;
+  if (lane == 0) red[threadIdx.x >> 6] = wacc;
   __syncthreads();
   if (threadIdx.x == 0) atomicAdd(wsum, red[0] + red[1] + red[2] + red[3]);
+}
+
+// Adds to each cell the conjugate of its mirror's sum: grid[c] = A[c] +
+// conj A[mirror c], mirror (iu, iv) -> (n - iu, n - iv), in place.  A thread
+// takes a cell and its mirror; row and column 0 have no mirror and stay zero.
+__global__ void __launch_bounds__(256) image_mirror_kernel(float2* __restrict__ grid, int n) {
+  const int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  const int iu = (int)(e / n), iv = (int)(e % n);
+  if (iu < 1 || iu > n / 2 || iv < 1 || (iu == n / 2 && iv > n / 2)) return;
+  const int64_t m = (int64_t)(n - iu) * n + (n - iv);
+  const float2 a = grid[e], b = grid[m];
+  grid[e] = make_float2(a.x + b.x, a.y - b.y);
+  if (m != e) grid[m] = make_float2(b.x + a.x, b.y - a.y);
 }
 
 __global__ void image_zero_kernel(float2* __restrict__ grid, int64_t npix, double* __restrict__ wsum) {
@@ -154,7 +229,70 @@ hipError_t rows_fft(float2* x, int n, const float2* tw, hipStream_t s) {
   return hipErrorInvalidValue;
 }
 
+// ---- Hogbom CLEAN ----------------------------------------------------------
+//
+// One launch of G workgroups runs every iteration.  Each thread owns the same
+// pixels throughout, so the residual needs no exchange; what crosses
+// workgroups is one 64-bit candidate peak each per iteration, written and
+// polled with agent-scope accesses (the compute dies' L2 caches are not
+// coherent with each other).  A candidate carries the iteration's tag, so the
+// poll is reduction and barrier in one: a workgroup that has seen every tag
+// of iteration i knows all have finished it.  Keys are kept for two iterations
+// (by parity): a workgroup writes i + 2 over i only after it has seen every
+// i + 1, which each workgroup writes after its last read of i.
+//
+// Bound: at 1024 x 1024 the sweep reads 4 MiB of beam (the residual stays in
+// registers) and the exchange costs two trips to memory.  One workgroup on one
+// CU took 0.65 ms per component there, bound by that CU's load path; 64
+// workgroups take 4.6 us, about half of it the exchange.
+//
+// All G workgroups have to be resident together.  G <= 64 of 1024 threads
+// leaves room for one such launch on each of the four hardware queues of a
+// process on 256 CUs; a wait is bounded in time all the same, and a launch
+// whose wait expires reports n_comp = -1 instead of a result.
 constexpr int CLEAN_NT = 1024;
+constexpr int CLEAN_MAX_WG = 64;
+constexpr int CLEAN_SLOTS = 16;  // launches in flight with an exchange area of their own
+constexpr uint64_t CLEAN_WAIT_TICKS = 200000000ull;  // 2 s of the 100 MHz wall clock
+
+struct CleanSlot {
+  uint64_t key[2][CLEAN_MAX_WG];
+  int busy, done, abort;
+};
+__device__ CleanSlot g_clean_slots[CLEAN_SLOTS];
+
+// Claims an exchange area for the launch that follows on the stream and hands
+// its index on in n_comp (-1: all taken; the launch then runs on one workgroup).
+__global__ void __launch_bounds__(CLEAN_MAX_WG) image_clean_claim_kernel(int* __restrict__ n_comp) {
+  __shared__ int slot_s;
+  if (threadIdx.x == 0) {
+    int slot = -1;
+    for (int i = 0; i < CLEAN_SLOTS && slot < 0; ++i)
+      if (atomicCAS(&g_clean_slots[i].busy, 0, 1) == 0) slot = i;
+    slot_s = slot;
+    *n_comp = slot;
+  }
+  __syncthreads();
+  if (slot_s < 0) return;
+  CleanSlot& c = g_clean_slots[slot_s];
+  for (int q = 0; q < 2; ++q)
+    __hip_atomic_store(&c.key[q][threadIdx.x], 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  if (threadIdx.x == 0) {
+    __hip_atomic_store(&c.done, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    __hip_atomic_store(&c.abort, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  }
+}
+
+// Candidate: |v| (31 bits), 2^26 - 1 - pixel (26), sign (1), tag (6): the
+// largest is the largest |v|, of those the smallest pixel (n <= 8192).  A NaN
+// is no candidate; 0 stands for none.
+__device__ __forceinline__ uint64_t clean_key(float v, int p) {
+  const uint32_t bits = __float_as_uint(v);
+  return ((uint64_t)(bits & 0x7fffffffu) << 33) | ((uint64_t)((1 << 26) - 1 - p) << 7) |
+         ((uint64_t)(bits >> 31) << 6);
+}
+
+__device__ __forceinline__ uint64_t key_max(uint64_t a, uint64_t b) { return a > b ? a : b; }
 
 // The beam subtraction rounds the product and the difference separately: no
 // contraction into a fused multiply-add in this kernel (the pragma covers
@@ -162,84 +300,153 @@ constexpr int CLEAN_NT = 1024;
 // is spelled out).
 #pragma clang fp contract(off)
 
+// PX > 0: PX pixels per thread held in registers (G * CLEAN_NT * PX >= n^2);
+// PX = 0: any number, read from and written to memory each iteration.
+template <int PX>
 __global__ void __launch_bounds__(CLEAN_NT)
-image_clean_kernel(float* __restrict__ r, const float* __restrict__ psf, int n, float gain, float thr,
+image_clean_kernel(float* __restrict__ r, const float* __restrict__ psf, int log2n, float gain, float thr,
                    int max_iter, int* __restrict__ comp_pix, float* __restrict__ comp_flux,
                    int* __restrict__ n_comp) {
-  __shared__ float bval[CLEAN_NT / 64];
-  __shared__ float bsig[CLEAN_NT / 64];
-  __shared__ int bidx[CLEAN_NT / 64];
-  __shared__ float peak_s;
-  __shared__ int pidx_s;
+  __shared__ uint64_t wkey[CLEAN_NT / 64];
+  __shared__ uint64_t all_s;
+  __shared__ int slot_s, stop_s;
   const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
-  const int64_t npix = (int64_t)n * n;
-  const int mask = n - 1, h = n / 2;
-  float g = 0.f;   // flux of the component whose beam is still to subtract
+  const int n = 1 << log2n, mask = n - 1, h = n / 2;
+  const int npix = 1 << (2 * log2n);
+  int G = gridDim.x, wg = blockIdx.x;
+  if (t == 0) slot_s = G > 1 ? *n_comp : -1;
+  __syncthreads();
+  const int slot = slot_s;
+  if (G > 1 && slot < 0) {  // no exchange area: the first workgroup does it all
+    if (wg > 0) return;
+    G = 1;
+  }
+  CleanSlot* const ex = g_clean_slots + (slot < 0 ? 0 : slot);
+  const int first = wg * CLEAN_NT + t, stride = G * CLEAN_NT;
+  const bool regs = PX > 0 && G == (int)gridDim.x;
+  float own[PX > 0 ? PX : 1];
+  if (regs) {
+#pragma unroll
+    for (int j = 0; j < PX; ++j) {
+      const int p = first + j * stride;
+      own[j] = p < npix ? r[p] : 0.f;
+    }
+  }
+  float g = 0.f;  // flux of the component whose beam is still to subtract
   int pl = 0, pm = 0;
   int it = 0;
+  bool failed = false;
   for (;; ++it) {
     // subtract the previous component's beam (none before the first peak)
     // and find the next peak in the same sweep
     float best = -1.f, bv = 0.f;  // largest |residual| and its signed value
-    int bi = 0x7fffffff;
-    for (int64_t p = t; p < npix; p += CLEAN_NT) {
-      float v = r[p];
-      if (it > 0) {
-        const int il = (int)(p / n), im = (int)(p % n);
-        const int qi = (il - pl + h) & mask, qm = (im - pm + h) & mask;
-        const float prod = g * psf[(int64_t)qi * n + qm];  // rounded product
-        v = v - prod;                                       // rounded difference
-        r[p] = v;
-      }
-      const float a = fabsf(v);
-      if (a > best) {  // p increases along the thread's sweep: ties keep the first
-        best = a;
-        bv = v;
-        bi = (int)p;
-      }
-    }
-    for (int d = 32; d >= 1; d >>= 1) {
-      const float ob = __shfl_down(best, d);
-      const float ov = __shfl_down(bv, d);
-      const int oi = __shfl_down(bi, d);
-      if (lane + d < 64 && (ob > best || (ob == best && oi < bi))) {
-        best = ob;
-        bv = ov;
-        bi = oi;
-      }
-    }
-    if (lane == 0) {
-      bval[wave] = best;
-      bsig[wave] = bv;
-      bidx[wave] = bi;
-    }
-    __syncthreads();
-    if (t == 0) {
-      float b = bval[0], sv = bsig[0];
-      int i = bidx[0];
-      for (int w = 1; w < CLEAN_NT / 64; ++w)
-        if (bval[w] > b || (bval[w] == b && bidx[w] < i)) {
-          b = bval[w];
-          sv = bsig[w];
-          i = bidx[w];
+    int bi = 0;
+    auto beam = [&](int p) -> float {
+      return psf[((((p >> log2n) - pl + h) & mask) << log2n) + (((p & mask) - pm + h) & mask)];
+    };
+    auto visit = [&](float v, float b, int p, bool in) -> float {
+      const float prod = g * b;      // rounded product
+      v = it > 0 ? v - prod : v;     // rounded difference
+      const bool more = in && fabsf(v) > best;
+      best = more ? fabsf(v) : best;  // p increases along the thread's sweep: ties keep the first
+      bv = more ? v : bv;
+      bi = more ? p : bi;
+      return v;
+    };
+    if (regs) {
+      float b[PX > 0 ? PX : 1];
+#pragma unroll
+      for (int j = 0; j < PX; ++j) b[j] = beam((first + j * stride) & (npix - 1));
+#pragma unroll
+      for (int j = 0; j < PX; ++j) own[j] = visit(own[j], b[j], first + j * stride, first + j * stride < npix);
+    } else {
+      constexpr int U = 8;
+      for (int p0 = first; p0 < npix; p0 += U * stride) {
+        float v[U], b[U];
+#pragma unroll
+        for (int j = 0; j < U; ++j) {
+          const int p = (p0 + j * stride) & (npix - 1);
+          v[j] = r[p];
+          b[j] = beam(p);
         }
-      pidx_s = i;
-      peak_s = sv;
+#pragma unroll
+        for (int j = 0; j < U; ++j) {
+          const int p = p0 + j * stride;
+          v[j] = visit(v[j], b[j], p, p < npix);
+          if (it > 0 && p < npix) r[p] = v[j];
+        }
+      }
+    }
+    uint64_t key = best < 0.f ? 0ull : clean_key(bv, bi);
+    for (int d = 32; d >= 1; d >>= 1) key = key_max(key, __shfl_xor((unsigned long long)key, d));
+    if (lane == 0) wkey[wave] = key;
+    __syncthreads();
+    if (wave == 0) {
+      key = lane < CLEAN_NT / 64 ? wkey[lane] : 0ull;
+      for (int d = 8; d >= 1; d >>= 1) key = key_max(key, __shfl_xor((unsigned long long)key, d));
+      int stop = 0;
+      if (G > 1) {
+        const uint64_t tag = (uint64_t)(it % 62 + 1);
+        uint64_t* const at = ex->key[it & 1];
+        if (lane == 0) __hip_atomic_store(&at[wg], key | tag, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        uint64_t began = 0;
+        for (unsigned spin = 0;; ++spin) {
+          key = lane < G ? __hip_atomic_load(&at[lane], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : tag;
+          if (__all((key & 63u) == tag)) break;
+          if ((spin & 255u) == 255u) {
+            const uint64_t now = wall_clock64();
+            if (began == 0) began = now;
+            if (now - began > CLEAN_WAIT_TICKS ||
+                __hip_atomic_load(&ex->abort, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0) {
+              stop = 1;
+              break;
+            }
+          }
+        }
+        if (stop && lane == 0) __hip_atomic_store(&ex->abort, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        key &= ~63ull;
+        for (int d = 32; d >= 1; d >>= 1) key = key_max(key, __shfl_xor((unsigned long long)key, d));
+      }
+      if (lane == 0) {
+        all_s = key;
+        stop_s = stop;
+      }
     }
     __syncthreads();
-    const float peak = peak_s;
-    const int pi = pidx_s;
-    __syncthreads();  // the shared values are read before the next reduction writes them
-    if (it >= max_iter || !(fabsf(peak) >= thr)) break;
+    const uint64_t top = all_s;
+    failed = stop_s != 0;
+    // written again only after the next iteration's first barrier
+    const bool none = top == 0ull;
+    const int pi = none ? 0x7fffffff : (1 << 26) - 1 - (int)((top >> 7) & ((1u << 26) - 1));
+    const float peak = none ? 0.f : __uint_as_float((uint32_t)(top >> 33) | ((uint32_t)((top >> 6) & 1u) << 31));
+    if (failed || it >= max_iter || !(fabsf(peak) >= thr)) break;
     g = gain * peak;
-    pl = pi / n;
-    pm = pi % n;
-    if (t == 0) {
+    pl = pi >> log2n;
+    pm = pi & mask;
+    if (wg == 0 && t == 0) {
       comp_pix[it] = pi;
       comp_flux[it] = g;
     }
   }
-  if (t == 0) *n_comp = it;
+  if (regs) {
+#pragma unroll
+    for (int j = 0; j < PX; ++j) {
+      const int p = first + j * stride;
+      if (p < npix) r[p] = own[j];
+    }
+  }
+  if (t == 0) {
+    if (G == 1) {
+      *n_comp = it;
+    } else {
+      // the last workgroup to get here has seen every other past its last wait
+      const int left = __hip_atomic_fetch_add(&ex->done, 1, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_AGENT);
+      if (left == G - 1) {
+        *n_comp = __hip_atomic_load(&ex->abort, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) ? -1 : it;
+        __hip_atomic_store(&ex->busy, 0, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT);
+      }
+    }
+  }
 }
 
 #pragma clang fp contract(on)
@@ -274,10 +481,17 @@ extern "C" qc_status qc_image_grid(const float* u, const float* v, const float* 
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return qc::api_fail(QC_EHIP, "zero kernel: %s", hipGetErrorString(e));
   if (n_vis > 0) {
-    const int64_t blocks = (n_vis + 255) / 256 < 4096 ? (n_vis + 255) / 256 : 4096;
-    hipLaunchKernelGGL(qc::image_grid_kernel, dim3((unsigned)blocks), dim3(256), 0, s, u, v,
-                       reinterpret_cast<const float2*>(vis), weight, n_vis, (int)n, (double)n * cell_rad,
-                       reinterpret_cast<float2*>(grid), wsum);
+    const int64_t per = 256 * qc::GRID_PER;
+    const int64_t blocks = (n_vis + per - 1) / per < 2048 ? (n_vis + per - 1) / per : 2048;
+    const bool vec = ((reinterpret_cast<uintptr_t>(u) | reinterpret_cast<uintptr_t>(v) |
+                       reinterpret_cast<uintptr_t>(vis) | reinterpret_cast<uintptr_t>(weight)) & 15u) == 0;
+    hipLaunchKernelGGL(vec ? qc::image_grid_kernel<true> : qc::image_grid_kernel<false>, dim3((unsigned)blocks),
+                       dim3(256), 0, s, u, v, reinterpret_cast<const float2*>(vis), weight, n_vis, (int)n,
+                       (double)n * cell_rad, reinterpret_cast<float2*>(grid), wsum);
+    e = hipGetLastError();
+    if (e != hipSuccess) return qc::api_fail(QC_EHIP, "grid kernel: %s", hipGetErrorString(e));
+    hipLaunchKernelGGL(qc::image_mirror_kernel, dim3((unsigned)((npix / 2 + n + 255) / 256)), dim3(256), 0, s,
+                       reinterpret_cast<float2*>(grid), (int)n);
     e = hipGetLastError();
     if (e != hipSuccess) return qc::api_fail(QC_EHIP, "grid kernel: %s", hipGetErrorString(e));
   }
@@ -329,9 +543,25 @@ extern "C" qc_status qc_image_clean(float* residual, const float* psf, int32_t n
   if (!residual || !psf || !n_comp || (max_iter > 0 && (!comp_pix || !comp_flux)))
     return qc::api_fail(QC_EINVAL, "null buffer");
   hipStream_t s = reinterpret_cast<hipStream_t>(stream);
-  hipLaunchKernelGGL(qc::image_clean_kernel, dim3(1), dim3(qc::CLEAN_NT), 0, s, residual, psf, (int)n, gain,
-                     threshold, (int)max_iter, reinterpret_cast<int*>(comp_pix), comp_flux,
-                     reinterpret_cast<int*>(n_comp));
+  // Workgroups by image size: 4 pixels per thread until 64 workgroups are
+  // reached at n = 512 (one workgroup and no exchange up to n = 64), then 16
+  // at n = 1024; larger images would need more than the 128 registers a thread
+  // of a full workgroup has, and keep the residual in memory.
+  int log2n = 0;
+  while ((1 << log2n) < n) ++log2n;
+  int* const pix = reinterpret_cast<int*>(comp_pix);
+  int* const count = reinterpret_cast<int*>(n_comp);
+  auto launch = [&](auto kernel, int wgs) {
+    if (wgs > 1) hipLaunchKernelGGL(qc::image_clean_claim_kernel, dim3(1), dim3(qc::CLEAN_MAX_WG), 0, s, count);
+    hipLaunchKernelGGL(kernel, dim3(wgs), dim3(qc::CLEAN_NT), 0, s, residual, psf, log2n, gain, threshold,
+                       (int)max_iter, pix, comp_flux, count);
+  };
+  if (log2n <= 6) launch(qc::image_clean_kernel<4>, 1);
+  else if (log2n == 7) launch(qc::image_clean_kernel<4>, 4);
+  else if (log2n == 8) launch(qc::image_clean_kernel<4>, 16);
+  else if (log2n == 9) launch(qc::image_clean_kernel<4>, 64);
+  else if (log2n == 10) launch(qc::image_clean_kernel<16>, 64);
+  else launch(qc::image_clean_kernel<0>, 64);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return qc::api_fail(QC_EHIP, "clean kernel: %s", hipGetErrorString(e));
   return QC_OK;
