@@ -316,7 +316,7 @@ image_clean_kernel(float* __restrict__ r, const float* __restrict__ psf, int log
   int G = gridDim.x, wg = blockIdx.x;
   if (t == 0) slot_s = G > 1 ? *n_comp : -1;
   __syncthreads();
-  const int slot = slot_s;
+  const int slot = __builtin_amdgcn_readfirstlane(slot_s);
   if (G > 1 && slot < 0) {  // no exchange area: the first workgroup does it all
     if (wg > 0) return;
     G = 1;
@@ -413,9 +413,12 @@ image_clean_kernel(float* __restrict__ r, const float* __restrict__ psf, int log
       }
     }
     __syncthreads();
-    const uint64_t top = all_s;
-    failed = stop_s != 0;
-    // written again only after the next iteration's first barrier
+    // block-uniform, read from LDS (written again only after the next
+    // iteration's first barrier): scalar for the compiler, so that the loop,
+    // which holds barriers, is a scalar loop
+    const uint64_t top = ((uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(all_s >> 32)) << 32) |
+                         (uint32_t)__builtin_amdgcn_readfirstlane((int)all_s);
+    failed = __builtin_amdgcn_readfirstlane(stop_s) != 0;
     const bool none = top == 0ull;
     const int pi = none ? 0x7fffffff : (1 << 26) - 1 - (int)((top >> 7) & ((1u << 26) - 1));
     const float peak = none ? 0.f : __uint_as_float((uint32_t)(top >> 33) | ((uint32_t)((top >> 6) & 1u) << 31));
