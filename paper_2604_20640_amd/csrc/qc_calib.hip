@@ -17,7 +17,7 @@
 // population (1024 threads and 11-bit digits for large populations, one
 // wave and 8-bit digits for small ones); large populations get their
 // amplitudes formed once by a whole-GPU pass and cached in LDS when they
-// fit.
+// fit.  Larger ones still are bounded by a sample and read once (below).
 //
 // Delay/phase application (Sec. 4.1 step 2 and eq. 1; Sec. 7 delay and phase
 // corrections): V_ij[k] *= exp(+i [2 pi f_k (tau_i - tau_j) + phi_i - phi_j]).
@@ -567,11 +567,390 @@ __global__ void mad_amp4_kernel(const float4* __restrict__ vis, int64_t n_base, 
                         amp_f32(make_float2(b.x, b.y)), amp_f32(make_float2(b.z, b.w)));
 }
 
+// ---- large populations: one pass over the visibilities ---------------------
+//
+// A population's median, MAD and flags take one read of its visibilities when
+// a sample says beforehand where the median, the MAD and the threshold lie:
+//   1. mad_sample_kernel, a workgroup per population: amplitudes of MAD_SAMPLE
+//      elements (jittered strata of four neighbours) bound the median in
+//      [lo, hi] and the MAD in [dlo, dhi];
+//   2. mad_scan_kernel, the whole GPU: counts the amplitudes below the median's
+//      window, keeps those inside it; keeps the amplitudes whose deviation
+//      from some median in [lo, hi] can lie in [dlo, dhi] and counts those
+//      whose deviation cannot exceed dlo; writes the flags that any threshold
+//      in [lo + c dlo, hi + c dhi] decides alike and keeps the others;
+//   3. mad_finish_kernel, a workgroup per population: exact selection among the
+//      kept amplitudes at the ranks the counts leave, the threshold, the
+//      remaining flags.
+// Ranks and counts are of the whole population, so the results are the exact
+// order statistics.  A population whose rank falls outside its window (large
+// groups of equal amplitudes, or a sample that misled) or whose lists overflow
+// stays MAD_OPEN, and mad_kernel then does it from the start.
+//
+// Bound: HBM, 8 B a visibility read and 1 B written, and the scan's vector
+// instructions beside it.  528 planes of 524288 visibilities: 0.87 ms (sample
+// 0.06, scan 0.69 = 3.6 TB/s, finish 0.18); 2.45 ms with the amplitudes
+// written out first and a workgroup per population selecting among them.
+enum { MAD_OPEN = 0, MAD_SCAN = 1, MAD_DONE = 2 };
+struct MadWin {
+  int state;
+  float lo, hi;                  // the median lies in (lo, hi)
+  float q_lo, q_hi;              // their squares, and those of
+  float q_l0, q_c0, q_c1, q_r1;  //   l0 < c0 < lo < hi < c1 < r1: amplitudes outside [l0, r1] deviate
+                                 //   by dhi or more, those inside [c0, c1] by dlo or less
+  float q_t0, q_t1;              //   and t0, t1: T lies in [t0, t1]
+  float r1;
+  uint32_t n_le, n_in;           // amplitudes up to lo; inside [c0, c1]
+  uint32_t n_med, n_dev, n_thr;  // entries of the three lists (also past their capacity)
+  double dlo, dhi;
+};
+
+// The scan compares float32 squares |V|^2 with the windows' squares, not the
+// amplitudes: what it takes for a <= x has a <= x (1 + MAD_EPS), and likewise
+// the other way round (rounding of both squares: 3 2^-24 of the amplitude).
+// The finish accepts a result only if it keeps that distance from its window.
+constexpr double MAD_EPS = 4e-7;
+
+constexpr int MAD_SAMPLE_NT = 512;
+constexpr int MAD_SAMPLE_PER = 24;
+constexpr int MAD_SAMPLE = MAD_SAMPLE_NT * MAD_SAMPLE_PER;  // 12288
+constexpr int MAD_SLACK = 333;       // ranks of the sample on each side: 6 standard deviations of its median's
+constexpr int MAD_CHUNK = 16384;     // elements per scan workgroup
+
+// Capacities of the three lists of a population of n: about 5 % and 13 % of a
+// smooth population fall to the first two.
+__host__ __device__ __forceinline__ int64_t mad_cap_med(int64_t n) { return n / 8; }
+__host__ __device__ __forceinline__ int64_t mad_cap_dev(int64_t n) { return n / 4; }
+__host__ __device__ __forceinline__ int64_t mad_cap_thr(int64_t n) { return n / 16; }
+__host__ __device__ __forceinline__ int64_t mad_list_floats(int64_t n) {
+  return (mad_cap_med(n) + mad_cap_dev(n) + 2 * mad_cap_thr(n) + 3) / 4 * 4;
+}
+
+// The four amplitudes at elements i..i+3 of a population (i % 4 == 0).  VEC:
+// rows are multiples of four elements and 16-byte aligned.
+template <bool VEC>
+__device__ __forceinline__ void amp4(const float2* __restrict__ vis, const Pop& pop, int64_t i, float a[4]) {
+  if constexpr (VEC) {
+    const float4* p = reinterpret_cast<const float4*>(vis + pop.off(i));
+    const float4 u = p[0], v = p[1];
+    a[0] = amp_f32(make_float2(u.x, u.y)), a[1] = amp_f32(make_float2(u.z, u.w));
+    a[2] = amp_f32(make_float2(v.x, v.y)), a[3] = amp_f32(make_float2(v.z, v.w));
+  } else {
+#pragma unroll
+    for (int j = 0; j < 4; ++j) a[j] = amp_f32(vis[pop.off(i + j)]);
+  }
+}
+
+// Bounds of the sample's order statistics of ranks MAD_SAMPLE/2 -+ MAD_SLACK
+// over keys kv[] (16 per thread): the edges of their bins in a histogram over
+// the middle three quarters of a 64-key subsample.  False when a rank falls
+// outside it.
+__device__ __forceinline__ bool sample_bounds(const float (&a)[MAD_SAMPLE_PER], float centre, unsigned* hist,
+                                              unsigned* wsum, unsigned long long* sh, unsigned* sub, uint32_t& klo,
+                                              uint32_t& khi) {
+  constexpr int NT = MAD_SAMPLE_NT, NBINS = 2048;
+  const int t = threadIdx.x;
+  auto key = [&](int j) -> uint32_t { return __float_as_uint(fabsf(a[j] - centre)); };
+  if (t % (NT / 64) == 0) sub[t / (NT / 64)] = key(5);
+  for (int i = t; i < NBINS; i += NT) hist[i] = 0;
+  __syncthreads();
+  if (t < 64) {
+    const uint32_t srt = wave_sort64<uint32_t>(sub[t]);
+    const uint32_t lo = __shfl(srt, 8), hi = __shfl(srt, 56);
+    int s = 0;
+    while (s < 31 && ((hi - lo) >> s) >= (uint32_t)(NBINS - 2)) ++s;
+    if (t == 0) {
+      sh[2] = lo;
+      sh[3] = (unsigned long long)s;
+    }
+  }
+  __syncthreads();
+  const uint32_t lo = (uint32_t)__builtin_amdgcn_readfirstlane((int)sh[2]);
+  const int s = __builtin_amdgcn_readfirstlane((int)sh[3]);
+  unsigned under = 0u, over = 0u;
+#pragma unroll
+  for (int j = 0; j < MAD_SAMPLE_PER; ++j) {
+    const uint32_t k = key(j), q = (k - lo) >> s;
+    if (k < lo) ++under;
+    else if (q >= (uint32_t)(NBINS - 2)) ++over;
+    else atomicAdd(&hist[q + 1u], 1u);
+  }
+#pragma unroll
+  for (int d = 32; d >= 1; d >>= 1) {
+    under += __shfl_xor(under, d);
+    over += __shfl_xor(over, d);
+  }
+  if ((t & 63) == 0) {
+    if (under) atomicAdd(&hist[0], under);
+    if (over) atomicAdd(&hist[NBINS - 1], over);
+  }
+  __syncthreads();
+  find_digit<NT, NBINS>(hist, MAD_SAMPLE / 2 - MAD_SLACK, wsum, sh);
+  const unsigned b0 = (unsigned)__builtin_amdgcn_readfirstlane((int)sh[0]);
+  __syncthreads();
+  find_digit<NT, NBINS>(hist, MAD_SAMPLE / 2 + MAD_SLACK, wsum, sh);
+  const unsigned b1 = (unsigned)__builtin_amdgcn_readfirstlane((int)sh[0]);
+  __syncthreads();
+  if (b0 == 0u || b1 == (unsigned)(NBINS - 1)) return false;
+  klo = lo + ((b0 - 1u) << s);
+  khi = lo + (b1 << s);
+  return true;
+}
+
+template <bool VEC>
+__global__ void __launch_bounds__(MAD_SAMPLE_NT)
+mad_sample_kernel(const float2* __restrict__ vis, int64_t n_time, int64_t n_base, int n_chan, float sigma,
+                  int population, MadWin* __restrict__ win) {
+  __shared__ unsigned hist[2048];
+  __shared__ unsigned wsum[MAD_SAMPLE_NT / 64];
+  __shared__ unsigned long long sh[4];
+  __shared__ unsigned sub[64];
+  const Pop pop = make_pop(blockIdx.x, n_time, n_base, n_chan, population);
+  const int64_t n4 = pop.count / 4;
+  // strata of the population in order, four neighbouring elements of each,
+  // their place in it scattered so that no channel or integration is favoured
+  constexpr int STRATA = MAD_SAMPLE / 4, PER = MAD_SAMPLE_PER / 4;
+  float a[MAD_SAMPLE_PER];
+#pragma unroll
+  for (int q = 0; q < PER; ++q) {
+    const int64_t g = PER * (int64_t)threadIdx.x + q;
+    const int64_t g0 = g * n4 / STRATA, g1 = (g + 1) * n4 / STRATA;
+    const uint32_t h = ((uint32_t)g * 2654435761u) >> 8;
+    amp4<VEC>(vis, pop, 4 * (g0 + (int64_t)(h % (uint32_t)(g1 - g0))), a + 4 * q);
+  }
+  uint32_t k0 = 0u, k1 = 0u, e0 = 0u, e1 = 0u;
+  bool ok = sample_bounds(a, 0.f, hist, wsum, sh, sub, k0, k1);
+  const float lo = __uint_as_float(k0), hi = __uint_as_float(k1);
+  // the sample's deviations are from the centre of the median's window
+  if (ok) ok = sample_bounds(a, 0.5f * (lo + hi), hist, wsum, sh, sub, e0, e1);
+  if (threadIdx.x != 0) return;
+  MadWin w;
+  w.state = MAD_OPEN;
+  w.n_le = w.n_in = w.n_med = w.n_dev = w.n_thr = 0u;
+  if (ok) {
+    // a quarter of the median's window covers what the true median moves the
+    // MAD by
+    const double slack = 0.25 * ((double)hi - (double)lo) + 4.0 * MAD_EPS * hi;
+    w.lo = lo;
+    w.hi = hi;
+    w.dlo = (double)__uint_as_float(e0) - slack;
+    w.dhi = (double)__uint_as_float(e1) + slack;
+    const double c = (double)sigma * 1.4826;
+    const float t0 = (float)((lo + c * w.dlo) * (1.0 - 4.0 * MAD_EPS));
+    const float t1 = (float)((hi + c * w.dhi) * (1.0 + 4.0 * MAD_EPS));
+    const float l0 = (float)((double)lo - w.dhi), c0 = (float)((double)hi - w.dlo);
+    const float c1 = (float)((double)lo + w.dlo), r1 = (float)((double)hi + w.dhi);
+    // an upper or lower band can be empty (the MAD exceeds the median):
+    // negative bounds have no amplitude below them
+    auto sq = [](float v) -> float { return v < 0.f ? -1.f : v * v; };
+    w.r1 = r1;
+    w.q_lo = sq(lo);
+    w.q_hi = sq(hi);
+    w.q_l0 = sq(l0);
+    w.q_c0 = sq(c0);
+    w.q_c1 = sq(c1);
+    w.q_r1 = sq(r1);
+    w.q_t0 = sq(t0);
+    w.q_t1 = sq(t1);
+    // the windows in order, and every square a normal float32
+    if (c0 < lo && hi < c1 && lo > 1e-15f && r1 < 1e18f && t1 < 1e18f) w.state = MAD_SCAN;
+  }
+  win[blockIdx.x] = w;
+}
+
+constexpr int MAD_SCAN_MED = 384, MAD_SCAN_DEV = 512;  // per wave (256 taken at most between flushes)
+
+template <bool VEC>
+__global__ void __launch_bounds__(256)
+mad_scan_kernel(const float2* __restrict__ vis, int64_t n_time, int64_t n_base, int n_chan, int population,
+                int chunks, MadWin* __restrict__ win, float* __restrict__ lists, uint8_t* __restrict__ mask) {
+  constexpr int NT = 256, Q = 4, STEP = 4 * NT * Q;
+  // each wave keeps lists of its own: appending needs no atomics
+  __shared__ float2 med_l[NT / 64][MAD_SCAN_MED], dev_l[NT / 64][MAD_SCAN_DEV];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int64_t id = blockIdx.x / (unsigned)chunks;
+  const int64_t i0 = (int64_t)(blockIdx.x % (unsigned)chunks) * MAD_CHUNK;
+  MadWin* const w = win + id;
+  if (w->state != MAD_SCAN) return;
+  const Pop pop = make_pop(id, n_time, n_base, n_chan, population);
+  const int64_t n = pop.count;
+  float* const g_med = lists + id * mad_list_floats(n);
+  float* const g_dev = g_med + mad_cap_med(n);
+  float* const g_thr = g_dev + mad_cap_dev(n);
+  const float q_lo = w->q_lo, q_hi = w->q_hi, q_l0 = w->q_l0, q_c0 = w->q_c0, q_c1 = w->q_c1, q_r1 = w->q_r1;
+  const float q_t0 = mask ? w->q_t0 : __builtin_inff(), q_t1 = w->q_t1;
+  float2* const my_med = med_l[wave];
+  float2* const my_dev = dev_l[wave];
+  unsigned m = 0u, d = 0u, n_le = 0u, n_in = 0u;  // wave-uniform
+  // the lists' exact amplitudes to memory, in any order
+  auto flush = [&]() {
+    unsigned at = 0u;
+    if (lane < 2) at = atomicAdd(lane == 0 ? &w->n_med : &w->n_dev, lane == 0 ? m : d);
+    const unsigned at_m = __builtin_amdgcn_readlane(at, 0), at_d = __builtin_amdgcn_readlane(at, 1);
+    for (unsigned k = lane; k < m; k += 64)
+      if (at_m + k < (unsigned)mad_cap_med(n)) g_med[at_m + k] = amp_f32(my_med[k]);
+    for (unsigned k = lane; k < d; k += 64)
+      if (at_d + k < (unsigned)mad_cap_dev(n)) g_dev[at_d + k] = amp_f32(my_dev[k]);
+    m = 0u;
+    d = 0u;
+  };
+  const unsigned long long below = (1ull << lane) - 1ull;
+  auto append = [&](float2* list, unsigned& count, unsigned long long hit, float2 v) {
+    if (hit == 0ull) return;
+    if ((hit >> lane) & 1ull) list[count + (unsigned)__popcll(hit & below)] = v;
+    count += (unsigned)__popcll(hit);
+  };
+  const int64_t end = i0 + MAD_CHUNK < n ? i0 + MAD_CHUNK : n;
+  for (int64_t b0 = i0; b0 < end; b0 += STEP) {
+    float2 v[Q][4];
+#pragma unroll
+    for (int q = 0; q < Q; ++q) {
+      const int64_t i = b0 + 4 * (q * NT + (int)threadIdx.x);
+      if (VEC) {  // n is a multiple of four
+        float4 x = make_float4(0.f, 0.f, 0.f, 0.f), y = x;
+        if (i < n) {
+          const float4* p = reinterpret_cast<const float4*>(vis + pop.off(i));
+          x = p[0];
+          y = p[1];
+        }
+        v[q][0] = make_float2(x.x, x.y), v[q][1] = make_float2(x.z, x.w);
+        v[q][2] = make_float2(y.x, y.y), v[q][3] = make_float2(y.z, y.w);
+      } else {
+#pragma unroll
+        for (int j = 0; j < 4; ++j) v[q][j] = i + j < n ? vis[pop.off(i + j)] : make_float2(0.f, 0.f);
+      }
+    }
+#pragma unroll
+    for (int q = 0; q < Q; ++q) {
+      const int64_t i = b0 + 4 * (q * NT + (int)threadIdx.x);
+      if (m > MAD_SCAN_MED - 4 * 64 || d > MAD_SCAN_DEV - 4 * 64) flush();
+      uint32_t flags = 0u;
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        const float2 z = v[q][j];
+        const float sq = z.x * z.x + z.y * z.y;
+        // tests that a NaN passes: it stands above every amplitude
+        const bool in = i + j < n;
+        const unsigned long long live = __ballot(in);
+        const unsigned long long p_l0 = __ballot(!(sq < q_l0)), p_c0 = __ballot(!(sq < q_c0));
+        const unsigned long long p_lo = __ballot(!(sq <= q_lo)), p_hi = __ballot(!(sq <= q_hi));
+        const unsigned long long p_c1 = __ballot(!(sq <= q_c1)), p_r1 = __ballot(!(sq <= q_r1));
+        n_le += (unsigned)__popcll(live & ~p_lo);
+        n_in += (unsigned)__popcll(live & p_c0 & ~p_c1);
+        append(my_med, m, live & p_lo & ~p_hi, z);
+        append(my_dev, d, live & ((p_l0 & ~p_c0) | (p_c1 & ~p_r1)), z);
+        if (__ballot(!(sq <= q_t0)) != 0ull) {
+          if (sq > q_t1) flags |= 1u << (8 * j);
+          else if (mask && in && !(sq <= q_t0)) {
+            const unsigned k = atomicAdd(&w->n_thr, 1u);
+            if (k < (unsigned)mad_cap_thr(n)) {
+              g_thr[2 * (int64_t)k] = __uint_as_float((uint32_t)(i + j));
+              g_thr[2 * (int64_t)k + 1] = amp_f32(z);
+            }
+          }
+        }
+      }
+      if (mask) {
+        if (VEC) {
+          if (i < n) *reinterpret_cast<uint32_t*>(mask + pop.off(i)) = flags;
+        } else {
+#pragma unroll
+          for (int j = 0; j < 4; ++j)
+            if (i + j < n) mask[pop.off(i + j)] = (uint8_t)(flags >> (8 * j));
+        }
+      }
+    }
+  }
+  flush();
+  if (lane < 2) atomicAdd(lane == 0 ? &w->n_le : &w->n_in, lane == 0 ? n_le : n_in);
+}
+
+constexpr int MAD_FINISH_NT = 512;
+constexpr int MAD_FINISH_COMP = 8192;
+
+__global__ void __launch_bounds__(MAD_FINISH_NT)
+mad_finish_kernel(int64_t n_time, int64_t n_base, int n_chan, float sigma, int population,
+                  MadWin* __restrict__ win, const float* __restrict__ lists, uint8_t* __restrict__ mask,
+                  double* __restrict__ thresh, double* __restrict__ stats) {
+  constexpr int NT = MAD_FINISH_NT, DB = 11;
+  __shared__ unsigned hist[1 << DB];
+  __shared__ unsigned wsum[NT / 64];
+  __shared__ unsigned long long sh[4];
+  __shared__ unsigned long long red[2 * (NT / 64)];
+  __shared__ unsigned long long cand[SEL_CAND];
+  __shared__ unsigned ncand;
+  __shared__ float comp[MAD_FINISH_COMP];
+  const SelScratch sc{hist, wsum, sh, red, cand, &ncand, comp, MAD_FINISH_COMP};
+  MadWin* const w = win + blockIdx.x;
+  auto uni = [](uint32_t v) -> uint32_t { return (uint32_t)__builtin_amdgcn_readfirstlane((int)v); };
+  if (uni((uint32_t)w->state) != MAD_SCAN) return;
+  const Pop pop = make_pop(blockIdx.x, n_time, n_base, n_chan, population);
+  const int64_t n = pop.count;
+  const float* const g_med = lists + (int64_t)blockIdx.x * mad_list_floats(n);
+  const float* const g_dev = g_med + mad_cap_med(n);
+  const float* const g_thr = g_dev + mad_cap_dev(n);
+  const int64_t n_med = uni(w->n_med), n_dev = uni(w->n_dev), n_thr = uni(w->n_thr);
+  if (n_med > mad_cap_med(n) || n_dev > mad_cap_dev(n) || n_thr > mad_cap_thr(n)) return;
+  const int64_t k1 = (n - 1) / 2, k2 = n / 2;
+  const bool two = k2 != k1;
+  // the median among the keys of its window
+  const int64_t km = k1 - (int64_t)uni(w->n_le);
+  if (km < 0 || km + (k2 - k1) >= n_med) return;
+  auto aval = [&](int64_t i) -> float { return g_med[i]; };
+  auto akeyof = [](float a) -> uint32_t { return __float_as_uint(a); };
+  auto akey = [&](int64_t i) -> uint32_t { return __float_as_uint(g_med[i]); };
+  uint32_t a1 = 0u, a2 = 0u;
+  bool has2;
+  if (n_med < 64 || !window_select<NT, (1 << DB), uint32_t>(n_med, km, two, aval, akeyof, sc, a1, a2, has2))
+    a1 = radix_select<NT, DB, uint32_t>(n_med, km, 0u, __float_as_uint(w->r1), aval, akeyof, sc, two, a2, has2);
+  if (!two) a2 = a1;
+  else if (!has2) a2 = next_rank<NT, uint32_t>(n_med, km, a1, akey, red);
+  a1 = uni(a1);
+  a2 = uni(a2);
+  const double v1 = (double)__uint_as_float(a1), v2 = (double)__uint_as_float(a2);
+  if (!(v1 > w->lo * (1.0 + MAD_EPS) && v2 < w->hi * (1.0 - MAD_EPS))) return;
+  const double med = (v1 + v2) / 2.0;
+  // the MAD among the deviations that can reach it
+  const int64_t kd = k1 - (int64_t)uni(w->n_in);
+  if (kd < 0 || kd + (k2 - k1) >= n_dev) return;
+  auto dval = [&](int64_t i) -> float { return g_dev[i]; };
+  auto dkeyof = [&](float a) -> uint64_t { return (uint64_t)__double_as_longlong(fabs((double)a - med)); };
+  auto dkey = [&](int64_t i) -> uint64_t { return dkeyof(g_dev[i]); };
+  // a band amplitude is at most r1 (1 + MAD_EPS), and a deviation no larger
+  const uint64_t dmax = (uint64_t)__double_as_longlong(2.0 * (double)w->r1);
+  uint64_t d1 = 0ull, d2 = 0ull;
+  if (n_dev < 64 || !window_select<NT, (1 << DB), uint64_t>(n_dev, kd, two, dval, dkeyof, sc, d1, d2, has2))
+    d1 = radix_select<NT, DB, uint64_t>(n_dev, kd, 0ull, dmax, dval, dkeyof, sc, two, d2, has2);
+  if (!two) d2 = d1;
+  else if (!has2) d2 = next_rank<NT, uint64_t>(n_dev, kd, d1, dkey, red);
+  d1 = (uint64_t)rfl64((int64_t)d1);
+  d2 = (uint64_t)rfl64((int64_t)d2);
+  const double m1 = __longlong_as_double((long long)d1), m2 = __longlong_as_double((long long)d2);
+  const double eps = 2.0 * MAD_EPS * (double)w->r1;
+  if (!(m1 > w->dlo + eps && m2 < w->dhi - eps)) return;
+  const double madv = (m1 + m2) / 2.0;
+  const double c = (double)sigma * 1.4826;
+  const double T = med + c * madv;
+  if (mask)
+    for (int64_t k = threadIdx.x; k < n_thr; k += NT)
+      mask[pop.off((int64_t)__float_as_uint(g_thr[2 * k]))] = (double)g_thr[2 * k + 1] > T ? 1 : 0;
+  if (threadIdx.x == 0) {
+    w->state = MAD_DONE;
+    if (thresh) thresh[blockIdx.x] = T;
+    if (stats) {
+      stats[2 * (int64_t)blockIdx.x] = med;
+      stats[2 * (int64_t)blockIdx.x + 1] = madv;
+    }
+  }
+}
+
 template <int NT, int DB>
 __global__ void __launch_bounds__(NT)
 mad_kernel(const float2* __restrict__ vis, int64_t n_time, int64_t n_base, int n_chan, float sigma,
            int population, int64_t cap, int64_t comp_cap, const float* __restrict__ gamp,
-           uint8_t* __restrict__ mask, double* __restrict__ thresh, double* __restrict__ stats) {
+           const MadWin* __restrict__ done, uint8_t* __restrict__ mask, double* __restrict__ thresh,
+           double* __restrict__ stats) {
+  if (done && __builtin_amdgcn_readfirstlane(done[blockIdx.x].state) == MAD_DONE) return;
   __shared__ unsigned hist[1 << DB];
   __shared__ unsigned wsum[NT / 64];
   __shared__ unsigned long long sh[4];
@@ -761,9 +1140,20 @@ constexpr int64_t MAD_CAP_SMALL = 2048;
 constexpr int64_t MAD_LDS_FLOATS = 38400;  // dynamic LDS of the 1024-thread kernel: cache + compaction
 constexpr int64_t MAD_COMP_MAX = 32768;
 
+// The one-pass route takes populations of contiguous rows (all but the
+// per-channel ones) that do not fit the LDS of one workgroup.  Below, mad_kernel
+// alone takes 44 us for ten populations of 32768 with their amplitude pass
+// (its selection passes read LDS), the three steps and the check 59 us.
+bool mad_scans(int64_t npop, int64_t count, int population) {
+  return population != 1 && count > MAD_CAP_BIG && count <= 0x7fffffffLL &&
+         npop * ((count + MAD_CHUNK - 1) / MAD_CHUNK) <= 0x7fffffffLL;
+}
+
 int64_t mad_scratch_floats(int64_t n_time, int64_t n_base, int n_chan, int population) {
   const int64_t npop = population == 0 ? n_base : population == 1 ? n_base * n_chan : n_time * n_base;
   const int64_t count = population == 0 ? n_time * n_chan : population == 1 ? n_time : n_chan;
+  if (mad_scans(npop, count, population))
+    return npop * ((int64_t)(sizeof(MadWin) / sizeof(float)) + mad_list_floats(count));
   return count > MAD_CAP_SMALL ? npop * count : 0;
 }
 
@@ -776,8 +1166,26 @@ hipError_t launch_mad(const float2* vis, int64_t n_time, int64_t n_base, int n_c
   if (count <= MAD_CAP_SMALL) {
     const size_t lds = (size_t)count * sizeof(float);
     return launch(mad_kernel<64, 8>, dim3((unsigned)npop), dim3(64), lds, s, vis, n_time, n_base, n_chan, sigma,
-                  population, MAD_CAP_SMALL, (int64_t)0, nullptr, mask, thresh, stats);
+                  population, MAD_CAP_SMALL, (int64_t)0, nullptr, nullptr, mask, thresh, stats);
   } else {
+    MadWin* win = nullptr;
+    if (amp_scratch && mad_scans(npop, count, population)) {
+      win = reinterpret_cast<MadWin*>(amp_scratch);
+      float* const lists = reinterpret_cast<float*>(win + npop);
+      const bool vec = n_chan % 4 == 0 && (reinterpret_cast<uintptr_t>(vis) & 15u) == 0 &&
+                       (reinterpret_cast<uintptr_t>(mask) & 3u) == 0;
+      const int chunks = (int)((count + MAD_CHUNK - 1) / MAD_CHUNK);
+      hipError_t e = launch(vec ? mad_sample_kernel<true> : mad_sample_kernel<false>, dim3((unsigned)npop),
+                            dim3(MAD_SAMPLE_NT), 0, s, vis, n_time, n_base, n_chan, sigma, population, win);
+      if (e == hipSuccess)
+        e = launch(vec ? mad_scan_kernel<true> : mad_scan_kernel<false>, dim3((unsigned)(npop * chunks)),
+                   dim3(256), 0, s, vis, n_time, n_base, n_chan, population, chunks, win, lists, mask);
+      if (e == hipSuccess)
+        e = launch(mad_finish_kernel, dim3((unsigned)npop), dim3(MAD_FINISH_NT), 0, s, n_time, n_base, n_chan, sigma,
+                   population, win, lists, mask, thresh, stats);
+      if (e != hipSuccess) return e;
+      amp_scratch = nullptr;
+    }
     const int64_t cap = count <= MAD_CAP_BIG ? count : 0;
     const float* gamp = nullptr;
     if (amp_scratch) {
@@ -809,7 +1217,7 @@ hipError_t launch_mad(const float2* vis, int64_t n_time, int64_t n_base, int n_c
                                        hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
     if (e != hipSuccess) return e;
     return launch(mad_kernel<1024, 11>, dim3((unsigned)npop), dim3(1024), lds, s, vis, n_time, n_base, n_chan,
-                  sigma, population, cap, comp_cap, gamp, mask, thresh, stats);
+                  sigma, population, cap, comp_cap, gamp, win, mask, thresh, stats);
   }
 }
 

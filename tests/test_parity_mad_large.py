@@ -1,0 +1,84 @@
+"""GPU parity: MAD of large populations, whose windows come from a sample.
+
+Masks and thresholds are bit-exact with the oracle at the edges of the route
+(36864 elements), with rows that do or do not divide into fours, unaligned
+planes, both contiguous populations, and on inputs where a sample misleads or
+the lists overflow, so that the selection from the start takes over.
+"""
+
+import numpy as np
+import pytest
+
+from oracle import mad
+
+pytestmark = pytest.mark.gpu
+
+
+def _check(qc, v, sigma, pop, off=0):
+    import torch
+    m_ref, T_ref = mad.mad_flag(v, sigma, pop)
+    buf = torch.zeros(v.size + off, dtype=torch.complex64, device="cuda")
+    d = buf[off:].view(v.shape)
+    d.copy_(torch.from_numpy(v).cuda())
+    m, T = qc.mad_flag(d, sigma, pop)
+    assert np.array_equal(T.cpu().numpy(), T_ref)
+    assert np.array_equal(m.cpu().numpy(), m_ref)
+
+
+def _noise(shape, seed):
+    rng = np.random.default_rng(seed)
+    return (rng.normal(size=shape) + 1j * rng.normal(size=shape)).astype(np.complex64)
+
+
+@pytest.mark.parametrize("shape,pop,off", [
+    ((1, 2, 36864), 0, 0), ((1, 3, 36868), 0, 0), ((1, 2, 36865), 0, 0), ((39, 2, 1001), 0, 0),
+    ((20, 3, 2048), 0, 1), ((3, 2, 40000), 2, 0), ((2, 2, 36870), 2, 1), ((5, 1, 98304), 0, 0),
+])
+@pytest.mark.parametrize("sigma", [0.0, 3.0])
+def test_large_populations(qc, shape, pop, off, sigma):
+    _check(qc, _noise(shape, sum(shape)), sigma, pop, off)
+
+
+def test_uneven_plane(qc):
+    """A steep bandpass, a drifting gain, strong lines and bursts: the sample
+    sees every channel and integration alike."""
+    shape = (128, 2, 2048)
+    rng = np.random.default_rng(5)
+    v = _noise(shape, 6) * (0.01 + np.sin(np.linspace(0, 3.1, 2048))) * np.linspace(0.2, 5, 128)[:, None, None]
+    v *= 1 + 40 * (rng.uniform(size=2048) < 0.03)
+    v *= 1 + 20 * (rng.uniform(size=(128, 1, 1)) < 0.05)
+    _check(qc, v.astype(np.complex64), 5.0, 0)
+
+
+@pytest.mark.parametrize("fill", ["zero", "mostly", "half", "blocks", "two"])
+def test_populations_a_sample_cannot_bound(qc, fill):
+    shape = (64, 3, 2048)
+    v = _noise(shape, 9)
+    if fill == "zero":
+        v[:, 1] = 0
+    elif fill == "mostly":
+        v[:48] = 0
+    elif fill == "half":
+        v[:32] = 0
+    elif fill == "blocks":  # one element of four carries the signal
+        v.reshape(64, 3, 512, 4)[..., 1:] *= np.float32(1e-3)
+    else:
+        v = np.where(np.arange(2048) % 2 == 0, np.complex64(3 + 4j), np.complex64(1)) * np.ones(shape, np.complex64)
+    _check(qc, v.astype(np.complex64), 5.0, 0)
+
+
+def test_not_finite_amplitudes(qc):
+    """Amplitudes that are no number order above infinity and are not flagged."""
+    import torch
+    v = _noise((24, 2, 2048), 3)
+    v[3, 0, ::7] = np.inf
+    w = v.copy()
+    w[5, 0, ::5] = np.nan
+    v[5, 0, ::5] = np.inf
+    with np.errstate(invalid="ignore"):
+        m_ref, T_ref = mad.mad_flag(v, 5.0, 0)
+    m_ref = np.array(m_ref)
+    m_ref[5, 0, ::5] = 0
+    m, T = qc.mad_flag(torch.from_numpy(w).cuda(), 5.0, 0)
+    assert np.array_equal(T.cpu().numpy(), T_ref)
+    assert np.array_equal(m.cpu().numpy(), m_ref)
