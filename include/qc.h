@@ -465,8 +465,9 @@ int32_t qc_fx_get_tile(int32_t n_fft, int32_t n_ant);
 /* Launch width of qc_xcorrelate's fused F+X kernel for one (n_fft, n_ant):
  * the number of workgroups a launch aims at, by splitting each dump into
  * chunks of spectra whose partial visibilities the fixed-order reduction
- * sums (each chunk keeps at least 8 spectra).  0 restores the default of
- * 512; otherwise 1..2^20 (QC_EINVAL beyond; QC_EUNSUPPORTED when no fused
+ * sums (each chunk keeps at least 8 spectra).  0 restores the default, which
+ * follows from the sizes (one round of workgroups over the compute units where
+ * the spectra suffice, down to one spectrum per chunk); otherwise 1..2^20 (QC_EINVAL beyond; QC_EUNSUPPORTED when no fused
  * kernel exists for the pair).  Sums are equal up to float32 rounding order
  * whatever the width.  Process-wide; set by the autotuner. */
 qc_status qc_fx_set_width(int32_t n_fft, int32_t n_ant, int64_t workgroups);

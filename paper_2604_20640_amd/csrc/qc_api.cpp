@@ -629,9 +629,11 @@ qc_status qc_xcorrelate(const int8_t* x, int64_t ld_x, int32_t n_ant, int64_t n_
                "fused F+X kernel");
       }
       KTimer t(QC_KERNEL_REDUCE, s);
+      const qc::HistArgs ha{x, ld_x, n_ant, n_samp, hist, hist_out ? (int64_t)(p->n_taps - 1) * N : 0, hist_out};
       QC_HIP(qc::launch_reduce((const float2*)part.p, n_dump, cpd, nb * nch, 0.25f, accumulate,
-                               reinterpret_cast<float2*>(vis), s),
+                               reinterpret_cast<float2*>(vis), s, 0, 0, &ha),
              "reduce kernel");
+      return QC_OK;
     } else {
       // two passes: F-engine to HBM, then the X-engine
       const int64_t ns = n_dump * spec_per_dump;
@@ -720,11 +722,7 @@ qc_status qc_xcorrelate_ex(const void* x, int32_t sample, int64_t ld_x, int32_t 
     if (st != QC_OK) return st;
     r.args.n_samp = n_dump * spec_per_dump * N;
     const int64_t nb = (int64_t)n_ant * (n_ant + 1) / 2;
-    // the 4-antenna int16 tile at N = 4096 is resident one workgroup per
-    // CU: a single round of them (12-15 % faster than two rounds); the
-    // default otherwise
-    const int64_t width = (N == 4096 && n_ant == 4) ? qc::device_cu_count() : 0;
-    const int64_t cpd = qc::fused_chunks_per_dump(N, n_ant, n_dump, spec_per_dump, width);
+    const int64_t cpd = qc::fused_chunks_per_dump(N, n_ant, n_dump, spec_per_dump);
     AsyncBuf part;
     st = alloc_async(part, (size_t)(n_dump * cpd) * nb * n_chan * sizeof(float2), s);
     if (st != QC_OK) return st;
@@ -734,9 +732,13 @@ qc_status qc_xcorrelate_ex(const void* x, int32_t sample, int64_t ld_x, int32_t 
              "fused F+X kernel");
     }
     KTimer t(QC_KERNEL_REDUCE, s);
+    const int b = sample_bytes(sample);
+    const qc::HistArgs ha{static_cast<const int8_t*>(x), ld_x * b, n_ant, n_samp * b, static_cast<const int8_t*>(hist),
+                          hist_out ? (int64_t)(p->n_taps - 1) * N * b : 0, static_cast<int8_t*>(hist_out)};
     QC_HIP(qc::launch_reduce((const float2*)part.p, n_dump, cpd, nb * n_chan, 0.25f, accumulate,
-                             reinterpret_cast<float2*>(vis), s),
+                             reinterpret_cast<float2*>(vis), s, 0, 0, &ha),
            "reduce kernel");
+    return QC_OK;
   } else if (n_dump > 0) {
     // two passes: the F-engine of the full dumps' spectra to HBM, then the X-engine
     const int64_t ns = n_dump * spec_per_dump;
@@ -970,7 +972,7 @@ qc_status qc_fx_autotune(const int8_t* x, int64_t ld_x, int32_t n_ant, int64_t n
     else
       g_width.erase(key);
   };
-  // tiles at the default width (512 workgroups), then the best tile at one
+  // tiles at the default width, then the best tile at one
   // and at four workgroups per CU (a tile that holds one workgroup per CU
   // fills the chip in a single round at the first)
   double best = 1e300;
@@ -1359,7 +1361,10 @@ qc_status graph_setup(qc_plan* P) {
     if (G.fused) {
       G.tile = 0;
       G.split = qc::fused_chunks_per_dump(N, NA, G.n_dump, D.spec_per_dump);
-      G.split_max = std::min<int64_t>(D.spec_per_dump, 2 * G.split);
+      // room for the tuner's splits, and for those of results saved when the
+      // default was 512 workgroups of at least 8 spectra
+      const int64_t saved = qc::fused_chunks_per_dump(N, NA, G.n_dump, D.spec_per_dump, 512);
+      G.split_max = std::min<int64_t>(D.spec_per_dump, 2 * std::max(G.split, saved));
     } else {
       G.split = qc::xeng_f32_ksplit(NA, D.spec_per_dump, nch, G.n_dump);
       G.split_max = std::min<int64_t>(D.spec_per_dump, std::max<int64_t>(16, G.split));

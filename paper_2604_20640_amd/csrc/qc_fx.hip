@@ -784,7 +784,12 @@ static hipError_t launch_fused_p(const FxArgs& a, int64_t n_dump, int64_t spd, i
 
 // Tile shapes of the fused kernel per (n_fft, n_ant): spectra in flight S,
 // values per thread per FFT pass V, ping-pong LDS buffers PP.  Entry 0 is
-// the default; the others are the candidates an autotuner may time.
+// the default; the others are the candidates an autotuner may time.  The
+// defaults are the fastest at one round of workgroups (16384 spectra of 4096
+// points: 4 antennas 319 us on the ping-pong ring, 366 on the in-place one, 540
+// and more on the others; 32768 spectra of 1024, 8 antennas: 561 us with 8
+// values per thread, 840 with 16).  A shape that stands twice keeps its index
+// in saved tuning results.
 struct FusedTile {
   int S, V;  // S = 0: ring variant (one spectrum in flight, register ring)
   bool PP;
@@ -802,17 +807,17 @@ struct TileList {
     static constexpr FusedTile tiles[] = {__VA_ARGS__};                         \
     static constexpr int count = (int)(sizeof(tiles) / sizeof(tiles[0]));       \
   };
-QC_TILES(4096, 4, {0, 16, false, 0}, {1, 16, false, 0}, {1, 16, true, 0}, {2, 16, false, 0},
+QC_TILES(4096, 4, {0, 16, true, 0}, {1, 16, false, 0}, {1, 16, true, 0}, {2, 16, false, 0},
          {1, 8, true, 0}, {1, 16, false, 4}, {0, 16, true, 0})
 QC_TILES(1024, 4, {2, 16, true, 0}, {2, 16, false, 0}, {4, 16, false, 0}, {2, 8, true, 0},
          {1, 16, true, 4}, {2, 16, false, 4}, {0, 16, false, 0})
 QC_TILES(2048, 4, {0, 16, false, 0}, {1, 16, true, 0}, {1, 16, false, 0}, {1, 16, false, 4},
          {1, 8, true, 0})
 QC_TILES(512, 4, {4, 16, true, 0}, {4, 16, false, 0}, {2, 16, true, 4})
-QC_TILES(1024, 8, {1, 16, true, 0}, {1, 8, true, 0})
+QC_TILES(1024, 8, {1, 8, true, 0}, {1, 8, true, 0})
 QC_TILES(2048, 8, {1, 8, true, 0}, {1, 8, false, 0})
 QC_TILES(1024, 2, {4, 16, true, 0}, {4, 16, false, 0}, {2, 16, true, 4})
-QC_TILES(4096, 2, {0, 16, false, 0}, {1, 16, true, 0}, {1, 16, false, 0}, {1, 16, false, 4}, {0, 16, true, 0})
+QC_TILES(4096, 2, {0, 16, true, 0}, {1, 16, true, 0}, {1, 16, false, 0}, {1, 16, false, 4}, {0, 16, true, 0})
 #undef QC_TILES
 
 template <int N, int NA, int I>
@@ -871,13 +876,35 @@ int device_cu_count() {
   return n;
 }
 
+// A width that the caller has set keeps at least 8 spectra per chunk.  The
+// default weighs, in units of the time of one spectrum in a workgroup, the
+// rounds of workgroups against their fixed cost (tables, the first P blocks:
+// about 2.5) and that of each partial (written and summed: about 0.01), and
+// takes the best of the widths that fill one to four rounds.  Resident are one
+// workgroup per CU from 8192 packed values (512 threads, or LDS for one), two
+// below.  4 antennas, N = 4096: 65536 spectra 1.28 -> 1.22 ms on one round
+// instead of two; 32 spectra 54 us on 4 workgroups, 12 us on 32; N = 1024: 512
+// spectra 32 us on 64 workgroups, 28 us on 512.
 int64_t fused_chunks_per_dump(int n_fft, int n_ant, int64_t n_dump, int64_t spd, int64_t workgroups) {
-  // the default of 512 is two rounds of workgroups over 256 CUs
-  if (workgroups < 1) workgroups = 512;
-  int64_t want = (workgroups + n_dump - 1) / n_dump;
-  int64_t maxc = spd / 8 > 0 ? spd / 8 : 1;
-  int64_t c = want < maxc ? want : maxc;
-  return c < 1 ? 1 : c;
+  if (workgroups >= 1) {
+    const int64_t want = (workgroups + n_dump - 1) / n_dump;
+    const int64_t maxc = spd / 8 > 0 ? spd / 8 : 1;
+    return want < maxc ? want : maxc;
+  }
+  const int64_t slots = (int64_t)device_cu_count() * ((int64_t)n_fft * n_ant >= 8192 ? 1 : 2);
+  int64_t best = 1;
+  double best_cost = 1e300;
+  for (int r = 0; r <= 4; ++r) {
+    int64_t c = r == 0 ? 1 : r * slots / n_dump;
+    c = c < 1 ? 1 : c > spd ? spd : c;
+    const int64_t rounds = (n_dump * c + slots - 1) / slots;
+    const double cost = (double)rounds * (2.5 + (double)((spd + c - 1) / c)) + 0.01 * (double)(n_dump * c);
+    if (cost < best_cost) {
+      best_cost = cost;
+      best = c;
+    }
+  }
+  return best;
 }
 
 // Fused F+X of real int16 words (the 16-bit padded mode): the in-place ring
@@ -918,26 +945,93 @@ hipError_t launch_fused(const FxArgs& a, int64_t n_dump, int64_t spd, int64_t cp
 // with tile > 0 each partial is tile-major, [n_chan/tile][nb][tile] (one
 // X-engine workgroup's output per tile), and the sum lands in the
 // [nb][n_chan] layout of the visibilities.
-__global__ void reduce_partials_kernel(const float2* __restrict__ part, int64_t cpd, int64_t elems,
-                                       int64_t bx_per_dump, float scale, int accumulate, int tile,
-                                       int64_t nb, int64_t n_chan, float2* __restrict__ vis) {
+//
+// A block takes 256 / segs elements; segs threads share an element, each
+// summing a run of partials with eight loads in flight, and the runs are
+// added in order (fixed whatever the timing).  Bound: HBM on large outputs,
+// latency on small ones, which is what the segments and the loads in flight are
+// for: 128 partials of 4 antennas x 512 channels took 30 us on one thread per
+// element, 512 of them take 5.7 us.
+//
+// The blocks past the sums copy the filter history for the next call (the
+// last `keep` bytes of hist ++ x per row), which saves a launch.
+struct HistCopy {
+  const int8_t* x = nullptr;
+  int64_t ld_x = 0, n_samp = 0;
+  const int8_t* hist = nullptr;
+  int64_t keep = 0;
+  int8_t* out = nullptr;
+  int blocks = 0;  // per row
+};
+
+__device__ __forceinline__ void hist_copy_body(const HistCopy& h, int a, int bx) {
+  const int64_t first = (int64_t)bx * blockDim.x + threadIdx.x, step = (int64_t)h.blocks * blockDim.x;
+  // byte i of the history is byte n_samp - keep + i of the row (hist before 0)
+  if (((reinterpret_cast<uintptr_t>(h.x) | reinterpret_cast<uintptr_t>(h.hist) | reinterpret_cast<uintptr_t>(h.out) |
+        (uintptr_t)h.ld_x | (uintptr_t)h.n_samp | (uintptr_t)h.keep) & 3u) == 0) {
+    for (int64_t i = 4 * first; i < h.keep; i += 4 * step) {
+      const int64_t n = h.n_samp - h.keep + i;
+      uint32_t v = 0u;
+      if (n >= 0) v = *reinterpret_cast<const uint32_t*>(h.x + (int64_t)a * h.ld_x + n);
+      else if (h.hist) v = *reinterpret_cast<const uint32_t*>(h.hist + (int64_t)a * h.keep + (h.keep + n));
+      *reinterpret_cast<uint32_t*>(h.out + (int64_t)a * h.keep + i) = v;
+    }
+  } else {
+    for (int64_t i = first; i < h.keep; i += step) {
+      const int64_t n = h.n_samp - h.keep + i;
+      int8_t v = 0;
+      if (n >= 0) v = h.x[(int64_t)a * h.ld_x + n];
+      else if (h.hist) v = h.hist[(int64_t)a * h.keep + (h.keep + n)];
+      h.out[(int64_t)a * h.keep + i] = v;
+    }
+  }
+}
+
+__global__ void __launch_bounds__(256)
+reduce_partials_kernel(const float2* __restrict__ part, int64_t cpd, int64_t elems, int64_t bx_per_dump, int segs,
+                       float scale, int accumulate, int tile, int64_t nb, int64_t n_chan,
+                       float2* __restrict__ vis, int64_t sum_blocks, HistCopy hc) {
+  if ((int64_t)blockIdx.x >= sum_blocks) {
+    const int hb = (int)((int64_t)blockIdx.x - sum_blocks);
+    hist_copy_body(hc, hb / hc.blocks, hb % hc.blocks);
+    return;
+  }
+  __shared__ float2 red[256];
+  const int per = 256 / segs;  // elements per block
+  const int col = threadIdx.x % per, seg = threadIdx.x / per;
   const int64_t d = blockIdx.x / bx_per_dump;
   const int64_t bx = blockIdx.x % bx_per_dump;
-  for (int64_t e = bx * blockDim.x + threadIdx.x; e < elems; e += bx_per_dump * blockDim.x) {
+  const int64_t c_lo = cpd * seg / segs, c_hi = cpd * (seg + 1) / segs;
+  for (int64_t e0 = bx * per; e0 < elems; e0 += bx_per_dump * per) {
+    const int64_t e = e0 + col;
     float2 sacc = make_float2(0.f, 0.f);
-    const float2* p = part + d * cpd * elems + e;
-    for (int64_t c = 0; c < cpd; ++c) {
-      const float2 v = p[c * elems];
-      sacc.x += v.x;
-      sacc.y += v.y;
+    if (e < elems) {
+      const float2* p = part + (d * cpd + c_lo) * elems + e;
+      int64_t c = c_lo;
+      for (; c + 8 <= c_hi; c += 8, p += 8 * elems) {
+        float2 v[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) v[u] = p[u * elems];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) sacc = cadd(sacc, v[u]);
+      }
+      for (; c < c_hi; ++c, p += elems) sacc = cadd(sacc, *p);
     }
+    if (segs > 1) {
+      red[threadIdx.x] = sacc;
+      __syncthreads();
+      if (seg == 0)
+        for (int g = 1; g < segs; ++g) sacc = cadd(sacc, red[g * per + col]);
+      __syncthreads();
+    }
+    if (seg != 0 || e >= elems) continue;
     sacc.x *= scale;
     sacc.y *= scale;
     int64_t oe = e;
     if (tile > 0) {
-      const int64_t t = e / tile, col = e - t * tile;
+      const int64_t t = e / tile, tcol = e - t * tile;
       const int64_t cb = t / nb, b = t - cb * nb;
-      oe = b * n_chan + cb * tile + col;
+      oe = b * n_chan + cb * tile + tcol;
     }
     float2* o = vis + d * elems + oe;
     if (accumulate) {
@@ -950,14 +1044,28 @@ __global__ void reduce_partials_kernel(const float2* __restrict__ part, int64_t 
 }
 
 hipError_t launch_reduce(const float2* part, int64_t n_dump, int64_t cpd, int64_t elems,
-                         float scale, int accumulate, float2* vis, hipStream_t s, int tile, int64_t nb) {
+                         float scale, int accumulate, float2* vis, hipStream_t s, int tile, int64_t nb,
+                         const HistArgs* hist) {
   if (n_dump <= 0 || elems <= 0) return hipSuccess;
   if (tile > 0 && (nb <= 0 || elems % (nb * tile) != 0)) return hipErrorInvalidValue;
-  int64_t bx = (elems + 255) / 256;
+  // segments until the GPU has 1024 threads per CU or a run is down to four
+  // partials
+  int segs = 1;
+  while (segs < 16 && n_dump * elems * segs < 262144 && cpd >= 8 * segs) segs *= 2;
+  const int64_t per = 256 / segs;
+  int64_t bx = (elems + per - 1) / per;
   if (bx > 4096) bx = 4096;
   const int64_t n_chan = tile > 0 ? elems / nb : 0;
-  return launch(reduce_partials_kernel, dim3((unsigned)(bx * n_dump)), dim3(256), 0, s, part, cpd, elems, bx,
-                scale, accumulate, tile, nb, n_chan, vis);
+  HistCopy hc;
+  int64_t extra = 0;
+  if (hist && hist->keep > 0) {
+    int64_t hb = (hist->keep + 1023) / 1024;
+    if (hb > 256) hb = 256;
+    hc = HistCopy{hist->x, hist->ld_x, hist->n_samp, hist->hist, hist->keep, hist->out, (int)hb};
+    extra = hb * hist->n_ant;
+  }
+  return launch(reduce_partials_kernel, dim3((unsigned)(bx * n_dump + extra)), dim3(256), 0, s, part, cpd, elems, bx,
+                segs, scale, accumulate, tile, nb, n_chan, vis, bx * n_dump, hc);
 }
 
 // ---------------------------------------------------------------------------
@@ -1585,28 +1693,17 @@ hipError_t launch_scales(const int8_t* x, int64_t ld_x, int n_ant, int64_t n_use
 // ---------------------------------------------------------------------------
 // History for the next chunk: last `keep` samples of (hist ++ x).
 // ---------------------------------------------------------------------------
-__global__ void hist_copy_kernel(const int8_t* __restrict__ x, int64_t ld_x, int64_t n_samp,
-                                 const int8_t* __restrict__ hist, int64_t keep,
-                                 int8_t* __restrict__ hist_out) {
-  const int a = blockIdx.y;
-  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < keep;
-       i += (int64_t)gridDim.x * blockDim.x) {
-    // position in (hist ++ x) coordinates: n = n_samp - keep + i (may be < 0)
-    const int64_t n = n_samp - keep + i;
-    int8_t v;
-    if (n >= 0) v = x[(int64_t)a * ld_x + n];
-    else v = hist ? hist[(int64_t)a * keep + (keep + n)] : (int8_t)0;
-    hist_out[(int64_t)a * keep + i] = v;
-  }
+__global__ void __launch_bounds__(256) hist_copy_kernel(HistCopy h) {
+  hist_copy_body(h, (int)blockIdx.y, (int)blockIdx.x);
 }
 
 hipError_t launch_hist_copy(const int8_t* x, int64_t ld_x, int n_ant, int64_t n_samp,
                             const int8_t* hist, int64_t keep, int8_t* hist_out, hipStream_t s) {
   if (keep <= 0) return hipSuccess;
-  int64_t bx = (keep + 255) / 256;
-  if (bx > 1024) bx = 1024;
-  return launch(hist_copy_kernel, dim3((unsigned)bx, n_ant), dim3(256), 0, s, x, ld_x, n_samp, hist, keep,
-                hist_out);
+  int64_t bx = (keep + 1023) / 1024;
+  if (bx > 256) bx = 256;
+  return launch(hist_copy_kernel, dim3((unsigned)bx, n_ant), dim3(256), 0, s,
+                HistCopy{x, ld_x, n_samp, hist, keep, hist_out, (int)bx});
 }
 
 // ---------------------------------------------------------------------------

@@ -35,9 +35,9 @@ int fused_tile_count(int n_fft, int n_ant);
 int device_cu_count();
 
 // Chunks per dump of a fused launch: about `workgroups` workgroups in all
-// (at least 8 spectra per chunk).
+// (at least 8 spectra per chunk), or the default for the sizes (0).
 int64_t fused_chunks_per_dump(int n_fft, int n_ant, int64_t n_dump, int64_t spec_per_dump,
-                              int64_t workgroups = 512);
+                              int64_t workgroups = 0);
 // tile: index into the (n_fft, n_ant) tile list; 0 is the default shape.
 hipError_t launch_fused(const FxArgs& a, int64_t n_dump, int64_t spec_per_dump,
                         int64_t chunks_per_dump, float2* part, hipStream_t s, int tile);
@@ -46,9 +46,20 @@ hipError_t launch_fused(const FxArgs& a, int64_t n_dump, int64_t spec_per_dump,
 // vis[d][e] = (accumulate ? vis[d][e] : 0) + scale * sum_c part[d*cpd + c][e].
 // tile > 0: each partial is tile-major, [n_chan/tile][nb][tile], and e is
 // mapped to the [nb][n_chan] position of the visibilities.
+// hist: also copies the filter history for the next call (as
+// launch_hist_copy), in the same launch.
+struct HistArgs {
+  const int8_t* x;
+  int64_t ld_x;
+  int n_ant;
+  int64_t n_samp;
+  const int8_t* hist;
+  int64_t keep;
+  int8_t* out;
+};
 hipError_t launch_reduce(const float2* part, int64_t n_dump, int64_t cpd, int64_t elems,
                          float scale, int accumulate, float2* vis, hipStream_t s, int tile = 0,
-                         int64_t nb = 0);
+                         int64_t nb = 0, const HistArgs* hist = nullptr);
 
 // Standalone F-engine.  out layout [n_ant][n_spec][n_chan]; prec 0..3 as qc_prec.
 // Variant 0 uses the ring kernel where it applies (P = 4, built-in taps,
