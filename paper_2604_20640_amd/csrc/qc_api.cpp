@@ -716,27 +716,30 @@ qc_status qc_xcorrelate_ex(const void* x, int32_t sample, int64_t ld_x, int32_t 
   hipStream_t s = reinterpret_cast<hipStream_t>(stream);
   if (n_dump > 0 && x_prec == QC_F32 &&
       qc::fused_words_supported(sample, N, n_ant, p->n_taps, p->taps == nullptr)) {
-    // real int16 words at a fused ring shape: F+X in one pass, as for int8
+    // words of a fused shape: F+X in one pass, as for int8
     Resolved r;
     st = resolve(static_cast<const int8_t*>(x), ld_x, n_ant, n_samp, p, static_cast<const int8_t*>(hist), &r);
     if (st != QC_OK) return st;
     r.args.n_samp = n_dump * spec_per_dump * N;
     const int64_t nb = (int64_t)n_ant * (n_ant + 1) / 2;
-    const int64_t cpd = qc::fused_chunks_per_dump(N, n_ant, n_dump, spec_per_dump);
+    const int64_t cpd = qc::fused_words_chunks(sample, N, n_ant, n_dump, spec_per_dump);
+    float2* twp = nullptr;
+    st = get_pass_twiddles(qc::fused_words_transform(sample, N, n_ant), &twp);
+    if (st != QC_OK) return st;
     AsyncBuf part;
     st = alloc_async(part, (size_t)(n_dump * cpd) * nb * n_chan * sizeof(float2), s);
     if (st != QC_OK) return st;
     {
       KTimer t(QC_KERNEL_FX_FUSED, s);
-      QC_HIP(qc::launch_fused_words(r.args, sample, n_dump, spec_per_dump, cpd, (float2*)part.p, s),
+      QC_HIP(qc::launch_fused_words(r.args, sample, n_dump, spec_per_dump, cpd, (float2*)part.p, s, twp),
              "fused F+X kernel");
     }
     KTimer t(QC_KERNEL_REDUCE, s);
     const int b = sample_bytes(sample);
     const qc::HistArgs ha{static_cast<const int8_t*>(x), ld_x * b, n_ant, n_samp * b, static_cast<const int8_t*>(hist),
                           hist_out ? (int64_t)(p->n_taps - 1) * N * b : 0, static_cast<int8_t*>(hist_out)};
-    QC_HIP(qc::launch_reduce((const float2*)part.p, n_dump, cpd, nb * n_chan, 0.25f, accumulate,
-                             reinterpret_cast<float2*>(vis), s, 0, 0, &ha),
+    QC_HIP(qc::launch_reduce((const float2*)part.p, n_dump, cpd, nb * n_chan, sample_complex(sample) ? 1.0f : 0.25f,
+                             accumulate, reinterpret_cast<float2*>(vis), s, 0, 0, &ha),
            "reduce kernel");
     return QC_OK;
   } else if (n_dump > 0) {

@@ -116,6 +116,18 @@ constexpr int ilog2(int n) { return n <= 1 ? 0 : 1 + ilog2(n / 2); }
 __device__ __forceinline__ int lds_pad(int i) { return i + (i >> 4); }
 __host__ __device__ constexpr int lds_padded_size(int n) { return n + (n >> 4) + 1; }
 
+// Values at a constant step of a multiple of 16 (or within one group of 16)
+// lie at a constant step in the padded buffer too.  Written as base plus
+// constant, a pass needs one address register and immediate offsets: left to
+// lds_pad(base + r STEP), the compiler forms every address by itself and either
+// recomputes them (300 instructions a spectrum in the fused tiles) or keeps
+// them over the caller's loop.
+template <int STEP>
+__device__ __forceinline__ int lds_at(int base, int padded, int r) {
+  if constexpr (STEP % 16 == 0) return padded + r * (STEP + STEP / 16);
+  else return lds_pad(base + r * STEP);
+}
+
 // One Stockham pass of radix R over NFFT transforms of length N stored back
 // to back (padded).  NT threads each hold V complex values (V/R butterflies).
 // With INPLACE the pass reads and writes the same buffer, so a barrier
@@ -169,8 +181,9 @@ __device__ __forceinline__ void stockham_pass(const float2* src, float2* dst,
   for (int i = 0; i < Q; ++i) {
     const int q = tid + i * NT;
     const int f = q / NB, j = q % NB;
+    const int p0 = lds_pad(f * N + j);
 #pragma unroll
-    for (int r = 0; r < R; ++r) v[i][r] = src[lds_pad(f * N + j + r * NB)];
+    for (int r = 0; r < R; ++r) v[i][r] = src[lds_at<NB>(f * N + j, p0, r)];
   }
   if constexpr (INPLACE) __syncthreads();
 #pragma unroll
@@ -196,9 +209,11 @@ __device__ __forceinline__ void stockham_pass(const float2* src, float2* dst,
         v[i][r] = cmul(v[i][r], TWL ? tw[(NS - 1) + (r - 1) * NS + jm] : tw[jm * r * STEP]);
     }
     dft_r<R>(v[i]);
-    const int k = (j / NS) * NS * R + jm;
+    const int k = (j / NS) * NS * R + jm, p0 = lds_pad(f * N + k);
+    // the first pass of radix 16 writes whole groups of 16
 #pragma unroll
-    for (int r = 0; r < R; ++r) dst[lds_pad(f * N + k + r * NS)] = v[i][r];
+    for (int r = 0; r < R; ++r)
+      dst[NS == 1 && R == 16 ? p0 + r : lds_at<NS>(f * N + k, p0, r)] = v[i][r];
   }
   __syncthreads();
 }

@@ -95,6 +95,36 @@ __device__ __forceinline__ void pin_word(uint4& w) {
   asm volatile("" : "+v"(w.x), "+v"(w.y), "+v"(w.z), "+v"(w.w));
 }
 
+// 8-bit ring words as halves: four real samples -> two half2, four complex
+// samples (I, Q) -> four half2; other words unchanged.
+__device__ __forceinline__ uint32_t half2_of(uint32_t w, int lo_byte) {
+  const __half a = __short2half_rn((short)(int8_t)((w >> (8 * lo_byte)) & 0xffu));
+  const __half b = __short2half_rn((short)(int8_t)((w >> (8 * lo_byte + 8)) & 0xffu));
+  const __half2 p = __halves2half2(a, b);
+  return *reinterpret_cast<const uint32_t*>(&p);
+}
+template <int ST, bool HALF, class T>
+__device__ __forceinline__ auto ring_word(const T& w) {
+  if constexpr (!HALF) {
+    return w;
+  } else if constexpr (ST == 0) {
+    return make_uint2(half2_of(w, 0), half2_of(w, 2));
+  } else {
+    return make_uint4(half2_of(w.x, 0), half2_of(w.x, 2), half2_of(w.y, 0), half2_of(w.y, 2));
+  }
+}
+// Half number j (0-based, low half first) of a ring word of halves, as float.
+__device__ __forceinline__ float half_at(const uint2& w, int j) {
+  const uint32_t u = j < 2 ? w.x : w.y;
+  const __half2 p = *reinterpret_cast<const __half2*>(&u);
+  return (j & 1) ? __high2float(p) : __low2float(p);
+}
+__device__ __forceinline__ float half_at(const uint4& w, int j) {
+  const uint32_t u = j < 2 ? w.x : j < 4 ? w.y : j < 6 ? w.z : w.w;
+  const __half2 p = *reinterpret_cast<const __half2*>(&u);
+  return (j & 1) ? __high2float(p) : __low2float(p);
+}
+
 // FIR for 4 consecutive samples n0..n0+3 of spectrum m, antennas a0 (real
 // part) and a1 (imaginary part; a1 < 0 means none).
 __device__ __forceinline__ void fir4(const int8_t* __restrict__ x, int64_t ld_x,
@@ -239,7 +269,7 @@ __device__ __forceinline__ void fused_body(const int8_t* __restrict__ x, int64_t
         for (int i = 0; i < 4; ++i) y[i] = make_float2(0.f, 0.f);
       }
 #pragma unroll
-      for (int i = 0; i < 4; ++i) b0[lds_pad(f * N + n0 + i)] = y[i];
+      for (int i = 0; i < 4; ++i) b0[lds_pad(f * N + n0) + i] = y[i];
     }
     __syncthreads();
     F::run(b0, b1, tw, tid);
@@ -531,9 +561,10 @@ __device__ __forceinline__ void stockham_last_pass_half(const float2* src, float
   constexpr int NB = N / R;
   const int f = tid / NB, j = tid % NB;
   const int jm = j % NS;
+  const int p0 = lds_pad(f * N + j);
   float2 v[R];
 #pragma unroll
-  for (int r = 0; r < R; ++r) v[r] = src[lds_pad(f * N + j + r * NB)];
+  for (int r = 0; r < R; ++r) v[r] = src[lds_at<NB>(f * N + j, p0, r)];
   float2 w[R];
 #pragma unroll
   for (int r = 1; r <= 8; ++r) w[r] = twl[(NS - 1) + (r - 1) * NS + jm];
@@ -542,9 +573,9 @@ __device__ __forceinline__ void stockham_last_pass_half(const float2* src, float
 #pragma unroll
   for (int r = 1; r < R; ++r) v[r] = cmul(v[r], w[r]);
   dft_r<R>(v);
-  const int k = (j / NS) * NS * R + jm;
+  const int k = (j / NS) * NS * R + jm, q0 = lds_pad(f * N + k);
 #pragma unroll
-  for (int r = 0; r < R; ++r) dst[lds_pad(f * N + k + r * NS)] = v[r];
+  for (int r = 0; r < R; ++r) dst[lds_at<NS>(f * N + k, q0, r)] = v[r];
   __syncthreads();
 }
 
@@ -618,14 +649,19 @@ fx_fused_ring_pp_kernel(const int8_t* __restrict__ x, int64_t ld_x, const int8_t
     const int a = 2 * (g / GP) + which;
     return a < NA ? *reinterpret_cast<const uint32_t*>(row(a) + nb * N + cn0[g]) : 0u;
   };
-  uint32_t ring[P][G][2];
+  // with 4 antennas the samples enter the ring as halves (exact; see the ring
+  // F-engine), one conversion each instead of one per tap: 4 x 2^26 samples
+  // 306 us, 322 without; with 2 antennas 242 us, 233 without
+  constexpr bool HALF = NA == 4;
+  using RT = typename std::conditional<HALF, uint2, uint32_t>::type;
+  RT ring[P][G][2];
 #pragma unroll
   for (int q = 0; q < P; ++q)
 #pragma unroll
     for (int g = 0; g < G; ++g) {
       const int64_t blk = m_lo - P + 1 + q;
-      ring[q][g][0] = load_blk(g, 0, blk);
-      ring[q][g][1] = load_blk(g, 1, blk);
+      ring[q][g][0] = ring_word<0, HALF>(load_blk(g, 0, blk));
+      ring[q][g][1] = ring_word<0, HALF>(load_blk(g, 1, blk));
     }
   float4 hr[GP][P];
 #pragma unroll
@@ -640,7 +676,7 @@ fx_fused_ring_pp_kernel(const int8_t* __restrict__ x, int64_t ld_x, const int8_t
     for (int b = 0; b < C::NB; ++b) acc[cc][b] = make_float2(0.f, 0.f);
   __syncthreads();  // twiddles in LDS
 
-  settle_words<P * G * 2>(&ring[0][0][0]);
+  settle_words<P * G * 2 * (HALF ? 2 : 1)>(reinterpret_cast<uint32_t*>(&ring[0][0][0]));
   settle_words<GP * P * 4>(&hr[0][0].x);
   for (int64_t m = m_lo; m < m_hi; ++m) {
     // prefetch block m+1 (consumed at the end of this iteration)
@@ -657,15 +693,18 @@ fx_fused_ring_pp_kernel(const int8_t* __restrict__ x, int64_t ld_x, const int8_t
 #pragma unroll
       for (int q = 0; q < P; ++q) {
         const float4 h = hr[g % GP][q];
-        const uint32_t w0 = ring[q][g][0], w1 = ring[q][g][1];
-        y0[0] += h.x * sbyte(w0, 0);
-        y0[1] += h.y * sbyte(w0, 1);
-        y0[2] += h.z * sbyte(w0, 2);
-        y0[3] += h.w * sbyte(w0, 3);
-        y1[0] += h.x * sbyte(w1, 0);
-        y1[1] += h.y * sbyte(w1, 1);
-        y1[2] += h.z * sbyte(w1, 2);
-        y1[3] += h.w * sbyte(w1, 3);
+        const RT w0 = ring[q][g][0], w1 = ring[q][g][1];
+        const float hv[4] = {h.x, h.y, h.z, h.w};
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          if constexpr (HALF) {
+            y0[i] = fmaf(hv[i], half_at(w0, i), y0[i]);
+            y1[i] = fmaf(hv[i], half_at(w1, i), y1[i]);
+          } else {
+            y0[i] += hv[i] * sbyte(w0, i);
+            y1[i] += hv[i] * sbyte(w1, i);
+          }
+        }
       }
 #pragma unroll
       for (int i = 0; i < 4; ++i) b0[lds_pad((g / GP) * N + cn0[g] + i)] = make_float2(y0[i], y1[i]);
@@ -715,8 +754,8 @@ fx_fused_ring_pp_kernel(const int8_t* __restrict__ x, int64_t ld_x, const int8_t
       }
 #pragma unroll
     for (int g = 0; g < G; ++g) {
-      ring[P - 1][g][0] = nxt[g][0];
-      ring[P - 1][g][1] = nxt[g][1];
+      ring[P - 1][g][0] = ring_word<0, HALF>(nxt[g][0]);
+      ring[P - 1][g][1] = ring_word<0, HALF>(nxt[g][1]);
     }
   }
   float2* out = part + w * (int64_t)C::NB * C::NCH;
@@ -728,6 +767,220 @@ fx_fused_ring_pp_kernel(const int8_t* __restrict__ x, int64_t ld_x, const int8_t
       for (int b = 0; b < C::NB; ++b) out[(int64_t)b * C::NCH + k] = acc[cc][b];
     }
   }
+}
+
+// ---------------------------------------------------------------------------
+// Fused F+X of complex words (I, Q of 8 or 16 bits), four taps: the register
+// ring of the real tiles, one transform per antenna, all N channels.
+//
+// DEC = 2 (4 antennas, N = 4096, whose transforms and sums exceed a CU): a
+// workgroup takes the even or the odd channels.  X[2k] is the N/2-point
+// transform of y[n] + y[n + N/2], X[2k+1] that of (y[n] - y[n + N/2]) W_N^n, so
+// each of the two repeats the filter (a fifth of its work) and halves the rest.
+// The two of a run are eight blocks apart, on one compute die, whose L2 serves
+// the second one's samples.
+// TR: taps in registers.  Without it they are read (L1 and L2) for each
+// spectrum, all antennas at once: with 16-bit words at N = 4096 the ring takes
+// 128 and the sums 64 of the 256 registers a thread has.
+//
+// Bound: FP32 vector ALU (1646 instructions a spectrum and thread at N = 4096
+// with 16-bit words, 96 of them the ring's shift).  4 antennas x 2^26 samples,
+// N = 4096: 16-bit words 0.88 ms with the reduction, 1.38 ms through float32
+// spectra in HBM (2 GiB written and read); 4 x 2^24: 8-bit words 217 us (352),
+// N = 1024 190 us (469, 16 bits 507), N = 2048 165 us (376, 16 bits 397).
+// ---------------------------------------------------------------------------
+template <int N, int NA, int DEC, int ST, bool TR>
+struct CplxCfg {
+  static constexpr int V = 16, P = 4;
+  static constexpr int M = N / DEC;             // transform length
+  static constexpr int NT = NA * M / V;
+  static constexpr int GP = N / (4 * NT);       // groups of four samples per antenna and thread
+  static constexpr int NB = NA * (NA + 1) / 2;
+  static constexpr int CPT = M / NT;            // channels per thread
+  static constexpr int BUF = lds_padded_size(NA * M);
+  static constexpr bool SQ = M == 4096;         // radix-16 throughout: the shortened table
+  static constexpr int tw_entries() {
+    if constexpr (SQ) return PpTw<M, V>::LDS_TW;
+    else return M;
+  }
+  static constexpr size_t LDS_BYTES = sizeof(float2) * (2 * (size_t)BUF + tw_entries());
+  static_assert(LDS_BYTES <= 160 * 1024, "complex tile: LDS");
+  static_assert(GP * 4 * NT == N && CPT * NT == M && (DEC == 1 || (DEC == 2 && GP == 2)), "complex tile: mapping");
+  static_assert(fft_pass_count(M, V) % 2 == 1, "odd pass count: the output lands in the second buffer");
+};
+
+template <int N, int NA, int DEC, int ST, bool TR>
+__global__ void __launch_bounds__((CplxCfg<N, NA, DEC, ST, TR>::NT))
+fx_fused_cplx_kernel(const int8_t* __restrict__ x, int64_t ld_x, const int8_t* __restrict__ hist,
+                     const float* __restrict__ taps, const float2* __restrict__ tw,
+                     const float2* __restrict__ twp, int64_t spec_per_dump, int64_t cpd, int64_t runs,
+                     float2* __restrict__ part) {
+  using C = CplxCfg<N, NA, DEC, ST, TR>;
+  using W = RingWord<ST>;
+  using T = typename W::T;
+  static_assert(W::CPLX, "complex words");
+  constexpr int P = C::P, GP = C::GP, M = C::M, NT = C::NT;
+  extern __shared__ float2 buf[];
+  float2* b0 = buf;
+  float2* b1 = buf + C::BUF;
+  float2* twl = buf + 2 * C::BUF;
+  const int tid = threadIdx.x;
+  // run and channel parity: blocks 16 q + 8 odd + r do run 8 q + r
+  int64_t w = blockIdx.x;
+  bool odd = false;
+  if constexpr (DEC == 2) {
+    odd = (blockIdx.x >> 3) & 1u;
+    w = (int64_t)(blockIdx.x >> 4) * 8 + (blockIdx.x & 7u);
+    if (w >= runs) return;
+  }
+  const int64_t d = w / cpd, c = w % cpd;
+  const int64_t m_lo = d * spec_per_dump + (c * spec_per_dump) / cpd;
+  const int64_t m_hi = d * spec_per_dump + ((c + 1) * spec_per_dump) / cpd;
+
+  for (int i = tid; i < (C::tw_entries() < M - 1 ? C::tw_entries() : M - 1); i += NT) twl[i] = twp[i];
+
+  int cn0[GP];
+#pragma unroll
+  for (int g = 0; g < GP; ++g) cn0[g] = 4 * (tid + g * NT);
+  auto load_blk = [&](int a, int g, int64_t blk) -> T {
+    if (blk >= 0)
+      return *reinterpret_cast<const T*>(x + ((int64_t)a * ld_x + (int)blk * N + cn0[g]) * W::BYTES);
+    if (!hist) return T{};
+    return *reinterpret_cast<const T*>(hist + ((int64_t)a * (P - 1) * N + (int)(blk + P - 1) * N + cn0[g]) * W::BYTES);
+  };
+  // block nb >= 0, unconditionally (see the real ring tile)
+  auto load_next = [&](int a, int g, int nb) -> T {
+    return *reinterpret_cast<const T*>(x + ((int64_t)a * ld_x + nb * N + cn0[g]) * W::BYTES);
+  };
+  T ring[P][NA][GP];
+#pragma unroll
+  for (int q = 0; q < P; ++q)
+#pragma unroll
+    for (int a = 0; a < NA; ++a)
+#pragma unroll
+      for (int g = 0; g < GP; ++g) ring[q][a][g] = load_blk(a, g, m_lo - P + 1 + q);
+  float4 hr[TR ? GP : 1][P];
+  if constexpr (TR) {
+#pragma unroll
+    for (int g = 0; g < GP; ++g)
+#pragma unroll
+      for (int q = 0; q < P; ++q) hr[g][q] = *reinterpret_cast<const float4*>(taps + q * N + cn0[g]);
+  }
+  float2 acc[C::CPT][C::NB];
+#pragma unroll
+  for (int cc = 0; cc < C::CPT; ++cc)
+#pragma unroll
+    for (int b = 0; b < C::NB; ++b) acc[cc][b] = make_float2(0.f, 0.f);
+  __syncthreads();  // tables in LDS
+
+  settle_words<P * NA * GP * (int)(sizeof(T) / 4)>(reinterpret_cast<uint32_t*>(&ring[0][0][0]));
+  for (int64_t m = m_lo; m < m_hi; ++m) {
+    int lt = tid;
+    // hidden per spectrum, so that no address is kept over the loop
+    if constexpr (!TR) asm volatile("" : "+v"(lt));
+    // polyphase FIR; with DEC = 2 the two halves of the block fold together
+    int at0 = 0;  // hidden: these loads stay inside the loop
+    if constexpr (DEC == 2) asm volatile("" : "+s"(at0));
+    constexpr int YG = DEC == 2 ? 1 : GP;
+    float2 y[YG][NA][4];
+#pragma unroll
+    for (int g = 0; g < YG; ++g)
+#pragma unroll
+      for (int a = 0; a < NA; ++a)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) y[g][a][i] = make_float2(0.f, 0.f);
+    const float fold = odd ? -1.f : 1.f;
+#pragma unroll
+    for (int g = 0; g < GP; ++g)
+#pragma unroll
+      for (int q = 0; q < P; ++q) {
+        float4 h;
+        if constexpr (TR) h = hr[g][q];
+        else h = *reinterpret_cast<const float4*>(taps + at0 + q * N + 4 * lt + g * 4 * NT);
+        if (DEC == 2 && g == 1) h = make_float4(fold * h.x, fold * h.y, fold * h.z, fold * h.w);
+        const float hv[4] = {h.x, h.y, h.z, h.w};
+#pragma unroll
+        for (int a = 0; a < NA; ++a)
+#pragma unroll
+          for (int i = 0; i < 4; ++i) {
+            y[g % YG][a][i].x += hv[i] * word_re<ST>(ring[q][a][g], i);
+            y[g % YG][a][i].y += hv[i] * word_im<ST>(ring[q][a][g], i);
+          }
+      }
+    if constexpr (DEC == 2) {
+      if (odd) {
+        const float4* wp = reinterpret_cast<const float4*>(tw + at0 + 4 * lt);
+        const float4 w0 = wp[0], w1 = wp[1];
+        const float2 wn[4] = {make_float2(w0.x, w0.y), make_float2(w0.z, w0.w), make_float2(w1.x, w1.y),
+                              make_float2(w1.z, w1.w)};
+#pragma unroll
+        for (int a = 0; a < NA; ++a)
+#pragma unroll
+          for (int i = 0; i < 4; ++i) y[0][a][i] = cmul(y[0][a][i], wn[i]);
+      }
+    }
+#pragma unroll
+    for (int g = 0; g < YG; ++g)
+#pragma unroll
+      for (int a = 0; a < NA; ++a)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) b0[lds_pad(4 * lt) + lds_pad(a * M + g * 4 * NT) + i] = y[g][a][i];
+    // the next block's words, in flight over the transforms
+    const int nb = (int)(m + 1 < m_hi ? m + 1 : m);
+#pragma unroll
+    for (int a = 0; a < NA; ++a)
+#pragma unroll
+      for (int g = 0; g < GP; ++g) {
+#pragma unroll
+        for (int q = 0; q + 1 < P; ++q) ring[q][a][g] = ring[q + 1][a][g];
+        ring[P - 1][a][g] = load_next(a, g, nb);
+      }
+    __syncthreads();
+    if constexpr (C::SQ) fft_pp_passes<M, 1, NT, C::V, 0>(b0, b1, twl, lt);
+    else Fft<M, NT, C::V, true, false, true>::run(b0, b1, twl, lt);
+    float2 z[C::CPT][NA];
+#pragma unroll
+    for (int cc = 0; cc < C::CPT; ++cc)
+#pragma unroll
+      for (int a = 0; a < NA; ++a) z[cc][a] = b1[lds_pad(lt) + lds_pad(a * M + cc * NT)];
+#pragma unroll
+    for (int cc = 0; cc < C::CPT; ++cc) {
+      int b = 0;
+#pragma unroll
+      for (int i = 0; i < NA; ++i) {
+        const float2 u = z[cc][i];
+        acc[cc][b].x += u.x * u.x + u.y * u.y;
+        ++b;
+#pragma unroll
+        for (int j = i + 1; j < NA; ++j) {
+          const float2 v = z[cc][j];
+          acc[cc][b].x += u.x * v.x + u.y * v.y;
+          acc[cc][b].y += u.y * v.x - u.x * v.y;
+          ++b;
+        }
+      }
+    }
+    // the next FIR writes b0, last read before the final pass's barrier
+  }
+  float2* out = part + w * (int64_t)C::NB * N + (odd ? 1 : 0);
+#pragma unroll
+  for (int cc = 0; cc < C::CPT; ++cc)
+#pragma unroll
+    for (int b = 0; b < C::NB; ++b) out[(int64_t)b * N + DEC * (tid + cc * NT)] = acc[cc][b];
+}
+
+template <int N, int NA, int DEC, int ST, bool TR>
+static hipError_t launch_fused_cplx(const FxArgs& a, int64_t n_dump, int64_t spd, int64_t cpd, float2* part,
+                                    hipStream_t s, const float2* twp) {
+  using C = CplxCfg<N, NA, DEC, ST, TR>;
+  auto kern = fx_fused_cplx_kernel<N, NA, DEC, ST, TR>;
+  hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
+                                     hipFuncAttributeMaxDynamicSharedMemorySize, (int)C::LDS_BYTES);
+  if (e != hipSuccess) return e;
+  const int64_t runs = n_dump * cpd;
+  const int64_t blocks = DEC == 2 ? 16 * ((runs + 7) / 8) : runs;
+  return launch(kern, dim3((unsigned)blocks), dim3(C::NT), C::LDS_BYTES, s, a.x, a.ld_x, a.hist, a.taps, a.tw, twp,
+                spd, cpd, runs, part);
 }
 
 template <int N, int NA, int V>
@@ -885,13 +1138,7 @@ int device_cu_count() {
 // below.  4 antennas, N = 4096: 65536 spectra 1.28 -> 1.22 ms on one round
 // instead of two; 32 spectra 54 us on 4 workgroups, 12 us on 32; N = 1024: 512
 // spectra 32 us on 64 workgroups, 28 us on 512.
-int64_t fused_chunks_per_dump(int n_fft, int n_ant, int64_t n_dump, int64_t spd, int64_t workgroups) {
-  if (workgroups >= 1) {
-    const int64_t want = (workgroups + n_dump - 1) / n_dump;
-    const int64_t maxc = spd / 8 > 0 ? spd / 8 : 1;
-    return want < maxc ? want : maxc;
-  }
-  const int64_t slots = (int64_t)device_cu_count() * ((int64_t)n_fft * n_ant >= 8192 ? 1 : 2);
+static int64_t chunks_of_rounds(int64_t slots, int64_t n_dump, int64_t spd) {
   int64_t best = 1;
   double best_cost = 1e300;
   for (int r = 0; r <= 4; ++r) {
@@ -907,16 +1154,52 @@ int64_t fused_chunks_per_dump(int n_fft, int n_ant, int64_t n_dump, int64_t spd,
   return best;
 }
 
-// Fused F+X of real int16 words (the 16-bit padded mode): the in-place ring
-// tile, for the shapes that have one, with P = 4 and the built-in prototype.
+int64_t fused_chunks_per_dump(int n_fft, int n_ant, int64_t n_dump, int64_t spd, int64_t workgroups) {
+  if (workgroups >= 1) {
+    const int64_t want = (workgroups + n_dump - 1) / n_dump;
+    const int64_t maxc = spd / 8 > 0 ? spd / 8 : 1;
+    return want < maxc ? want : maxc;
+  }
+  return chunks_of_rounds((int64_t)device_cu_count() * ((int64_t)n_fft * n_ant >= 8192 ? 1 : 2), n_dump, spd);
+}
+
+// Fused F+X of the other input words, P = 4: real int16 (the 16-bit padded
+// mode, the built-in prototype) on the in-place ring tile, complex words (any
+// prototype) on the complex tile, for the shapes that have one.
 bool fused_words_supported(int sample, int n_fft, int n_ant, int n_taps, bool taps_symmetric) {
-  if (sample != 1 || n_taps != 4 || !taps_symmetric) return false;
+  if (sample < 1 || sample > 3 || n_taps != 4 || (sample == 1 && !taps_symmetric)) return false;
   return (n_ant == 4 && (n_fft == 1024 || n_fft == 2048 || n_fft == 4096)) || (n_ant == 2 && n_fft == 4096);
 }
 
+// Length of the transforms a fused word tile runs (its per-pass twiddles).
+int fused_words_transform(int sample, int n_fft, int n_ant) {
+  return sample >= 2 && n_fft == 4096 && n_ant == 4 ? n_fft / 2 : n_fft;
+}
+
+int64_t fused_words_chunks(int sample, int n_fft, int n_ant, int64_t n_dump, int64_t spd) {
+  if (sample < 2) return fused_chunks_per_dump(n_fft, n_ant, n_dump, spd);
+  // complex words: resident as the real tile of as many packed values; at
+  // N = 4096 with 4 antennas two workgroups make a run
+  const bool halves = n_fft == 4096 && n_ant == 4;
+  return chunks_of_rounds((int64_t)device_cu_count() * (n_fft * n_ant >= 8192 ? 1 : 2) / (halves ? 2 : 1), n_dump, spd);
+}
+
+template <int ST>
+static hipError_t launch_fused_cplx_st(const FxArgs& a, int64_t n_dump, int64_t spd, int64_t cpd, float2* part,
+                                       hipStream_t s, const float2* twp) {
+  if (a.n_ant == 2) return launch_fused_cplx<4096, 2, 1, ST, true>(a, n_dump, spd, cpd, part, s, twp);
+  switch (a.n_fft) {
+    case 1024: return launch_fused_cplx<1024, 4, 1, ST, true>(a, n_dump, spd, cpd, part, s, twp);
+    case 2048: return launch_fused_cplx<2048, 4, 1, ST, true>(a, n_dump, spd, cpd, part, s, twp);
+    default: return launch_fused_cplx<4096, 4, 2, ST, ST == 2>(a, n_dump, spd, cpd, part, s, twp);
+  }
+}
+
 hipError_t launch_fused_words(const FxArgs& a, int sample, int64_t n_dump, int64_t spd, int64_t cpd,
-                              float2* part, hipStream_t s) {
+                              float2* part, hipStream_t s, const float2* twp) {
   if (!fused_words_supported(sample, a.n_fft, a.n_ant, a.n_taps, a.taps_symmetric)) return hipErrorNotSupported;
+  if (sample == 2) return launch_fused_cplx_st<2>(a, n_dump, spd, cpd, part, s, twp);
+  if (sample == 3) return launch_fused_cplx_st<3>(a, n_dump, spd, cpd, part, s, twp);
   if (a.n_ant == 2) return launch_fused_ring<4096, 2, 16, 1>(a, n_dump, spd, cpd, part, s);
   switch (a.n_fft) {
     case 1024: return launch_fused_ring<1024, 4, 16, 1>(a, n_dump, spd, cpd, part, s);
@@ -1137,7 +1420,7 @@ __device__ __forceinline__ void chan_body(const int8_t* __restrict__ x, int64_t 
         for (int i = 0; i < 4; ++i) y[i] = make_float2(0.f, 0.f);
       }
 #pragma unroll
-      for (int i = 0; i < 4; ++i) buf[lds_pad(s * N + n0 + i)] = y[i];
+      for (int i = 0; i < 4; ++i) buf[lds_pad(s * N + n0) + i] = y[i];
     }
     __syncthreads();
     fft_lds<N, C::NT>(buf, tw, tid);
@@ -1210,36 +1493,6 @@ struct ChanRingCfg {
   }
   static constexpr size_t LDS_BYTES = lds_bytes();
 };
-
-// 8-bit ring words as halves: four real samples -> two half2, four complex
-// samples (I, Q) -> four half2; other words unchanged.
-__device__ __forceinline__ uint32_t half2_of(uint32_t w, int lo_byte) {
-  const __half a = __short2half_rn((short)(int8_t)((w >> (8 * lo_byte)) & 0xffu));
-  const __half b = __short2half_rn((short)(int8_t)((w >> (8 * lo_byte + 8)) & 0xffu));
-  const __half2 p = __halves2half2(a, b);
-  return *reinterpret_cast<const uint32_t*>(&p);
-}
-template <int ST, bool HALF, class T>
-__device__ __forceinline__ auto ring_word(const T& w) {
-  if constexpr (!HALF) {
-    return w;
-  } else if constexpr (ST == 0) {
-    return make_uint2(half2_of(w, 0), half2_of(w, 2));
-  } else {
-    return make_uint4(half2_of(w.x, 0), half2_of(w.x, 2), half2_of(w.y, 0), half2_of(w.y, 2));
-  }
-}
-// Half number j (0-based, low half first) of a ring word of halves, as float.
-__device__ __forceinline__ float half_at(const uint2& w, int j) {
-  const uint32_t u = j < 2 ? w.x : w.y;
-  const __half2 p = *reinterpret_cast<const __half2*>(&u);
-  return (j & 1) ? __high2float(p) : __low2float(p);
-}
-__device__ __forceinline__ float half_at(const uint4& w, int j) {
-  const uint32_t u = j < 2 ? w.x : j < 4 ? w.y : j < 6 ? w.z : w.w;
-  const __half2 p = *reinterpret_cast<const __half2*>(&u);
-  return (j & 1) ? __high2float(p) : __low2float(p);
-}
 
 // Body of the ring F-engine for antenna group grp and run chk of spb
 // spectra, by all threads of a block, on an LDS region of
