@@ -1476,17 +1476,15 @@ channelize_kernel(const int8_t* __restrict__ x, int64_t ld_x, int n_ant, int64_t
 // registers, per-pass twiddles in LDS) for a group of NA antennas (NA/2
 // packed transforms: four antennas up to N = 4096, two at N = 8192),
 // writing the separated spectra out instead of correlating them.
-// Block = (antenna group, run of spectra).  The half of the symmetric
-// prototype the threads pick their taps from is staged once through the
-// transform buffer, so LDS holds only the buffer(s) and the twiddles.
+// Block = (antenna group, run of spectra).  Any prototype of up to P taps: a
+// thread reads the taps of its sample positions into registers once; a
+// shorter filter of n_taps runs with zero taps on the older blocks.
 // With PP the transform ping-pongs between two buffers as in the fused
 // ping-pong tile (one barrier per radix pass, none after the stores);
 // without it the transform runs in place.
 template <int N, int NA, int V, int P, bool PP = false>
 struct ChanRingCfg {
   using C = FusedCfg<N, NA, 1, V, false, 0>;
-  static constexpr int TAPS = P * N / 2;  // floats: half of a symmetric prototype
-  static_assert(sizeof(float) * TAPS <= sizeof(float2) * C::LDS, "taps staged in the transform buffer");
   static constexpr size_t lds_bytes() {
     if constexpr (PP) return RingPpCfg<N, NA, V, P>::LDS_BYTES;
     else return sizeof(float2) * (C::LDS + N);  // transform, twiddles
@@ -1499,7 +1497,7 @@ struct ChanRingCfg {
 // ChanRingCfg<N, NAF, V, P, PP>::LDS_BYTES (NAF = NA for real words, 2 NA
 // for complex ones: the same number of transforms).  x and hist are byte
 // pointers to rows of ST words (ld_x in samples).  twp: the per-pass
-// twiddle table (read with PP only).  Output [antenna][spectrum][channel]:
+// twiddle table (read with PP only).  n_taps <= P.  Output [antenna][spectrum][channel]:
 // N/2 channels for real words (separated, times 1/2), N for complex words.
 template <int N, int NA, int V, int P, int PREC, bool PP = false, int ST = 0, bool WT = false>
 __device__ __forceinline__ void chan_ring_body(const int8_t* __restrict__ x, int64_t ld_x, int n_ant,
@@ -1507,7 +1505,7 @@ __device__ __forceinline__ void chan_ring_body(const int8_t* __restrict__ x, int
                                                const float2* __restrict__ tw, int64_t n_spec, int64_t spb,
                                                int grp, int64_t chk, const float* __restrict__ scale,
                                                void* __restrict__ out, float2* buf,
-                                               const float2* __restrict__ twp = nullptr) {
+                                               const float2* __restrict__ twp = nullptr, int n_taps = P) {
   using W = RingWord<ST>;
   using T = typename W::T;
   constexpr bool CPLX = W::CPLX;
@@ -1517,14 +1515,13 @@ __device__ __forceinline__ void chan_ring_body(const int8_t* __restrict__ x, int
   // (up to N = 4096: at 8192 a thread holds four tap positions and the
   // wider ring would spill; and for requantised output only: with float32
   // output the wider ring measured 3 % slower, with FP16 3 % faster)
-  constexpr bool HALF = (ST == 0 || ST == 2) && N <= 4096 && PREC != 0;
+  constexpr bool HALF = (ST == 0 || ST == 2) && N <= 4096 && PREC != 0 && P == 4;
   using RT = typename std::conditional<HALF, typename std::conditional<CPLX, uint4, uint2>::type, T>::type;
   constexpr int SL = CPLX ? 1 : 2;               // ring slots per chunk
   constexpr int NAF = CPLX ? 2 * NA : NA;
   using C = FusedCfg<N, NAF, 1, V, false, 0>;
   using F = Fft<N, C::NT, V, false, false, true>;
   constexpr int G = C::CHUNKS;
-  constexpr int L = P * N;
   constexpr int NCH = CPLX ? N : N / 2;          // channels out per transform
   constexpr int CPT = NCH / C::NT;               // per thread per transform
   static_assert(NCH % C::NT == 0, "every thread has CPT channels");
@@ -1532,13 +1529,11 @@ __device__ __forceinline__ void chan_ring_body(const int8_t* __restrict__ x, int
   float2* b0 = buf;
   float2* b1 = PP ? buf + C::BUF : buf;      // where the transform's output lands
   float2* twl = PP ? buf + 2 * C::BUF : buf + C::LDS;
-  float4* tl = reinterpret_cast<float4*>(b0);  // taps, until they are in registers
   const int tid = threadIdx.x;
   const int a_base = NA * grp;
   const int64_t m_lo = chk * spb;
   const int64_t m_hi = m_lo + spb < n_spec ? m_lo + spb : n_spec;
 
-  for (int i = tid; i < L / 8; i += C::NT) tl[i] = reinterpret_cast<const float4*>(taps)[i];
   if constexpr (PP) {
     for (int i = tid; i < PpTw<N, V>::LDS_TW; i += C::NT) twl[i] = twp[i];
   } else {
@@ -1554,11 +1549,11 @@ __device__ __forceinline__ void chan_ring_body(const int8_t* __restrict__ x, int
   auto ant = [&](int g, int which) -> int { return a_base + (CPLX ? g / GP : 2 * (g / GP) + which); };
   auto load_blk = [&](int g, int which, int64_t blk) -> T {
     const int a = ant(g, which);
-    if (a >= n_ant) return T{};
+    if (a >= n_ant || blk <= m_lo - n_taps) return T{};  // past the last antenna, or under a zero tap
     if (blk >= 0)
       return *reinterpret_cast<const T*>(x + ((int64_t)a * ld_x + (int)blk * N + cn0[g]) * W::BYTES);
     if (!hist) return T{};
-    return *reinterpret_cast<const T*>(hist + ((int64_t)a * (P - 1) * N + (int)(blk + P - 1) * N + cn0[g]) *
+    return *reinterpret_cast<const T*>(hist + ((int64_t)a * (n_taps - 1) * N + (int)(blk + n_taps - 1) * N + cn0[g]) *
                                                   W::BYTES);
   };
   // Prefetch of stream block nb >= 0 (see the fused ring tile): one
@@ -1583,20 +1578,15 @@ __device__ __forceinline__ void chan_ring_body(const int8_t* __restrict__ x, int
     const int a = a_base + i;
     hs[i] = (CPLX ? 1.f : 0.5f) * ((PREC != 0 && a < n_ant) ? scale[a] : 1.f);
   }
-  __syncthreads();  // taps and twiddles in LDS
   float4 hr[GP][P];   // taps of the thread's distinct chunk positions
 #pragma unroll
   for (int g = 0; g < GP; ++g)
 #pragma unroll
     for (int q = 0; q < P; ++q) {
-      if (2 * q < P) {
-        hr[g][q] = tl[(q * N + cn0[g]) / 4];
-      } else {
-        const float4 r = tl[(L - q * N - cn0[g] - 4) / 4];
-        hr[g][q] = make_float4(r.w, r.z, r.y, r.x);
-      }
+      const int row = q - (P - n_taps);
+      hr[g][q] = row >= 0 ? *reinterpret_cast<const float4*>(taps + row * N + cn0[g]) : make_float4(0.f, 0.f, 0.f, 0.f);
     }
-  __syncthreads();  // the transform buffer is free for the FIR output
+  __syncthreads();  // twiddles in LDS
 
   settle_words<P * G * SL * (int)(sizeof(RT) / 4)>(reinterpret_cast<uint32_t*>(&ring[0][0][0]));
   for (int64_t m = m_lo; m < m_hi; ++m) {
@@ -1706,67 +1696,54 @@ __device__ __forceinline__ void chan_ring_body(const int8_t* __restrict__ x, int
 template <int N, int NA, int V, int P, int PREC, bool PP, int ST>
 __global__ void __launch_bounds__((FusedCfg<N, (ST >= 2 ? 2 * NA : NA), 1, V, false, 0>::NT))
 chan_ring_kernel(const int8_t* __restrict__ x, int64_t ld_x, int n_ant, const int8_t* __restrict__ hist,
-                 const float* __restrict__ taps, const float2* __restrict__ tw, const float2* __restrict__ twp,
-                 int64_t n_spec, int64_t spb, int64_t chunks, const float* __restrict__ scale,
-                 void* __restrict__ out) {
+                 const float* __restrict__ taps, int n_taps, const float2* __restrict__ tw,
+                 const float2* __restrict__ twp, int64_t n_spec, int64_t spb, int64_t chunks,
+                 const float* __restrict__ scale, void* __restrict__ out) {
   extern __shared__ float2 buf[];
   chan_ring_body<N, NA, V, P, PREC, PP, ST>(x, ld_x, n_ant, hist, taps, tw, n_spec, spb,
                                             (int)(blockIdx.x / chunks), (int64_t)(blockIdx.x % chunks), scale,
-                                            out, buf, twp);
+                                            out, buf, twp, n_taps);
 }
 
 // The ring F-engine over n_ant rows of ST words.  Four real antennas (two
 // packed transforms) per workgroup up to N = 4096 and two at N = 8192;
 // complex words take half as many antennas, one transform each.  Ping-pong
 // transform buffers at N = 4096 (154 KiB of LDS).
-template <int N, int PREC, int ST>
-static hipError_t launch_chan_ring_w(const int8_t* x, int64_t ld_x, int n_ant, int64_t n_samp,
-                                     const int8_t* hist, const float* taps, const float2* tw,
-                                     const float2* twp, void* out, const float* scale, hipStream_t s) {
+template <int N, int P, int PREC, int ST>
+static hipError_t launch_chan_ring_w(const ChanxArgs& a, void* out, const float* scale, hipStream_t s) {
   constexpr int V = 16;
   constexpr bool PP = N == 4096;
   constexpr int NAR = N >= 8192 ? 2 : 4;
   constexpr int NA = ST >= 2 ? NAR / 2 : NAR;
-  using RC = ChanRingCfg<N, NAR, V, 4, PP>;
+  using RC = ChanRingCfg<N, NAR, V, P, PP>;
   using C = FusedCfg<N, NAR, 1, V, false, 0>;
   static_assert(RC::LDS_BYTES <= 160 * 1024, "channelize ring: LDS");
-  if (PP && !twp) return hipErrorInvalidValue;
-  const int64_t n_spec = n_samp / N;
-  const int groups = (n_ant + NA - 1) / NA;
-  // runs of at least 16 spectra (the ring reloads P-1 blocks per run and
-  // each workgroup rebuilds its twiddle tables).  Workgroups of 512 threads
-  // (N >= 4096) are resident one per CU: one workgroup per CU in total, a
-  // single round (1-4 % faster than two rounds at 32 antennas, N = 4096);
-  // smaller ones keep 512 in total
-  const int64_t wg = C::NT >= 512 ? device_cu_count() : 512;
-  int64_t spb = (n_spec * groups + wg - 1) / wg;
-  if (spb < 16) spb = 16;
-  const int64_t chunks = (n_spec + spb - 1) / spb;
+  if (PP && !a.twp) return hipErrorInvalidValue;
+  const int64_t n_spec = a.n_samp / N;
+  const int groups = (a.n_ant + NA - 1) / NA;
+  // runs that fill rounds of workgroups, 512 threads per CU (what the
+  // registers allow)
+  int64_t chunks = chunks_of_rounds((int64_t)device_cu_count() * (512 / C::NT), groups, n_spec);
+  const int64_t spb = (n_spec + chunks - 1) / chunks;
+  chunks = (n_spec + spb - 1) / spb;
   if ((int64_t)groups * chunks > 0x7fffffffLL) return hipErrorInvalidValue;
-  const void* k = reinterpret_cast<const void*>(chan_ring_kernel<N, NA, V, 4, PREC, PP, ST>);
-  hipError_t e = hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)RC::LDS_BYTES);
+  auto kern = chan_ring_kernel<N, NA, V, P, PREC, PP, ST>;
+  hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
+                                     hipFuncAttributeMaxDynamicSharedMemorySize, (int)RC::LDS_BYTES);
   if (e != hipSuccess) return e;
-  return launch(chan_ring_kernel<N, NA, V, 4, PREC, PP, ST>, dim3((unsigned)(groups * chunks)), dim3(C::NT),
-                RC::LDS_BYTES, s, x, ld_x, n_ant, hist, taps, tw, twp, n_spec, spb, chunks, scale, out);
+  return launch(kern, dim3((unsigned)(groups * chunks)), dim3(C::NT), RC::LDS_BYTES, s, static_cast<const int8_t*>(a.x),
+                a.ld_x, a.n_ant, static_cast<const int8_t*>(a.hist), a.taps, a.n_taps, a.tw, a.twp, n_spec, spb, chunks,
+                scale, out);
 }
 
-template <int N, int ST>
-static hipError_t launch_chan_ring_st(const int8_t* x, int64_t ld_x, int n_ant, int64_t n_samp,
-                                      const int8_t* hist, const float* taps, const float2* tw,
-                                      const float2* twp, int prec, void* out, const float* scale,
-                                      hipStream_t s) {
+template <int N, int P, int ST>
+static hipError_t launch_chan_ring_st(const ChanxArgs& a, int prec, void* out, const float* scale, hipStream_t s) {
   switch (prec) {
-    case 0: return launch_chan_ring_w<N, 0, ST>(x, ld_x, n_ant, n_samp, hist, taps, tw, twp, out, scale, s);
-    case 1: return launch_chan_ring_w<N, 1, ST>(x, ld_x, n_ant, n_samp, hist, taps, tw, twp, out, scale, s);
-    case 2: return launch_chan_ring_w<N, 2, ST>(x, ld_x, n_ant, n_samp, hist, taps, tw, twp, out, scale, s);
-    default: return launch_chan_ring_w<N, 3, ST>(x, ld_x, n_ant, n_samp, hist, taps, tw, twp, out, scale, s);
+    case 0: return launch_chan_ring_w<N, P, 0, ST>(a, out, scale, s);
+    case 1: return launch_chan_ring_w<N, P, 1, ST>(a, out, scale, s);
+    case 2: return launch_chan_ring_w<N, P, 2, ST>(a, out, scale, s);
+    default: return launch_chan_ring_w<N, P, 3, ST>(a, out, scale, s);
   }
-}
-
-template <int N>
-static hipError_t launch_chan_ring(const FxArgs& a, int prec, void* out, const float* scale, hipStream_t s) {
-  return launch_chan_ring_st<N, 0>(a.x, a.ld_x, a.n_ant, a.n_samp, a.hist, a.taps, a.tw, a.twp, prec, out,
-                                   scale, s);
 }
 
 template <int N>
@@ -1809,45 +1786,46 @@ void set_channelize_variant(int v) { g_chan_variant = v; }
 int get_channelize_variant() { return g_chan_variant; }
 
 template <int N>
-static hipError_t launch_chan_ring_any_n(const ChanxArgs& a, int sample, int prec, void* out,
-                                         const float* scale, hipStream_t s) {
-  const int8_t* x = static_cast<const int8_t*>(a.x);
-  const int8_t* h = static_cast<const int8_t*>(a.hist);
+static hipError_t launch_chan_ring_n(const ChanxArgs& a, int sample, int prec, void* out, const float* scale,
+                                     hipStream_t s) {
+  if constexpr (N <= 4096)
+    if (a.n_taps > 4) return launch_chan_ring_st<N, 8, 0>(a, prec, out, scale, s);
   switch (sample) {
-    case 0: return launch_chan_ring_st<N, 0>(x, a.ld_x, a.n_ant, a.n_samp, h, a.taps, a.tw, a.twp, prec, out, scale, s);
-    case 1: return launch_chan_ring_st<N, 1>(x, a.ld_x, a.n_ant, a.n_samp, h, a.taps, a.tw, a.twp, prec, out, scale, s);
-    case 2: return launch_chan_ring_st<N, 2>(x, a.ld_x, a.n_ant, a.n_samp, h, a.taps, a.tw, a.twp, prec, out, scale, s);
-    case 3: return launch_chan_ring_st<N, 3>(x, a.ld_x, a.n_ant, a.n_samp, h, a.taps, a.tw, a.twp, prec, out, scale, s);
+    case 0: return launch_chan_ring_st<N, 4, 0>(a, prec, out, scale, s);
+    case 1: return launch_chan_ring_st<N, 4, 1>(a, prec, out, scale, s);
+    case 2: return launch_chan_ring_st<N, 4, 2>(a, prec, out, scale, s);
+    case 3: return launch_chan_ring_st<N, 4, 3>(a, prec, out, scale, s);
   }
   return hipErrorInvalidValue;
 }
 
+// The ring takes every prototype whose taps and samples fit a thread's
+// registers: up to 4 taps (zero taps make up the rest), up to 8 for int8 words
+// below N = 8192.  It reads each sample once, the plain kernel once per tap: 13
+// antennas x 2^22 samples, N = 4096: 85 us at 1 to 4 taps, 106 at 5 to 8 (plain
+// 113, 161, 258 us at 1, 4, 8 taps); N = 1024, 8 taps: 98 (160); complex words
+// at 2 taps 92 to 119 (175 to 190).
 hipError_t launch_channelize_ring_any(const ChanxArgs& a, int sample, int prec, void* out, const float* scale,
                                       hipStream_t s) {
-  if (g_chan_variant != 0 || a.n_taps != 4 || !a.taps_symmetric) return hipErrorNotSupported;
+  if (g_chan_variant != 0) return hipErrorNotSupported;
+  if (a.n_taps > 4 && (a.n_taps > 8 || sample != 0 || a.n_fft == 8192)) return hipErrorNotSupported;
   // 16-bit words at N = 8192 (four distinct tap positions per thread and a
   // ring twice as wide) would spill inside the loop: the plain kernel
   if (a.n_fft == 8192 && (sample == 1 || sample == 3)) return hipErrorNotSupported;
   switch (a.n_fft) {
-    case 1024: return launch_chan_ring_any_n<1024>(a, sample, prec, out, scale, s);
-    case 2048: return launch_chan_ring_any_n<2048>(a, sample, prec, out, scale, s);
-    case 4096: return launch_chan_ring_any_n<4096>(a, sample, prec, out, scale, s);
-    case 8192: return launch_chan_ring_any_n<8192>(a, sample, prec, out, scale, s);
+    case 1024: return launch_chan_ring_n<1024>(a, sample, prec, out, scale, s);
+    case 2048: return launch_chan_ring_n<2048>(a, sample, prec, out, scale, s);
+    case 4096: return launch_chan_ring_n<4096>(a, sample, prec, out, scale, s);
+    case 8192: return launch_chan_ring_n<8192>(a, sample, prec, out, scale, s);
   }
   return hipErrorNotSupported;
 }
 
 hipError_t launch_channelize(const FxArgs& a, int prec, void* out, const float* scale,
                              hipStream_t s) {
-  if (g_chan_variant == 0 && a.n_taps == 4 && a.taps_symmetric) {
-    switch (a.n_fft) {
-      case 1024: return launch_chan_ring<1024>(a, prec, out, scale, s);
-      case 2048: return launch_chan_ring<2048>(a, prec, out, scale, s);
-      case 4096: return launch_chan_ring<4096>(a, prec, out, scale, s);
-      case 8192: return launch_chan_ring<8192>(a, prec, out, scale, s);
-      default: break;
-    }
-  }
+  const hipError_t r = launch_channelize_ring_any(
+      ChanxArgs{a.x, a.ld_x, a.n_ant, a.n_samp, a.n_fft, a.n_taps, a.taps, a.tw, a.hist, a.twp}, 0, prec, out, scale, s);
+  if (r != hipErrorNotSupported) return r;
   switch (a.n_fft) {
     case 4: return launch_chan_t<4>(a, prec, out, scale, s);
     case 8: return launch_chan_t<8>(a, prec, out, scale, s);
