@@ -521,9 +521,9 @@ qc_status qc_timing_read(int32_t kernel, double* total_ms, int64_t* launches);
 
 /* F-engine kernel choice (process-wide; not thread-safe against concurrent
  * calls): 0 (default) uses the register-ring kernel where it applies (n_fft
- * 1024..8192, P <= 4, or P <= 8 for int8 words up to n_fft 4096; any taps: the
- * fused ring tile's FIR and transform, writing spectra out), 1 always the plain
- * kernel.  Both compute the same
+ * 1024..8192; float32 output with any taps, P <= 4, or P <= 8 for int8 words up
+ * to n_fft 4096; requantised output with the built-in P = 4: the fused ring
+ * tile's FIR and transform, writing spectra out), 1 always the plain kernel.  Both compute the same
  * sums (Sec. 4.2 F-engine); the choice only affects speed.  Used by
  * qc_pfb_channelize and the two-pass paths of qc_xcorrelate. */
 qc_status qc_channelize_set_variant(int32_t variant);

@@ -490,7 +490,7 @@ qc_status channelize_any_impl(const void* x, int32_t sample, int64_t ld_x, int32
   qc_status st = resolve(nullptr, ld_x, n_ant, n_samp, p, nullptr, &r);
   if (st != QC_OK) return st;
   const qc::ChanxArgs a{x, ld_x, n_ant, n_samp, p->n_fft, p->n_taps, r.args.taps, r.args.tw, hist,
-                       r.args.twp};
+                       r.args.taps_symmetric, r.args.twp};
   if (out_prec != QC_F32) {
     double s2 = r.sum_h2;
     if (p->taps != nullptr) {
@@ -892,9 +892,11 @@ qc_status qc_solve_delay_phase(const float* vis, const uint8_t* mask, int64_t n_
   QC_HIP(qc::launch_solve(reinterpret_cast<const float2*>(vis), mask, n_time, n_ant, n_chan, f0_hz, df_hz,
                           ref_ant, chan_lo, chan_hi, n_lag, tw, tb, pb, ta, pa, s),
          "solve kernels");
-  QC_HIP(hipMemcpyAsync(tau_s, ta, sizeof(double) * n_ant, hipMemcpyDeviceToHost, s), "copy tau");
-  QC_HIP(hipMemcpyAsync(phi_rad, pa, sizeof(double) * n_ant, hipMemcpyDeviceToHost, s), "copy phi");
+  double host[2 * 64];  // delays, then phases (n_ant <= 64)
+  QC_HIP(hipMemcpyAsync(host, ta, sizeof(double) * 2 * n_ant, hipMemcpyDeviceToHost, s), "copy solution");
   QC_HIP(hipStreamSynchronize(s), "hipStreamSynchronize");
+  std::memcpy(tau_s, host, sizeof(double) * n_ant);
+  std::memcpy(phi_rad, host + n_ant, sizeof(double) * n_ant);
   return QC_OK;
 }
 

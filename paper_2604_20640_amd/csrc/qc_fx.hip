@@ -1497,7 +1497,8 @@ struct ChanRingCfg {
 // ChanRingCfg<N, NAF, V, P, PP>::LDS_BYTES (NAF = NA for real words, 2 NA
 // for complex ones: the same number of transforms).  x and hist are byte
 // pointers to rows of ST words (ld_x in samples).  twp: the per-pass
-// twiddle table (read with PP only).  n_taps <= P.  Output [antenna][spectrum][channel]:
+// twiddle table (read with PP only).  n_taps <= P; mirrored: a symmetric
+// prototype of P taps, whose second half is read from the first.  Output [antenna][spectrum][channel]:
 // N/2 channels for real words (separated, times 1/2), N for complex words.
 template <int N, int NA, int V, int P, int PREC, bool PP = false, int ST = 0, bool WT = false>
 __device__ __forceinline__ void chan_ring_body(const int8_t* __restrict__ x, int64_t ld_x, int n_ant,
@@ -1505,7 +1506,8 @@ __device__ __forceinline__ void chan_ring_body(const int8_t* __restrict__ x, int
                                                const float2* __restrict__ tw, int64_t n_spec, int64_t spb,
                                                int grp, int64_t chk, const float* __restrict__ scale,
                                                void* __restrict__ out, float2* buf,
-                                               const float2* __restrict__ twp = nullptr, int n_taps = P) {
+                                               const float2* __restrict__ twp = nullptr, int n_taps = P,
+                                               bool mirrored = true) {
   using W = RingWord<ST>;
   using T = typename W::T;
   constexpr bool CPLX = W::CPLX;
@@ -1584,7 +1586,12 @@ __device__ __forceinline__ void chan_ring_body(const int8_t* __restrict__ x, int
 #pragma unroll
     for (int q = 0; q < P; ++q) {
       const int row = q - (P - n_taps);
-      hr[g][q] = row >= 0 ? *reinterpret_cast<const float4*>(taps + row * N + cn0[g]) : make_float4(0.f, 0.f, 0.f, 0.f);
+      if (mirrored && 2 * q >= P) {
+        const float4 r = *reinterpret_cast<const float4*>(taps + (P - q) * N - cn0[g] - 4);
+        hr[g][q] = make_float4(r.w, r.z, r.y, r.x);
+      } else {
+        hr[g][q] = row >= 0 ? *reinterpret_cast<const float4*>(taps + row * N + cn0[g]) : make_float4(0.f, 0.f, 0.f, 0.f);
+      }
     }
   __syncthreads();  // twiddles in LDS
 
@@ -1696,13 +1703,13 @@ __device__ __forceinline__ void chan_ring_body(const int8_t* __restrict__ x, int
 template <int N, int NA, int V, int P, int PREC, bool PP, int ST>
 __global__ void __launch_bounds__((FusedCfg<N, (ST >= 2 ? 2 * NA : NA), 1, V, false, 0>::NT))
 chan_ring_kernel(const int8_t* __restrict__ x, int64_t ld_x, int n_ant, const int8_t* __restrict__ hist,
-                 const float* __restrict__ taps, int n_taps, const float2* __restrict__ tw,
+                 const float* __restrict__ taps, int n_taps, int mirrored, const float2* __restrict__ tw,
                  const float2* __restrict__ twp, int64_t n_spec, int64_t spb, int64_t chunks,
                  const float* __restrict__ scale, void* __restrict__ out) {
   extern __shared__ float2 buf[];
   chan_ring_body<N, NA, V, P, PREC, PP, ST>(x, ld_x, n_ant, hist, taps, tw, n_spec, spb,
                                             (int)(blockIdx.x / chunks), (int64_t)(blockIdx.x % chunks), scale,
-                                            out, buf, twp, n_taps);
+                                            out, buf, twp, n_taps, mirrored != 0);
 }
 
 // The ring F-engine over n_ant rows of ST words.  Four real antennas (two
@@ -1732,8 +1739,8 @@ static hipError_t launch_chan_ring_w(const ChanxArgs& a, void* out, const float*
                                      hipFuncAttributeMaxDynamicSharedMemorySize, (int)RC::LDS_BYTES);
   if (e != hipSuccess) return e;
   return launch(kern, dim3((unsigned)(groups * chunks)), dim3(C::NT), RC::LDS_BYTES, s, static_cast<const int8_t*>(a.x),
-                a.ld_x, a.n_ant, static_cast<const int8_t*>(a.hist), a.taps, a.n_taps, a.tw, a.twp, n_spec, spb, chunks,
-                scale, out);
+                a.ld_x, a.n_ant, static_cast<const int8_t*>(a.hist), a.taps, a.n_taps,
+                (int)(a.taps_symmetric && a.n_taps == P), a.tw, a.twp, n_spec, spb, chunks, scale, out);
 }
 
 template <int N, int P, int ST>
@@ -1804,10 +1811,13 @@ static hipError_t launch_chan_ring_n(const ChanxArgs& a, int sample, int prec, v
 // below N = 8192.  It reads each sample once, the plain kernel once per tap: 13
 // antennas x 2^22 samples, N = 4096: 85 us at 1 to 4 taps, 106 at 5 to 8 (plain
 // 113, 161, 258 us at 1, 4, 8 taps); N = 1024, 8 taps: 98 (160); complex words
-// at 2 taps 92 to 119 (175 to 190).
+// at 2 taps 92 to 119 (175 to 190).  Requantised output of such prototypes stays
+// with the plain kernel: the two differ in the last bit of float32, which
+// now and then moves a value to the next step of a short format.
 hipError_t launch_channelize_ring_any(const ChanxArgs& a, int sample, int prec, void* out, const float* scale,
                                       hipStream_t s) {
   if (g_chan_variant != 0) return hipErrorNotSupported;
+  if (prec != 0 && !(a.n_taps == 4 && a.taps_symmetric)) return hipErrorNotSupported;
   if (a.n_taps > 4 && (a.n_taps > 8 || sample != 0 || a.n_fft == 8192)) return hipErrorNotSupported;
   // 16-bit words at N = 8192 (four distinct tap positions per thread and a
   // ring twice as wide) would spill inside the loop: the plain kernel
@@ -1824,7 +1834,7 @@ hipError_t launch_channelize_ring_any(const ChanxArgs& a, int sample, int prec, 
 hipError_t launch_channelize(const FxArgs& a, int prec, void* out, const float* scale,
                              hipStream_t s) {
   const hipError_t r = launch_channelize_ring_any(
-      ChanxArgs{a.x, a.ld_x, a.n_ant, a.n_samp, a.n_fft, a.n_taps, a.taps, a.tw, a.hist, a.twp}, 0, prec, out, scale, s);
+      ChanxArgs{a.x, a.ld_x, a.n_ant, a.n_samp, a.n_fft, a.n_taps, a.taps, a.tw, a.hist, a.taps_symmetric, a.twp}, 0, prec, out, scale, s);
   if (r != hipErrorNotSupported) return r;
   switch (a.n_fft) {
     case 4: return launch_chan_t<4>(a, prec, out, scale, s);

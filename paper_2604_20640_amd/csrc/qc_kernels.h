@@ -83,6 +83,7 @@ struct ChanxArgs {
   const float* taps;  // device [P*N]
   const float2* tw;   // device [N], exp(-2 pi i e/N)
   const void* hist;   // device [n_ant][(P-1)N] samples or null
+  bool taps_symmetric = false;  // h[q] == h[P*N-1-q] (the built-in prototype)
   const float2* twp = nullptr;  // per-pass twiddles, as in FxArgs
 };
 // Fused F+X of int16 and complex words where a tile applies (n_ant 4 at
@@ -95,9 +96,10 @@ int fused_words_transform(int sample, int n_fft, int n_ant);
 int64_t fused_words_chunks(int sample, int n_fft, int n_ant, int64_t n_dump, int64_t spec_per_dump);
 hipError_t launch_fused_words(const FxArgs& a, int sample, int64_t n_dump, int64_t spd, int64_t cpd,
                               float2* part, hipStream_t s, const float2* twp);
-// The ring F-engine for any word where it applies (N = 1024..8192, P <= 4, or
-// P <= 8 with int8 words up to N = 4096, ring variant selected);
-// hipErrorNotSupported otherwise.
+// The ring F-engine for any word where it applies (N = 1024..8192; float32
+// output with P <= 4, or P <= 8 with int8 words up to N = 4096; requantised
+// output with the built-in P = 4; ring variant selected); hipErrorNotSupported
+// otherwise.
 hipError_t launch_channelize_ring_any(const ChanxArgs& a, int sample, int prec, void* out, const float* scale,
                                       hipStream_t s);
 hipError_t launch_channelize_any(const ChanxArgs& a, int sample, int prec, void* out, const float* scale,

@@ -29,23 +29,51 @@ namespace {
 
 constexpr double kPi = 3.14159265358979323846;
 
-// Sums K doubles over the block; every thread gets the totals.
+// Sums K doubles over the block; every thread gets the totals: over each wave
+// by lane exchanges, then the waves' sums in order (one barrier; a tree over
+// LDS took one per level).
 template <int NT, int K>
 __device__ __forceinline__ void block_sum(double (&v)[K], double* red) {
-  const int t = threadIdx.x;
+  constexpr int W = NT < 64 ? NT : 64, NW = NT / W;
 #pragma unroll
-  for (int q = 0; q < K; ++q) red[q * NT + t] = v[q];
-  __syncthreads();
-  for (int st = NT / 2; st > 0; st >>= 1) {
-    if (t < st) {
+  for (int q = 0; q < K; ++q)
 #pragma unroll
-      for (int q = 0; q < K; ++q) red[q * NT + t] += red[q * NT + t + st];
+    for (int d = W / 2; d > 0; d >>= 1) v[q] += __shfl_xor(v[q], d, W);
+  if constexpr (NW > 1) {
+    const int lane = threadIdx.x % W, wave = threadIdx.x / W;
+    if (lane == 0)
+#pragma unroll
+      for (int q = 0; q < K; ++q) red[q * NW + wave] = v[q];
+    __syncthreads();
+#pragma unroll
+    for (int q = 0; q < K; ++q) {
+      double s = red[q * NW];
+      for (int w = 1; w < NW; ++w) s += red[q * NW + w];
+      v[q] = s;
     }
     __syncthreads();
   }
+}
+
+// Exclusive prefix sum of one int per thread over the block.
+template <int NT>
+__device__ __forceinline__ int block_prefix(int v, int* red) {
+  constexpr int W = NT < 64 ? NT : 64, NW = NT / W;
+  const int lane = threadIdx.x % W, wave = threadIdx.x / W;
+  int s = v;
 #pragma unroll
-  for (int q = 0; q < K; ++q) v[q] = red[q * NT];
-  __syncthreads();
+  for (int d = 1; d < W; d <<= 1) {
+    const int o = __shfl_up(s, d, W);
+    if (lane >= d) s += o;
+  }
+  int before = 0;
+  if constexpr (NW > 1) {
+    if (lane == W - 1) red[wave] = s;
+    __syncthreads();
+    for (int w = 0; w < NW; ++w) before += w < wave ? red[w] : 0;
+    __syncthreads();
+  }
+  return before + s - v;
 }
 
 __device__ __forceinline__ double wrap_pi(double a) {
@@ -79,15 +107,28 @@ solve_baseline_kernel(const float2* __restrict__ vis, const uint8_t* __restrict_
   const int64_t nb = (int64_t)n_ant * (n_ant + 1) / 2;
 
   // 1. time integration with flags zeroed
+  // (the loads do not wait for the flags, and eight are in flight)
   for (int k = tid; k < n_chan; k += NT) {
     double sx = 0.0, sy = 0.0;
-    for (int64_t t = 0; t < n_time; ++t) {
-      const int64_t o = (t * nb + b) * n_chan + k;
-      if (mask == nullptr || mask[o] == 0) {
-        const float2 v = vis[o];
-        sx += (double)v.x;
-        sy += (double)v.y;
+    const int64_t step = nb * n_chan;
+    int64_t o = b * n_chan + k;
+    constexpr int U = 8;
+    for (int64_t t = 0; t < n_time; t += U) {
+      float2 v[U];
+      uint8_t f[U];
+#pragma unroll
+      for (int q = 0; q < U; ++q) {
+        const bool in = t + q < n_time;
+        v[q] = in ? vis[o + q * step] : make_float2(0.f, 0.f);
+        f[q] = in && mask ? mask[o + q * step] : (uint8_t)0;
       }
+#pragma unroll
+      for (int q = 0; q < U; ++q)
+        if (f[q] == 0) {
+          sx += (double)v[q].x;
+          sy += (double)v[q].y;
+        }
+      o += U * step;
     }
     vi[k] = make_float2((float)sx, (float)sy);
   }
@@ -109,22 +150,33 @@ solve_baseline_kernel(const float2* __restrict__ vis, const uint8_t* __restrict_
       best_l = l;
     }
   }
-  red[tid] = (double)best;
-  cnt[tid] = best_l;
-  __syncthreads();
-  for (int st = NT / 2; st > 0; st >>= 1) {
-    if (tid < st) {
-      const double o = red[tid + st];
-      const int ol = cnt[tid + st];
-      if (o > red[tid] || (o == red[tid] && ol < cnt[tid])) {
-        red[tid] = o;
-        cnt[tid] = ol;
+  // the largest; ties to the smallest lag
+  constexpr int W = NT < 64 ? NT : 64, NW = NT / W;
+#pragma unroll
+  for (int d = W / 2; d > 0; d >>= 1) {
+    const float o = __shfl_xor(best, d, W);
+    const int ol = __shfl_xor(best_l, d, W);
+    if (o > best || (o == best && ol < best_l)) {
+      best = o;
+      best_l = ol;
+    }
+  }
+  if constexpr (NW > 1) {
+    if (tid % W == 0) {
+      red[tid / W] = (double)best;
+      cnt[tid / W] = best_l;
+    }
+    __syncthreads();
+    for (int w = 0; w < NW; ++w) {
+      const float o = (float)red[w];
+      if (o > best || (o == best && cnt[w] < best_l)) {
+        best = o;
+        best_l = cnt[w];
       }
     }
     __syncthreads();
   }
-  const int lstar = cnt[0];
-  __syncthreads();
+  const int lstar = best_l;
   const int ls = lstar < NLAG / 2 ? lstar : lstar - NLAG;
   const double tau_c = (double)ls / ((double)NLAG * df);
 
@@ -152,19 +204,8 @@ solve_baseline_kernel(const float2* __restrict__ vis, const uint8_t* __restrict_
     const float dd = psi[q] - psi[q - 1];
     local += dd > (float)kPi ? -1 : (dd < -(float)kPi ? 1 : 0);
   }
-  cnt[tid] = local;
-  __syncthreads();
-  if (tid == 0) {
-    int acc = 0;
-    for (int t = 0; t < NT; ++t) {
-      const int v = cnt[t];
-      cnt[t] = acc;
-      acc += v;
-    }
-  }
-  __syncthreads();
   double sums[5] = {0.0, 0.0, 0.0, 0.0, 0.0};
-  int cj = cnt[tid];
+  int cj = block_prefix<NT>(local, cnt);
   for (int q = q0; q < q1; ++q) {
     if (q > 0) {
       const float dd = psi[q] - psi[q - 1];
