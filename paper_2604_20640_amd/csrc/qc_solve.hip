@@ -107,30 +107,41 @@ solve_baseline_kernel(const float2* __restrict__ vis, const uint8_t* __restrict_
   const int64_t nb = (int64_t)n_ant * (n_ant + 1) / 2;
 
   // 1. time integration with flags zeroed
-  // (the loads do not wait for the flags, and eight are in flight)
-  for (int k = tid; k < n_chan; k += NT) {
-    double sx = 0.0, sy = 0.0;
-    const int64_t step = nb * n_chan;
-    int64_t o = b * n_chan + k;
+  // (a thread loads eight integrations of four channels at a time, whether
+  // flagged or not: 31 us of this kernel's 52 went to loads that waited for
+  // one another, 16 x 2048 cells of 6 baselines)
+  const int64_t step = nb * n_chan;
+  for (int k0 = tid; k0 < n_chan; k0 += 4 * NT) {
     constexpr int U = 8;
+    double sx[4] = {0.0, 0.0, 0.0, 0.0}, sy[4] = {0.0, 0.0, 0.0, 0.0};
     for (int64_t t = 0; t < n_time; t += U) {
-      float2 v[U];
-      uint8_t f[U];
+      float2 v[U][4];
+      uint8_t f[U][4];
 #pragma unroll
       for (int q = 0; q < U; ++q) {
-        const bool in = t + q < n_time;
-        v[q] = in ? vis[o + q * step] : make_float2(0.f, 0.f);
-        f[q] = in && mask ? mask[o + q * step] : (uint8_t)0;
+        const int64_t row = (t + q < n_time ? t + q : n_time - 1) * step + b * n_chan;
+#pragma unroll
+        for (int c = 0; c < 4; ++c) {
+          const int k = k0 + c * NT < n_chan ? k0 + c * NT : n_chan - 1;
+          v[q][c] = vis[row + k];
+          f[q][c] = 0;
+        }
+        if (mask)
+#pragma unroll
+          for (int c = 0; c < 4; ++c) f[q][c] = mask[row + (k0 + c * NT < n_chan ? k0 + c * NT : n_chan - 1)];
       }
 #pragma unroll
       for (int q = 0; q < U; ++q)
-        if (f[q] == 0) {
-          sx += (double)v[q].x;
-          sy += (double)v[q].y;
-        }
-      o += U * step;
+#pragma unroll
+        for (int c = 0; c < 4; ++c)
+          if (t + q < n_time && f[q][c] == 0) {
+            sx[c] += (double)v[q][c].x;
+            sy[c] += (double)v[q][c].y;
+          }
     }
-    vi[k] = make_float2((float)sx, (float)sy);
+#pragma unroll
+    for (int c = 0; c < 4; ++c)
+      if (k0 + c * NT < n_chan) vi[k0 + c * NT] = make_float2((float)sx[c], (float)sy[c]);
   }
   __syncthreads();
   for (int l = tid; l < NLAG; l += NT) {
