@@ -588,8 +588,8 @@ __global__ void mad_amp4_kernel(const float4* __restrict__ vis, int64_t n_base, 
 // stays MAD_OPEN, and mad_kernel then does it from the start.
 //
 // Bound: HBM, 8 B a visibility read and 1 B written, and the scan's vector
-// instructions beside it.  528 planes of 524288 visibilities: 0.87 ms (sample
-// 0.06, scan 0.69 = 3.6 TB/s, finish 0.18); 2.45 ms with the amplitudes
+// instructions beside it.  528 planes of 524288 visibilities: 0.82 ms (sample
+// 0.06, scan 0.65 = 4.2 TB/s with the lists, finish 0.15); 2.45 ms with the amplitudes
 // written out first and a workgroup per population selecting among them.
 enum { MAD_OPEN = 0, MAD_SCAN = 1, MAD_DONE = 2 };
 struct MadWin {
@@ -758,15 +758,15 @@ mad_sample_kernel(const float2* __restrict__ vis, int64_t n_time, int64_t n_base
   win[blockIdx.x] = w;
 }
 
-constexpr int MAD_SCAN_MED = 384, MAD_SCAN_DEV = 512;  // per wave (256 taken at most between flushes)
+constexpr int MAD_SCAN_LIST = 640;  // per wave; 256 entries at most come between flushes
 
 template <bool VEC>
 __global__ void __launch_bounds__(256)
 mad_scan_kernel(const float2* __restrict__ vis, int64_t n_time, int64_t n_base, int n_chan, int population,
                 int chunks, MadWin* __restrict__ win, float* __restrict__ lists, uint8_t* __restrict__ mask) {
-  constexpr int NT = 256, Q = 4, STEP = 4 * NT * Q;
-  // each wave keeps lists of its own: appending needs no atomics
-  __shared__ float2 med_l[NT / 64][MAD_SCAN_MED], dev_l[NT / 64][MAD_SCAN_DEV];
+  constexpr int NT = 256;
+  // each wave keeps a list of its own: appending needs no atomics
+  __shared__ float2 list_l[NT / 64][MAD_SCAN_LIST];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int64_t id = blockIdx.x / (unsigned)chunks;
   const int64_t i0 = (int64_t)(blockIdx.x % (unsigned)chunks) * MAD_CHUNK;
@@ -779,100 +779,130 @@ mad_scan_kernel(const float2* __restrict__ vis, int64_t n_time, int64_t n_base, 
   float* const g_thr = g_dev + mad_cap_dev(n);
   const float q_lo = w->q_lo, q_hi = w->q_hi, q_l0 = w->q_l0, q_c0 = w->q_c0, q_c1 = w->q_c1, q_r1 = w->q_r1;
   const float q_t0 = mask ? w->q_t0 : __builtin_inff(), q_t1 = w->q_t1;
-  float2* const my_med = med_l[wave];
-  float2* const my_dev = dev_l[wave];
-  unsigned m = 0u, d = 0u, n_le = 0u, n_in = 0u;  // wave-uniform
-  // the lists' exact amplitudes to memory, in any order
-  auto flush = [&]() {
-    unsigned at = 0u;
-    if (lane < 2) at = atomicAdd(lane == 0 ? &w->n_med : &w->n_dev, lane == 0 ? m : d);
-    const unsigned at_m = __builtin_amdgcn_readlane(at, 0), at_d = __builtin_amdgcn_readlane(at, 1);
-    for (unsigned k = lane; k < m; k += 64)
-      if (at_m + k < (unsigned)mad_cap_med(n)) g_med[at_m + k] = amp_f32(my_med[k]);
-    for (unsigned k = lane; k < d; k += 64)
-      if (at_d + k < (unsigned)mad_cap_dev(n)) g_dev[at_d + k] = amp_f32(my_dev[k]);
-    m = 0u;
-    d = 0u;
-  };
+  float2* const list = list_l[wave];
+  unsigned m = 0u;                  // wave-uniform
+  unsigned n_le = 0u, n_in = 0u;    // per lane
   const unsigned long long below = (1ull << lane) - 1ull;
-  auto append = [&](float2* list, unsigned& count, unsigned long long hit, float2 v) {
-    if (hit == 0ull) return;
-    if ((hit >> lane) & 1ull) list[count + (unsigned)__popcll(hit & below)] = v;
-    count += (unsigned)__popcll(hit);
-  };
-  const int64_t end = i0 + MAD_CHUNK < n ? i0 + MAD_CHUNK : n;
-  for (int64_t b0 = i0; b0 < end; b0 += STEP) {
-    float2 v[Q][4];
-#pragma unroll
-    for (int q = 0; q < Q; ++q) {
-      const int64_t i = b0 + 4 * (q * NT + (int)threadIdx.x);
-      if (VEC) {  // n is a multiple of four
-        float4 x = make_float4(0.f, 0.f, 0.f, 0.f), y = x;
-        if (i < n) {
-          const float4* p = reinterpret_cast<const float4*>(vis + pop.off(i));
-          x = p[0];
-          y = p[1];
-        }
-        v[q][0] = make_float2(x.x, x.y), v[q][1] = make_float2(x.z, x.w);
-        v[q][2] = make_float2(y.x, y.y), v[q][3] = make_float2(y.z, y.w);
-      } else {
-#pragma unroll
-        for (int j = 0; j < 4; ++j) v[q][j] = i + j < n ? vis[pop.off(i + j)] : make_float2(0.f, 0.f);
-      }
+  auto square = [](float2 z) -> float { return z.x * z.x + z.y * z.y; };
+  // the list's exact amplitudes to the population's two lists, in any order
+  auto flush = [&]() {
+    unsigned k_med = 0u;
+    for (unsigned k = lane; k < m; k += 64) {
+      const float sq = square(list[k]);
+      k_med += !(sq <= q_lo) && sq <= q_hi;
     }
 #pragma unroll
-    for (int q = 0; q < Q; ++q) {
-      const int64_t i = b0 + 4 * (q * NT + (int)threadIdx.x);
-      if (m > MAD_SCAN_MED - 4 * 64 || d > MAD_SCAN_DEV - 4 * 64) flush();
-      uint32_t flags = 0u;
+    for (int d = 32; d >= 1; d >>= 1) k_med += __shfl_xor(k_med, d);
+    unsigned at = 0u;
+    if (lane < 2) at = atomicAdd(lane == 0 ? &w->n_med : &w->n_dev, lane == 0 ? k_med : m - k_med);
+    unsigned at_m = __builtin_amdgcn_readlane(at, 0), at_d = __builtin_amdgcn_readlane(at, 1);
+    for (unsigned k0 = 0u; k0 < m; k0 += 64) {
+      const bool in = k0 + lane < m;
+      const float2 z = list[in ? k0 + lane : 0];
+      const float sq = square(z), a = amp_f32(z);
+      const bool med = !(sq <= q_lo) && sq <= q_hi;
+      const unsigned long long bm = __ballot(in && med), bd = __ballot(in && !med);
+      const unsigned pm = at_m + (unsigned)__popcll(bm & below), pd = at_d + (unsigned)__popcll(bd & below);
+      if (in && med && pm < (unsigned)mad_cap_med(n)) g_med[pm] = a;
+      if (in && !med && pd < (unsigned)mad_cap_dev(n)) g_dev[pd] = a;
+      at_m += (unsigned)__popcll(bm);
+      at_d += (unsigned)__popcll(bd);
+    }
+    m = 0u;
+  };
+  // four neighbouring elements per thread and step, the next two steps' loads
+  // in flight
+  struct Step {
+    float2 v[4];
+    int64_t off;
+  };
+  auto load = [&](int64_t i) -> Step {
+    Step s;
+    if (VEC) {  // n is a multiple of four
+      s.off = pop.off(i < n ? i : 0);
+      const float4* p = reinterpret_cast<const float4*>(vis + s.off);
+      const float4 x = p[0], y = p[1];
+      s.v[0] = make_float2(x.x, x.y), s.v[1] = make_float2(x.z, x.w);
+      s.v[2] = make_float2(y.x, y.y), s.v[3] = make_float2(y.z, y.w);
+    } else {
 #pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        const float2 z = v[q][j];
-        const float sq = z.x * z.x + z.y * z.y;
-        // tests that a NaN passes: it stands above every amplitude
-        const bool in = i + j < n;
-        const unsigned long long live = __ballot(in);
-        const unsigned long long p_l0 = __ballot(!(sq < q_l0)), p_c0 = __ballot(!(sq < q_c0));
-        const unsigned long long p_lo = __ballot(!(sq <= q_lo)), p_hi = __ballot(!(sq <= q_hi));
-        const unsigned long long p_c1 = __ballot(!(sq <= q_c1)), p_r1 = __ballot(!(sq <= q_r1));
-        n_le += (unsigned)__popcll(live & ~p_lo);
-        n_in += (unsigned)__popcll(live & p_c0 & ~p_c1);
-        append(my_med, m, live & p_lo & ~p_hi, z);
-        append(my_dev, d, live & ((p_l0 & ~p_c0) | (p_c1 & ~p_r1)), z);
-        if (__ballot(!(sq <= q_t0)) != 0ull) {
-          if (sq > q_t1) flags |= 1u << (8 * j);
-          else if (mask && in && !(sq <= q_t0)) {
+      for (int j = 0; j < 4; ++j) s.v[j] = vis[pop.off(i + j < n ? i + j : 0)];
+    }
+    return s;
+  };
+  const int64_t end = i0 + MAD_CHUNK < n ? i0 + MAD_CHUNK : n;
+  int64_t i = i0 + 4 * (int)threadIdx.x;
+  Step s0 = load(i), s1 = load(i + 4 * NT);
+#pragma unroll 1
+  for (int64_t b0 = i0; b0 < end; b0 += 4 * NT, i += 4 * NT) {
+    const Step s = s0;
+    s0 = s1;
+    s1 = load(i + 8 * NT);
+    if (m > MAD_SCAN_LIST - 4 * 64) flush();
+    bool over = false;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      const float sq = square(s.v[j]);
+      // tests that a NaN passes: it stands above every amplitude
+      const bool in = VEC ? i < n : i + j < n;
+      const bool p_c0 = !(sq < q_c0), p_lo = !(sq <= q_lo), p_c1 = !(sq <= q_c1);
+      n_le += in && !p_lo;
+      n_in += in && p_c0 && !p_c1;
+      over = over || !(sq <= q_t0);
+      const unsigned long long hit =
+          __ballot(in) & ((__ballot(!(sq < q_l0)) & ~__ballot(p_c0)) | (__ballot(p_lo) & ~__ballot(!(sq <= q_hi))) |
+                          (__ballot(p_c1) & ~__ballot(!(sq <= q_r1))));
+      if (hit != 0ull) {
+        if ((hit >> lane) & 1ull) list[m + (unsigned)__popcll(hit & below)] = s.v[j];
+        m += (unsigned)__popcll(hit);
+      }
+    }
+    // flags: few amplitudes are over t0, and of those few under t1
+    if (mask) {
+      uint32_t flags = 0u;
+      if (over) {
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+          const float sq = square(s.v[j]);
+          if (sq > q_t1) {
+            flags |= 1u << (8 * j);
+          } else if (i + j < n && !(sq <= q_t0)) {
             const unsigned k = atomicAdd(&w->n_thr, 1u);
             if (k < (unsigned)mad_cap_thr(n)) {
               g_thr[2 * (int64_t)k] = __uint_as_float((uint32_t)(i + j));
-              g_thr[2 * (int64_t)k + 1] = amp_f32(z);
+              g_thr[2 * (int64_t)k + 1] = amp_f32(s.v[j]);
             }
           }
         }
       }
-      if (mask) {
-        if (VEC) {
-          if (i < n) *reinterpret_cast<uint32_t*>(mask + pop.off(i)) = flags;
-        } else {
+      if (VEC) {
+        if (i < n) *reinterpret_cast<uint32_t*>(mask + s.off) = flags;
+      } else {
 #pragma unroll
-          for (int j = 0; j < 4; ++j)
-            if (i + j < n) mask[pop.off(i + j)] = (uint8_t)(flags >> (8 * j));
-        }
+        for (int j = 0; j < 4; ++j)
+          if (i + j < n) mask[pop.off(i + j)] = (uint8_t)(flags >> (8 * j));
       }
     }
   }
   flush();
+#pragma unroll
+  for (int d = 32; d >= 1; d >>= 1) {
+    n_le += __shfl_xor(n_le, d);
+    n_in += __shfl_xor(n_in, d);
+  }
   if (lane < 2) atomicAdd(lane == 0 ? &w->n_le : &w->n_in, lane == 0 ? n_le : n_in);
 }
 
-constexpr int MAD_FINISH_NT = 512;
 constexpr int MAD_FINISH_COMP = 8192;
 
-__global__ void __launch_bounds__(MAD_FINISH_NT)
+// 512 threads leave room for three populations per CU (768 in one round),
+// 1024 halve the time of one where there are CUs enough for all.
+template <int NT>
+__global__ void __launch_bounds__(NT, NT == 512 ? 6 : 4)
 mad_finish_kernel(int64_t n_time, int64_t n_base, int n_chan, float sigma, int population,
                   MadWin* __restrict__ win, const float* __restrict__ lists, uint8_t* __restrict__ mask,
                   double* __restrict__ thresh, double* __restrict__ stats) {
-  constexpr int NT = MAD_FINISH_NT, DB = 11;
+  constexpr int DB = 11;
   __shared__ unsigned hist[1 << DB];
   __shared__ unsigned wsum[NT / 64];
   __shared__ unsigned long long sh[4];
@@ -1181,8 +1211,11 @@ hipError_t launch_mad(const float2* vis, int64_t n_time, int64_t n_base, int n_c
         e = launch(vec ? mad_scan_kernel<true> : mad_scan_kernel<false>, dim3((unsigned)(npop * chunks)),
                    dim3(256), 0, s, vis, n_time, n_base, n_chan, population, chunks, win, lists, mask);
       if (e == hipSuccess)
-        e = launch(mad_finish_kernel, dim3((unsigned)npop), dim3(MAD_FINISH_NT), 0, s, n_time, n_base, n_chan, sigma,
-                   population, win, lists, mask, thresh, stats);
+        e = npop <= device_cu_count()
+                ? launch(mad_finish_kernel<1024>, dim3((unsigned)npop), dim3(1024), 0, s, n_time, n_base, n_chan,
+                         sigma, population, win, lists, mask, thresh, stats)
+                : launch(mad_finish_kernel<512>, dim3((unsigned)npop), dim3(512), 0, s, n_time, n_base, n_chan, sigma,
+                         population, win, lists, mask, thresh, stats);
       if (e != hipSuccess) return e;
       amp_scratch = nullptr;
     }
