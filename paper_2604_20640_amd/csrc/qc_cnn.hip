@@ -772,25 +772,77 @@ __global__ void cnn_adam_kernel(float* __restrict__ w, const float* __restrict__
   w[e] -= lr * (mi / c1) / (sqrtf(vi / c2) + eps);
 }
 
+// log1p(r), r >= 0, to about 1e-15 of the result: y = 1 + r = 2^e m with m in
+// [sqrt(1/2), sqrt(2)), log m = 2 artanh(s), s = (m - 1)/(m + 1), by the series
+// 2 s (1 + s^2/3 + s^4/5 + ...), |s| <= 0.1716, up to s^20/21 (the next term is
+// below 1e-18 of the sum).  Below 2^-10, where 1 + r would drop bits of r, the
+// series of log1p itself up to r^6.  The library's float64 log1p and division
+// took most of the kernel below.
+__device__ __forceinline__ double log1p_pos(double r) {
+  if (r < 0x1p-10)
+    return r * fma(r, fma(r, fma(r, fma(r, fma(r, -1.0 / 6.0, 1.0 / 5.0), -1.0 / 4.0), 1.0 / 3.0), -1.0 / 2.0), 1.0);
+  if (!(r <= 1.7976931348623157e308)) return r;  // infinite, or not a number
+  const double y = 1.0 + r;
+  double m = 2.0 * __builtin_amdgcn_frexp_mant(y);  // [1, 2)
+  int e = __builtin_amdgcn_frexp_exp(y) - 1;
+  if (m >= 1.4142135623730951) {
+    m *= 0.5;
+    ++e;
+  }
+  const double d = m + 1.0;
+  double q = __builtin_amdgcn_rcp(d);
+  q = fma(fma(-d, q, 1.0), q, q);
+  q = fma(fma(-d, q, 1.0), q, q);
+  const double s = (m - 1.0) * q, z = s * s;
+  double p = 1.0 / 21.0;
+  p = fma(p, z, 1.0 / 19.0);
+  p = fma(p, z, 1.0 / 17.0);
+  p = fma(p, z, 1.0 / 15.0);
+  p = fma(p, z, 1.0 / 13.0);
+  p = fma(p, z, 1.0 / 11.0);
+  p = fma(p, z, 1.0 / 9.0);
+  p = fma(p, z, 1.0 / 7.0);
+  p = fma(p, z, 1.0 / 5.0);
+  p = fma(p, z, 1.0 / 3.0);
+  return fma((double)e, 0.693147180559945309417, fma(2.0 * s, p * z, 2.0 * s));
+}
+
 // Network input of one baseline plane: A = |V| (float64, rounded to
-// float32), r = (A - med)/(1.4826 MAD), x = sign(r) log1p|r|.
-__global__ void cnn_normalize_kernel(const float2* __restrict__ vis, const double* __restrict__ stats,
-                                     int64_t n_time, int64_t n_base, int n_chan, int64_t b0, int64_t nb,
-                                     float* __restrict__ x) {
-  const int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  const int64_t per = n_time * n_chan;
-  if (e >= nb * per) return;
-  const int64_t bl = e / per, p = e % per;
-  const int64_t b = b0 + bl, tt = p / n_chan, f = p % n_chan;
-  const float2 v = vis[(tt * n_base + b) * n_chan + f];
-  const double re = (double)v.x, im = (double)v.y;
-  const float A = (float)sqrt(re * re + im * im);
-  const double med = stats[2 * b], mad = stats[2 * b + 1];
-  double scale = 1.4826 * mad;
-  if (scale == 0.0) scale = 1.0;
-  const double r = ((double)A - med) / scale;
-  const double xv = r < 0.0 ? -log1p(-r) : log1p(r);
-  x[e] = (float)xv;
+// float32), r = (A - med)/(1.4826 MAD), x = sign(r) log1p|r|.  A block takes
+// NORM_PER elements of one row (baseline, integration).  Bound: HBM, 12 B an
+// element: 66 planes of 524288 in 122 us, 3.4 TB/s (403 us with the library's
+// log1p and division and a thread per element).
+constexpr int NORM_PER = 1024;
+__global__ void __launch_bounds__(256)
+cnn_normalize_kernel(const float2* __restrict__ vis, const double* __restrict__ stats, int64_t n_time,
+                     int64_t n_base, int n_chan, int64_t b0, int64_t rows, unsigned row_blocks,
+                     float* __restrict__ x) {
+  const int f0 = (int)(blockIdx.x % row_blocks) * NORM_PER;
+  // row = bl * n_time + tt; more than one only beyond 2^30 blocks
+  for (int64_t row = blockIdx.x / row_blocks; row < rows; row += gridDim.x / row_blocks) {
+    const int64_t bl = row / n_time, tt = row - bl * n_time, b = b0 + bl;
+    const double med = stats[2 * b], mad = stats[2 * b + 1];
+    double scale = 1.4826 * mad;
+    if (scale == 0.0) scale = 1.0;
+    const double inv = 1.0 / scale;
+    const float2* const v = vis + (tt * n_base + b) * n_chan;
+    float* const o = x + row * n_chan;
+    float2 in[NORM_PER / 256];
+#pragma unroll
+    for (int i = 0; i < NORM_PER / 256; ++i) {
+      const int f = f0 + i * 256 + (int)threadIdx.x;
+      in[i] = v[f < n_chan ? f : n_chan - 1];
+    }
+#pragma unroll
+    for (int i = 0; i < NORM_PER / 256; ++i) {
+      const int f = f0 + i * 256 + (int)threadIdx.x;
+      const double re = (double)in[i].x, im = (double)in[i].y;
+      const float A = (float)sqrt(re * re + im * im);
+      const double r = ((double)A - med) * inv;
+      const double xv = log1p_pos(fabs(r));
+      if (f < n_chan) o[f] = (float)(r < 0.0 ? -xv : xv);
+    }
+  }
 }
 
 // ---------------------------------------------------------------------------
@@ -955,36 +1007,60 @@ cnn_mfma_conv_kernel(const _Float16* __restrict__ in, const _Float16* __restrict
   }
 }
 
-// L1 (3x3, 1 -> 32, ReLU) from the float32 image to NHWC half.
+// L1 (3x3, 1 -> 32, ReLU) from the float32 image to NHWC half: a thread forms
+// one pixel's 32 channels, and the block's 256 pixels (16 KiB in a row) leave
+// through LDS, 16 bytes a lane.  Bound: HBM, 64 B written a pixel: 282 us
+// for 16.8 M pixels, 3.8 TB/s (382 us with each thread's 64 bytes stored by itself
+// and 64-bit index divisions).
+constexpr int L1_PITCH = 40;  // halves per pixel in LDS: 80 B, conflict-free 16-byte accesses
 __global__ void __launch_bounds__(256)
 cnn_l1_nhwc_kernel(const float* __restrict__ x, const float* __restrict__ w1, const float* __restrict__ b1,
                    int H, int W, int64_t n_pix, _Float16* __restrict__ out) {
-  const int64_t e = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  if (e >= n_pix) return;
-  const int64_t hw = (int64_t)H * W;
-  const int64_t n = e / hw;
-  const int y = (int)((e % hw) / W), xx = (int)(e % W);
-  float v[9];
-#pragma unroll
-  for (int ky = 0; ky < 3; ++ky)
-#pragma unroll
-    for (int kx = 0; kx < 3; ++kx) {
-      const int yy = y + ky - 1, xc = xx + kx - 1;
-      v[ky * 3 + kx] = (yy >= 0 && yy < H && xc >= 0 && xc < W) ? x[n * hw + (int64_t)yy * W + xc] : 0.f;
-    }
+  __shared__ __align__(16) _Float16 st[256 * L1_PITCH];
   typedef _Float16 half8v __attribute__((ext_vector_type(8)));
+  const int64_t e0 = (int64_t)blockIdx.x * 256;
+  const int hw = H * W;
+  // the block's first pixel (uniform), then 32-bit indices within the images
+  const int64_t n0 = e0 / hw;
+  int64_t n = n0;
+  uint32_t p = (uint32_t)(e0 - n0 * hw) + threadIdx.x;
+  while (p >= (uint32_t)hw) {
+    p -= (uint32_t)hw;
+    ++n;
+  }
+  if (e0 + threadIdx.x < n_pix) {
+    const int y = (int)(p / (uint32_t)W), xx = (int)(p - (uint32_t)y * (uint32_t)W);
+    const float* const img = x + n * hw;
+    float v[9];
 #pragma unroll
-  for (int c8 = 0; c8 < 4; ++c8) {
-    half8v o;
+    for (int ky = 0; ky < 3; ++ky)
 #pragma unroll
-    for (int i = 0; i < 8; ++i) {
-      const int co = 8 * c8 + i;
-      float a = b1[co];
+      for (int kx = 0; kx < 3; ++kx) {
+        const int yy = y + ky - 1, xc = xx + kx - 1;
+        v[ky * 3 + kx] = (yy >= 0 && yy < H && xc >= 0 && xc < W) ? img[yy * W + xc] : 0.f;
+      }
 #pragma unroll
-      for (int k = 0; k < 9; ++k) a = fmaf(w1[co * 9 + k], v[k], a);
-      o[i] = (_Float16)fmaxf(a, 0.f);
+    for (int c8 = 0; c8 < 4; ++c8) {
+      half8v o;
+#pragma unroll
+      for (int i = 0; i < 8; ++i) {
+        const int co = 8 * c8 + i;
+        float a = b1[co];
+#pragma unroll
+        for (int k = 0; k < 9; ++k) a = fmaf(w1[co * 9 + k], v[k], a);
+        o[i] = (_Float16)fmaxf(a, 0.f);
+      }
+      *reinterpret_cast<half8v*>(st + threadIdx.x * L1_PITCH + 8 * c8) = o;
     }
-    *reinterpret_cast<half8v*>(out + e * 32 + 8 * c8) = o;
+  }
+  __syncthreads();
+  const int live = n_pix - e0 < 256 ? (int)(n_pix - e0) : 256;
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    const int k = i * 256 + (int)threadIdx.x;  // 16-byte piece k of the block's run
+    if ((k >> 2) < live)
+      *reinterpret_cast<half8v*>(out + e0 * 32 + 8 * k) =
+          *reinterpret_cast<const half8v*>(st + (k >> 2) * L1_PITCH + 8 * (k & 3));
   }
 }
 
@@ -1220,8 +1296,10 @@ hipError_t cnn_normalize(const float2* vis, const double* stats, int64_t n_time,
                          int64_t b0, int64_t nb, float* x, hipStream_t s) {
   const int64_t n = nb * n_time * n_chan;
   if (n <= 0) return hipSuccess;
-  hipLaunchKernelGGL(cnn_normalize_kernel, dim3((unsigned)ceil_div(n, 256)), dim3(256), 0, s, vis, stats, n_time,
-                     n_base, n_chan, b0, nb, x);
+  const int64_t row_blocks = (n_chan + NORM_PER - 1) / NORM_PER, rows = nb * n_time;
+  const int64_t fit = (1ll << 30) / row_blocks;
+  hipLaunchKernelGGL(cnn_normalize_kernel, dim3((unsigned)((rows < fit ? rows : fit) * row_blocks)), dim3(256), 0, s,
+                     vis, stats, n_time, n_base, n_chan, b0, rows, (unsigned)row_blocks, x);
   return hipGetLastError();
 }
 

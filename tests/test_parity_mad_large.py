@@ -82,3 +82,24 @@ def test_not_finite_amplitudes(qc):
     m, T = qc.mad_flag(torch.from_numpy(w).cuda(), 5.0, 0)
     assert np.array_equal(T.cpu().numpy(), T_ref)
     assert np.array_equal(m.cpu().numpy(), m_ref)
+
+
+def test_normalised_input_over_its_range(qc):
+    """The flagger's input sign(r) log1p|r| over 16 decades of r, to one unit
+    of float32 of the float64 value (one rounding each): rows that are not a
+    multiple of a block, a constant plane and infinite amplitudes."""
+    import torch
+    from oracle import cnn
+    rng = np.random.default_rng(4)
+    n_time, n_chan = 8, 1030
+    v = _noise((n_time, 3, n_chan), 12)
+    v[:, 0] += 1000.0
+    v[0, 0, :600] += (10.0 ** rng.uniform(-9, 9, 600)).astype(np.float32)
+    v[:, 1] = 3 + 4j
+    v[1, 2, 5] = np.inf
+    with np.errstate(invalid="ignore"):
+        ref = np.asarray(cnn.normalize(v), np.float64)
+    x = qc.cnn_normalize(torch.from_numpy(v).cuda()).cpu().numpy()
+    fin = np.isfinite(ref)
+    assert np.array_equal(fin, np.isfinite(x))
+    assert np.all(np.abs(x[fin] - ref[fin]) <= 2.0 ** -23 * np.abs(ref[fin]))
