@@ -125,18 +125,25 @@ cnn_conv_kernel(const float* __restrict__ in, const float* __restrict__ wp, cons
 // 8 x 32 pixels (wave w: row w), reduced in two halves of 16 input channels
 // h; within a half, product (q, j) pairs channels 16h + 4q + j and
 // 16h + 8 + 4q + j (lane l: output channel = pixel slot l % 32, the pair's
-// member l / 32), so each lane's operands of four products are 16
-// contiguous bytes in LDS: the weights [tap][h][q][lane][4] (copied once
-// per workgroup, 100 KB) and the staged half-tile channel-fastest,
-// [pixel][16 channels] with an 80-byte pixel stride (conflict-free 16-byte
-// reads).  The next half-tile's values travel in registers while this one
-// is reduced; four accumulators take the four j.  MODE as for
-// cnn_conv_kernel, and 3: forward with ReLU followed by the output layer,
-// writing logits and/or flags instead of the activations.
-constexpr int CM_NTH = 512, CM_HC = 16, CM_PS = 20;
+// member l / 32), and accumulator j takes the q in turn at every tap.  A half
+// is staged in two stages, j = 0, 1 and j = 2, 3, of 8 channels, so that two
+// stages fit the LDS beside the weights: while one is reduced, the next one's
+// values arrive in registers and are stored to the other buffer, and a stage
+// begins with a single barrier.  A lane's operands of a tap's four products
+// are 16 contiguous bytes in LDS: the weights [tap][h][stage][lane][4]
+// (copied once per workgroup, 100 KB) and the pixels
+// [pixel][pair member][4] with a 48-byte pixel stride (conflict-free 16-byte
+// reads).  MODE as for cnn_conv_kernel, and 3: forward with ReLU followed by
+// the output layer, writing logits and/or flags instead of the activations.
+// Bound: the matrix cores (26.8 GFLOP for 32 images of 128 x 128, 177 us at
+// the 152 TFLOP/s that a large product reaches): 248-256 us there, 279-293 us
+// with each value's place formed anew (two divisions) at every stage and a
+// barrier before and after its store.
+constexpr int CM_NTH = 512, CM_PS = 12;
+constexpr int CM_STORE_TAP = 20;  // tap of a stage after which the next one is stored
 
 constexpr int cm_pl(int D) { return (CT_H + 4 * D) * (CT_W + 4 * D); }
-constexpr size_t cm_lds(int D) { return sizeof(float) * (25 * 16 * 64 + cm_pl(D) * CM_PS); }
+constexpr size_t cm_lds(int D) { return sizeof(float) * (25 * 16 * 64 + 2 * cm_pl(D) * CM_PS); }
 
 template <int D, int MODE>
 __global__ void __launch_bounds__(CM_NTH)
@@ -145,46 +152,75 @@ cnn_conv32_mfma_kernel(const float* __restrict__ in, const float* __restrict__ w
                        int64_t n_tiles, float* __restrict__ out, HeadArgs hd) {
   constexpr int C = 32, NT = 25, R = 2 * D;
   constexpr int LH = CT_H + 2 * R, LW = CT_W + 2 * R, PL = LH * LW;
-  constexpr int IH = (CM_HC * PL + CM_NTH - 1) / CM_NTH;
   static_assert(cm_lds(D) <= 160 * 1024, "LDS");
   static_assert(CM_NTH / 64 == CT_H && CT_W == 32, "one tile row per wave, one MFMA column block");
   extern __shared__ float4 sm4[];
-  float4* sw = sm4;                                              // [tap][h][q][lane]
-  float* st = reinterpret_cast<float*>(sm4 + NT * 2 * 2 * 64);  // [pixel][CM_PS]
+  float4* sw = sm4;                                              // [tap][h][stage][lane]
+  float* st = reinterpret_cast<float*>(sm4 + NT * 2 * 2 * 64);  // two of [pixel][CM_PS]
   const int t = threadIdx.x, lane = t & 63;
   const int wave = __builtin_amdgcn_readfirstlane(t >> 6);
   const int px = lane & 31, kh = lane >> 5;
-  for (int e = t; e < NT * 2 * 2 * 64; e += CM_NTH) {
-    const int l = e & 63, q = (e >> 6) & 1, h = (e >> 7) & 1, tap = e >> 8;
-    const int c0 = 16 * h + 8 * (l >> 5) + 4 * q, co = l & 31;
-    sw[e] = make_float4(wp[((c0 + 0) * NT + tap) * C + co], wp[((c0 + 1) * NT + tap) * C + co],
-                        wp[((c0 + 2) * NT + tap) * C + co], wp[((c0 + 3) * NT + tap) * C + co]);
+  {
+    // all of the thread's weights in flight at once
+    constexpr int NWT = NT * 2 * 2 * 64, IW = (NWT + CM_NTH - 1) / CM_NTH;
+    float4 wv[IW];
+#pragma unroll
+    for (int i = 0; i < IW; ++i) {
+      const int e = t + i * CM_NTH < NWT ? t + i * CM_NTH : t;
+      const int l = e & 63, sg = (e >> 6) & 1, h = (e >> 7) & 1, tap = e >> 8;
+      const float* const p = wp + ((16 * h + 8 * (l >> 5) + 2 * sg) * NT + tap) * C + (l & 31);
+      wv[i] = make_float4(p[0], p[NT * C], p[4 * NT * C], p[5 * NT * C]);
+    }
+#pragma unroll
+    for (int i = 0; i < IW; ++i)
+      if (t + i * CM_NTH < NWT) sw[t + i * CM_NTH] = wv[i];
   }
   float bco[16];
 #pragma unroll
   for (int r = 0; r < 16; ++r) bco[r] = MODE != 1 ? bias[8 * (r >> 2) + 4 * kh + (r & 3)] : 0.f;
   const int HW = H * W;             // C * H * W < 2^31: 32-bit offsets in an image
-  float pre[IH];
-  // half h of tile tl: input channels 16 h .. 16 h + 15 with the halo,
-  // element f = [channel][row][col] (coalesced global reads)
-  auto load_half = [&](int64_t tl, int h) {
+  // Staging: thread t takes pair member t / 256, channels 0, 1, 4 and 5 of
+  // its eight, at pixels t % 256 + 256 j of the tile with its halo (coalesced
+  // global reads, one 16-byte LDS store per pixel); the pixels' places are
+  // formed once.
+  constexpr int NJ = (PL + 255) / 256;
+  const int km = t >> 8;
+  float4 pre[NJ];
+  uint32_t off[NJ];                 // from the tile's first halo pixel
+  int rq[NJ];
+#pragma unroll
+  for (int j = 0; j < NJ; ++j) {
+    const int p = (t & 255) + 256 * j, r = p / LW, q = p % LW;
+    off[j] = p < PL ? (uint32_t)(r * W + q) : 0u;
+    rq[j] = p < PL ? r << 16 | q : 0;
+  }
+  auto load_stage = [&](int64_t tl, int h, int sg) {
     const int64_t n = tl / tiles_per_img;
     const int tt = (int)(tl % tiles_per_img);
-    const int y0 = (tt / tiles_x) * CT_H, x0 = (tt % tiles_x) * CT_W;
-    const float* ip = in + img_off(n, CM_HC * h, C, H, W);
-    int tv = t;
-    asm volatile("" : "+v"(tv));    // offsets are recomputed per stage, not held live
+    const int y0 = (tt / tiles_x) * CT_H - R, x0 = (tt % tiles_x) * CT_W - R;
+    const float* const ip = in + img_off(n, 16 * h + 8 * km + 2 * sg, C, H, W) + ((int64_t)y0 * W + x0);
+    const uint32_t safe = (uint32_t)(R * W + R);  // the tile's first own pixel
 #pragma unroll
-    for (int i = 0; i < IH; ++i) {
-      const int f = tv + CM_NTH * i;
-      const int c = f / PL, r = (f / LW) % LH, q = f % LW;
-      const int y = y0 + r - R, x = x0 + q - R;
-      const bool ok = (IH * CM_NTH == CM_HC * PL || f < CM_HC * PL) && y >= 0 && y < H && x >= 0 && x < W;
-      const float v = ip[ok ? c * HW + y * W + x : 0];
-      pre[i] = ok ? v : 0.f;
+    for (int j = 0; j < NJ; ++j) {
+      const int y = y0 + (rq[j] >> 16), x = x0 + (rq[j] & 0xffff);
+      const bool ok = y >= 0 && y < H && x >= 0 && x < W;
+      const float* const v = ip + (ok ? off[j] : safe);
+      pre[j] = make_float4(v[0], v[HW], v[4 * HW], v[5 * HW]);
+      if (!ok) pre[j] = make_float4(0.f, 0.f, 0.f, 0.f);
     }
   };
-  if ((int64_t)blockIdx.x < n_tiles) load_half(blockIdx.x, 0);
+  auto store_stage = [&](int buf) {
+    float* const o = st + buf * (PL * CM_PS) + 4 * km;
+#pragma unroll
+    for (int j = 0; j < NJ; ++j) {
+      const int p = (t & 255) + 256 * j;
+      if (PL % 256 == 0 || p < PL) *reinterpret_cast<float4*>(o + p * CM_PS) = pre[j];
+    }
+  };
+  if ((int64_t)blockIdx.x < n_tiles) {
+    load_stage(blockIdx.x, 0, 0);
+    store_stage(0);
+  }
   for (int64_t tl = blockIdx.x; tl < n_tiles; tl += gridDim.x) {
     mf32x16_t acc[4];
 #pragma unroll
@@ -193,47 +229,39 @@ cnn_conv32_mfma_kernel(const float* __restrict__ in, const float* __restrict__ w
       for (int r = 0; r < 16; ++r) acc[j][r] = 0.f;
 #pragma unroll 1
     for (int h = 0; h < 2; ++h) {
-      __syncthreads();  // the previous stage's reads are done (and the weights stored)
-      {
-        int tv = t;
-        asm volatile("" : "+v"(tv));
 #pragma unroll
-        for (int i = 0; i < IH; ++i) {
-          const int f = tv + CM_NTH * i;
-          if (IH * CM_NTH == CM_HC * PL || f < CM_HC * PL) st[(f % PL) * CM_PS + f / PL] = pre[i];
+      for (int sg = 0; sg < 2; ++sg) {
+        // this stage's values are stored, and the other buffer's reads are done
+        __syncthreads();
+        const bool more = sg == 0 || h == 0 || tl + gridDim.x < n_tiles;
+        const float4* const ab = sw + (h * 2 + sg) * 64 + lane;
+        const float* const bb = st + sg * (PL * CM_PS) + (wave * LW + px) * CM_PS + 4 * kh;
+        // operands of tap + 1 are read while tap's products run
+        float4 a = ab[0], b = *reinterpret_cast<const float4*>(bb);
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int tap = 0; tap < NT; ++tap) {
+          const int tn = tap + 1 < NT ? tap + 1 : tap;
+          const float4 an = ab[tn * 4 * 64];
+          const float4 bn = *reinterpret_cast<const float4*>(bb + ((tn / 5) * D * LW + (tn % 5) * D) * CM_PS);
+          __builtin_amdgcn_sched_barrier(0);
+          acc[2 * sg] = __builtin_amdgcn_mfma_f32_32x32x2f32(a.x, b.x, acc[2 * sg], 0, 0, 0);
+          acc[2 * sg + 1] = __builtin_amdgcn_mfma_f32_32x32x2f32(a.y, b.y, acc[2 * sg + 1], 0, 0, 0);
+          acc[2 * sg] = __builtin_amdgcn_mfma_f32_32x32x2f32(a.z, b.z, acc[2 * sg], 0, 0, 0);
+          acc[2 * sg + 1] = __builtin_amdgcn_mfma_f32_32x32x2f32(a.w, b.w, acc[2 * sg + 1], 0, 0, 0);
+          __builtin_amdgcn_sched_barrier(0);
+          a = an;
+          b = bn;
+          if (tap == 0 && more) {
+            if (sg == 0)
+              load_stage(tl, h, 1);
+            else if (h == 0)
+              load_stage(tl, 1, 0);
+            else
+              load_stage(tl + gridDim.x, 0, 0);
+          }
+          if (tap == CM_STORE_TAP && more) store_stage(1 - sg);
         }
-      }
-      __syncthreads();
-      if (h == 0)
-        load_half(tl, 1);
-      else if (tl + gridDim.x < n_tiles)
-        load_half(tl + gridDim.x, 0);
-      const float4* ab = sw + h * 2 * 64 + lane;
-      const float* bb = st + (wave * LW + px) * CM_PS + 8 * kh;
-      // operands of tap + 1 are read while tap's products run
-      float4 a0 = ab[0], a1 = ab[64];
-      float4 b0 = *reinterpret_cast<const float4*>(bb), b1 = *reinterpret_cast<const float4*>(bb + 4);
-#pragma unroll 5
-      for (int tap = 0; tap < NT; ++tap) {
-        const int tn = tap + 1 < NT ? tap + 1 : tap;
-        const float4* a = ab + tn * 4 * 64;
-        const float* b = bb + ((tn / 5) * D * LW + (tn % 5) * D) * CM_PS;
-        const float4 an0 = a[0], an1 = a[64];
-        const float4 bn0 = *reinterpret_cast<const float4*>(b), bn1 = *reinterpret_cast<const float4*>(b + 4);
-        __builtin_amdgcn_sched_barrier(0);
-        acc[0] = __builtin_amdgcn_mfma_f32_32x32x2f32(a0.x, b0.x, acc[0], 0, 0, 0);
-        acc[1] = __builtin_amdgcn_mfma_f32_32x32x2f32(a0.y, b0.y, acc[1], 0, 0, 0);
-        acc[2] = __builtin_amdgcn_mfma_f32_32x32x2f32(a0.z, b0.z, acc[2], 0, 0, 0);
-        acc[3] = __builtin_amdgcn_mfma_f32_32x32x2f32(a0.w, b0.w, acc[3], 0, 0, 0);
-        acc[0] = __builtin_amdgcn_mfma_f32_32x32x2f32(a1.x, b1.x, acc[0], 0, 0, 0);
-        acc[1] = __builtin_amdgcn_mfma_f32_32x32x2f32(a1.y, b1.y, acc[1], 0, 0, 0);
-        acc[2] = __builtin_amdgcn_mfma_f32_32x32x2f32(a1.z, b1.z, acc[2], 0, 0, 0);
-        acc[3] = __builtin_amdgcn_mfma_f32_32x32x2f32(a1.w, b1.w, acc[3], 0, 0, 0);
-        __builtin_amdgcn_sched_barrier(0);
-        a0 = an0;
-        a1 = an1;
-        b0 = bn0;
-        b1 = bn1;
       }
     }
     const int64_t n = tl / tiles_per_img;
@@ -365,38 +393,34 @@ cnn_wgrad32_kernel(const float* __restrict__ a, const float* __restrict__ g, int
   }
 }
 
-// One staged pixel tile's products for a wave's NQ taps: rows of 32 pixels,
-// each two pixels per step (lanes 32..63 the odd one), every tap's operand at
-// the tap's offset from the same pixel.  g points at channel cl's gradient
-// row plus the lane's pixel slot, a at channel cl's input tile likewise.
-template <int NQ, int TG, int LW>
-__device__ __forceinline__ void wgrad_tile_products(const float* __restrict__ g, const float* __restrict__ a,
-                                                    const int (&toff)[TG], mf32x16_t (&acc)[TG]) {
+// The products of one row of a staged pixel tile for NQ of a wave's taps:
+// two pixels per step (lanes 32..63 the odd one), every tap's operand at the
+// tap's offset from the same pixel.  gr points at channel cl's gradient row
+// plus the lane's pixel slot, a at channel cl's input row likewise.
+template <int NQ, int TG>
+__device__ __forceinline__ void wgrad_row_products(const float* __restrict__ gr, const float* __restrict__ a,
+                                                   const int (&toff)[TG], mf32x16_t (&acc)[TG]) {
   // operands of step px + 2 are read before step px's products are issued
-#pragma unroll 1
-  for (int py = 0; py < CT_H; ++py) {
-    const float* gr = g + py * CT_W;
-    const float* ar[NQ];
+  const float* ar[NQ];
 #pragma unroll
-    for (int q = 0; q < NQ; ++q) ar[q] = a + py * LW + toff[q];
-    float gv = gr[0], av[NQ];
+  for (int q = 0; q < NQ; ++q) ar[q] = a + toff[q];
+  float gv = gr[0], av[NQ];
 #pragma unroll
-    for (int q = 0; q < NQ; ++q) av[q] = ar[q][0];
+  for (int q = 0; q < NQ; ++q) av[q] = ar[q][0];
 #pragma unroll
-    for (int px = 0; px < CT_W; px += 2) {
-      float gn = 0.f, an[NQ];
-      if (px + 2 < CT_W) {
-        gn = gr[px + 2];
+  for (int px = 0; px < CT_W; px += 2) {
+    float gn = 0.f, an[NQ];
+    if (px + 2 < CT_W) {
+      gn = gr[px + 2];
 #pragma unroll
-        for (int q = 0; q < NQ; ++q) an[q] = ar[q][px + 2];
-      }
-      __builtin_amdgcn_sched_barrier(0);   // keep the reads ahead of the products
-#pragma unroll
-      for (int q = 0; q < NQ; ++q) acc[q] = __builtin_amdgcn_mfma_f32_32x32x2f32(gv, av[q], acc[q], 0, 0, 0);
-      gv = gn;
-#pragma unroll
-      for (int q = 0; q < NQ; ++q) av[q] = an[q];
+      for (int q = 0; q < NQ; ++q) an[q] = ar[q][px + 2];
     }
+    __builtin_amdgcn_sched_barrier(0);   // keep the reads ahead of the products
+#pragma unroll
+    for (int q = 0; q < NQ; ++q) acc[q] = __builtin_amdgcn_mfma_f32_32x32x2f32(gv, av[q], acc[q], 0, 0, 0);
+    gv = gn;
+#pragma unroll
+    for (int q = 0; q < NQ; ++q) av[q] = an[q];
   }
 }
 
@@ -406,11 +430,16 @@ __device__ __forceinline__ void wgrad_tile_products(const float* __restrict__ g,
 // by v_mfma_f32_32x32x2_f32 (lane l: channel l % 32, pixel slot l / 32 of
 // both operands).  All 32 input channels of a pixel tile are staged at once,
 // the next tile's values travelling in registers while this one is reduced.
-// Wave w owns taps w, w + 8, w + 16, w + 24, so that the two waves sharing a
-// SIMD hold 6 or 7 of the 25 taps.  The bias gradient is summed from the
-// staged tile, 16 lanes per output channel.  Workgroups stride over pixel
-// tiles and write their partial sums to part[block][...] in the layout of
-// the vector-ALU kernel.
+// Wave w owns taps w, w + 8 and w + 16 of every pixel and the last tap of
+// tile row w (its eight sums are added in wave order at the end), so that all
+// waves issue the same number of products; with tap 24 held by wave 0 alone
+// its SIMD had 7 products to the others' 6.  The bias gradient is summed from
+// the staged tile, 16 lanes per output channel.  Workgroups stride over pixel
+// tiles and write their partial sums, put in order in LDS, to part[block][...]
+// in the layout of the vector-ALU kernel.  Bound: the matrix cores, as the
+// convolution: 250 us for 32 images of 128 x 128 (290-295 us with tap 24 on
+// one wave and the sums stored from the registers, 313-326 us before that
+// with the staged values' places formed anew for every tile).
 template <int K, int D>
 __global__ void __launch_bounds__(512)
 cnn_wgrad32_mfma_kernel(const float* __restrict__ a, const float* __restrict__ g, int H, int W,
@@ -421,9 +450,10 @@ cnn_wgrad32_mfma_kernel(const float* __restrict__ a, const float* __restrict__ g
   constexpr int AS = LH * LW + 1;   // odd channel strides: the 32 channels a
   constexpr int GS = CNT + 1;       // wave reads at one pixel hit distinct banks
   constexpr int NT = K * K;
-  constexpr int TG = (NT + NW - 1) / NW;
-  constexpr int IG = C * CNT / NTH, IA = C * LH * LW / NTH, ITER = IG + IA;
-  static_assert(IG * NTH == C * CNT && IA * NTH == C * LH * LW && NTH % CNT == 0, "whole staging rounds");
+  constexpr int TQ = NT / NW, TG = TQ + 1;   // whole taps of a wave; the shared one
+  static_assert(NT == TQ * NW + 1 && CT_H == NW, "one shared tap, a tile row of it per wave");
+  constexpr int IG = C * CNT / NTH, PL = LH * LW, NJ = (PL + 127) / 128, CG = C / (NTH / 128);
+  static_assert(IG * NTH == C * CNT && NTH % CNT == 0, "whole staging rounds");
   static_assert(CNT % 2 == 0 && CNT == 16 * 16, "pixel pairs; 16 lanes x 16 pixels per bias sum");
   extern __shared__ float sm[];
   float* sg = sm;                   // [32][GS]
@@ -440,79 +470,100 @@ cnn_wgrad32_mfma_kernel(const float* __restrict__ a, const float* __restrict__ g
   int toff[TG];                     // LDS offsets of the wave's taps (uniform)
 #pragma unroll
   for (int q = 0; q < TG; ++q) {
-    const int tap = wave + NW * q;
-    toff[q] = tap < NT ? (tap / K) * D * LW + (tap % K) * D : 0;
+    const int tap = q < TQ ? wave + NW * q : NT - 1;
+    toff[q] = (tap / K) * D * LW + (tap % K) * D;
   }
-  const int nq = wave + NW * (TG - 1) < NT ? TG : TG - 1;
-  static_assert(NW * (TG - 1) < NT, "every wave holds at least TG - 1 taps");
-  float pre[ITER];
+  float preg[IG], prea[NJ][CG];
   const int HW = H * W;             // C * H * W < 2^31: 32-bit offsets in an image
   // Staging: the gradient tile as 16 rounds of 2 channels (thread t: channel
-  // t / 256 + 2 i, pixel t % 256), the input tile with halo as IA rounds over
-  // [channel][row][col].  Padding reads a valid element and discards it, so
-  // the loads are straight-line code.
+  // t / 256 + 2 i, pixel t % 256); of the input tile with halo, channels
+  // 8 (t / 128) .. + 7 at pixels t % 128 + 128 j, whose places are formed
+  // once.  Padding reads a valid element and discards it, so the loads are
+  // straight-line code.
+  const int cg = CG * (t >> 7);
+  uint32_t off[NJ];                 // from the tile's first halo pixel
+  int rq[NJ];
+#pragma unroll
+  for (int j = 0; j < NJ; ++j) {
+    const int p = (t & 127) + 128 * j, r = p / LW, q = p % LW;
+    off[j] = p < PL ? (uint32_t)(r * W + q) : 0u;
+    rq[j] = p < PL ? r << 16 | q : 0;
+  }
   auto load_tile = [&](int64_t tl) {
     const int64_t n = tl / tiles_per_img;
     const int tt = (int)(tl % tiles_per_img);
     const int y0 = (tt / tiles_x) * CT_H, x0 = (tt % tiles_x) * CT_W;
-    const float* gi = g + img_off(n, 0, C, H, W);
-    const float* ai = a + img_off(n, 0, C, H, W);
-    int tv = t, hw = HW;
-    asm volatile("" : "+v"(tv), "+s"(hw));   // offsets are recomputed per tile, not held live
     {
-      const int p = tv % CNT, y = y0 + p / CT_W, x = x0 + p % CT_W;
+      const int p = t % CNT, y = y0 + p / CT_W, x = x0 + p % CT_W;
       const bool in = y < H && x < W;
-      int o = in ? (tv / CNT) * hw + y * W + x : 0;
-      const int step = in ? (NTH / CNT) * hw : 0;
+      const float* const gi = g + img_off(n, 0, C, H, W) + (in ? (t / CNT) * HW + y * W + x : 0);
+      const int step = in ? (NTH / CNT) * HW : 0;
 #pragma unroll
-      for (int i = 0; i < IG; ++i, o += step) {
-        const float v = gi[o];
-        pre[i] = in ? v : 0.f;
+      for (int i = 0; i < IG; ++i) {
+        const float v = gi[(int64_t)i * step];
+        preg[i] = in ? v : 0.f;
       }
     }
+    const float* const ai = a + img_off(n, cg, C, H, W) + ((int64_t)(y0 - R) * W + (x0 - R));
+    const uint32_t safe = (uint32_t)(R * W + R);  // the tile's first own pixel
 #pragma unroll
-    for (int i = 0; i < IA; ++i) {
-      const int f = tv + NTH * i;
-      const int c = f / (LH * LW), r = (f / LW) % LH, q = f % LW;
-      const int y = y0 + r - R, x = x0 + q - R;
-      const bool in = y >= 0 && y < H && x >= 0 && x < W;
-      const float v = ai[in ? c * HW + y * W + x : 0];
-      pre[IG + i] = in ? v : 0.f;
+    for (int j = 0; j < NJ; ++j) {
+      const int y = y0 - R + (rq[j] >> 16), x = x0 - R + (rq[j] & 0xffff);
+      const bool ok = y >= 0 && y < H && x >= 0 && x < W;
+      const float* const v = ai + (ok ? off[j] : safe);
+#pragma unroll
+      for (int c = 0; c < CG; ++c) {
+        const float f = v[(int64_t)c * HW];
+        prea[j][c] = ok ? f : 0.f;
+      }
     }
   };
   if (blockIdx.x < n_tiles) load_tile(blockIdx.x);
   for (int64_t tl = blockIdx.x; tl < n_tiles; tl += gridDim.x) {
     __syncthreads();  // the previous tile's reads are done
-    int tv = t;
-    asm volatile("" : "+v"(tv));
 #pragma unroll
-    for (int i = 0; i < IG; ++i) sg[((NTH / CNT) * i + tv / CNT) * GS + tv % CNT] = pre[i];
+    for (int i = 0; i < IG; ++i) sg[((NTH / CNT) * i + t / CNT) * GS + t % CNT] = preg[i];
 #pragma unroll
-    for (int i = 0; i < IA; ++i) {
-      const int f = tv + NTH * i;
-      sa[f + f / (LH * LW)] = pre[IG + i];   // channel stride LH * LW + 1
+    for (int j = 0; j < NJ; ++j) {
+      const int p = (t & 127) + 128 * j;
+      if (PL % 128 == 0 || p < PL)
+#pragma unroll
+        for (int c = 0; c < CG; ++c) sa[(cg + c) * AS + p] = prea[j][c];
     }
     __syncthreads();
     if (tl + gridDim.x < n_tiles) load_tile(tl + gridDim.x);
 #pragma unroll
     for (int j = 0; j < 16; ++j) sb += sg[(t >> 4) * GS + (t & 15) + 16 * j];
-    if (nq == TG)
-      wgrad_tile_products<TG, TG, LW>(sg + cl * GS + kh, sa + cl * AS + kh, toff, acc);
-    else
-      wgrad_tile_products<TG - 1, TG, LW>(sg + cl * GS + kh, sa + cl * AS + kh, toff, acc);
-  }
-  float* out = part + (int64_t)blockIdx.x * (C * C * NT + C);
-#pragma unroll
-  for (int q = 0; q < TG; ++q) {
-    const int tap = wave + NW * q;
-    if (tap < NT) {
-#pragma unroll
-      for (int r = 0; r < 16; ++r) {
-        const int o = 8 * (r >> 2) + 4 * kh + (r & 3);   // accumulator row
-        out[(o * C + cl) * NT + tap] = acc[q][r];
-      }
+#pragma unroll 1
+    for (int py = 0; py < CT_H; ++py) {
+      const float* const gr = sg + cl * GS + kh + py * CT_W;
+      const float* const ar = sa + cl * AS + kh + py * LW;
+      if (py == wave)
+        wgrad_row_products<TG>(gr, ar, toff, acc);
+      else
+        wgrad_row_products<TQ>(gr, ar, toff, acc);
     }
   }
+  float* out = part + (int64_t)blockIdx.x * (C * C * NT + C);
+  float* const so = sm;              // [output][input][tap]
+  float* const sl = sm + C * C * NT;  // the shared tap's sums [wave][output][input]
+  __syncthreads();
+#pragma unroll
+  for (int r = 0; r < 16; ++r) {
+    const int e = (8 * (r >> 2) + 4 * kh + (r & 3)) * C + cl;   // accumulator row: output
+#pragma unroll
+    for (int q = 0; q < TQ; ++q) so[e * NT + wave + NW * q] = acc[q][r];
+    sl[wave * C * C + e] = acc[TQ][r];
+  }
+  __syncthreads();
+  for (int e = t; e < C * C; e += NTH) {
+    float v = sl[e];
+#pragma unroll
+    for (int w = 1; w < NW; ++w) v += sl[w * C * C + e];
+    so[e * NT + NT - 1] = v;
+  }
+  __syncthreads();
+  for (int e = t; e < C * C * NT; e += NTH) out[e] = so[e];
 #pragma unroll
   for (int m = 8; m >= 1; m >>= 1) sb += __shfl_xor(sb, m, 16);
   if ((t & 15) == 0) out[C * C * NT + (t >> 4)] = sb;
@@ -1140,7 +1191,10 @@ static hipError_t wgrad32_t(const float* a, const float* g, int64_t n_img, int H
   if (g_cnn_mfma && 32LL * H * W < (1LL << 31)) {
     // one 512-thread workgroup fills a CU's LDS: one per CU
     if (blocks > 256) blocks = 256;
-    const size_t lds = sizeof(float) * (32 * (CNT + 1) + 32 * (LH * LW + 1));
+    // the two staged tiles, or the sums at the end
+    constexpr size_t tiles = 32 * (CNT + 1) + 32 * (LH * LW + 1), sums = 32 * 32 * (K * K + 8);
+    constexpr size_t lds = sizeof(float) * (tiles > sums ? tiles : sums);
+    static_assert(lds <= 160 * 1024, "LDS");
     const void* k = reinterpret_cast<const void*>(cnn_wgrad32_mfma_kernel<K, D>);
     hipError_t e = hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
     if (e != hipSuccess) return e;
