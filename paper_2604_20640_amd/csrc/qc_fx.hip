@@ -1042,7 +1042,7 @@ static hipError_t launch_fused_p(const FxArgs& a, int64_t n_dump, int64_t spd, i
 // points: 4 antennas 319 us on the ping-pong ring, 366 on the in-place one, 540
 // and more on the others; 32768 spectra of 1024, 8 antennas: 561 us with 8
 // values per thread, 840 with 16).  A shape that stands twice keeps its index
-// in saved tuning results.
+// in saved tuning results; the in-place ring of (4096, 4) is a candidate.
 struct FusedTile {
   int S, V;  // S = 0: ring variant (one spectrum in flight, register ring)
   bool PP;
@@ -1061,7 +1061,7 @@ struct TileList {
     static constexpr int count = (int)(sizeof(tiles) / sizeof(tiles[0]));       \
   };
 QC_TILES(4096, 4, {0, 16, true, 0}, {1, 16, false, 0}, {1, 16, true, 0}, {2, 16, false, 0},
-         {1, 8, true, 0}, {1, 16, false, 4}, {0, 16, true, 0})
+         {1, 8, true, 0}, {1, 16, false, 4}, {0, 16, true, 0}, {0, 16, false, 0})
 QC_TILES(1024, 4, {2, 16, true, 0}, {2, 16, false, 0}, {4, 16, false, 0}, {2, 8, true, 0},
          {1, 16, true, 4}, {2, 16, false, 4}, {0, 16, false, 0})
 QC_TILES(2048, 4, {0, 16, false, 0}, {1, 16, true, 0}, {1, 16, false, 0}, {1, 16, false, 4},
