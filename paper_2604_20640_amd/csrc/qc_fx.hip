@@ -1270,8 +1270,12 @@ __device__ __forceinline__ void hist_copy_body(const HistCopy& h, int a, int bx)
   }
 }
 
+// I: unsigned index type that holds elems and a dump's grid (uint32_t wherever
+// it can: one partial of 528 baselines x 2048 channels 10.6 us with 64-bit
+// divisions, 9.3 without)
+template <typename I>
 __global__ void __launch_bounds__(256)
-reduce_partials_kernel(const float2* __restrict__ part, int64_t cpd, int64_t elems, int64_t bx_per_dump, int segs,
+reduce_partials_kernel(const float2* __restrict__ part, int64_t cpd, int64_t elems, unsigned bx_per_dump, int segs,
                        float scale, int accumulate, int tile, int64_t nb, int64_t n_chan,
                        float2* __restrict__ vis, int64_t sum_blocks, HistCopy hc) {
   if ((int64_t)blockIdx.x >= sum_blocks) {
@@ -1280,15 +1284,16 @@ reduce_partials_kernel(const float2* __restrict__ part, int64_t cpd, int64_t ele
     return;
   }
   __shared__ float2 red[256];
-  const int per = 256 / segs;  // elements per block
-  const int col = threadIdx.x % per, seg = threadIdx.x / per;
+  const int lg = 31 - __clz(segs);     // segs is a power of two
+  const unsigned per = 256u >> lg;     // elements per block
+  const int col = (int)(threadIdx.x & (per - 1)), seg = (int)(threadIdx.x >> (8 - lg));
   const int64_t d = blockIdx.x / bx_per_dump;
-  const int64_t bx = blockIdx.x % bx_per_dump;
-  const int64_t c_lo = cpd * seg / segs, c_hi = cpd * (seg + 1) / segs;
-  for (int64_t e0 = bx * per; e0 < elems; e0 += bx_per_dump * per) {
-    const int64_t e = e0 + col;
+  const unsigned bx = blockIdx.x % bx_per_dump;
+  const int64_t c_lo = (cpd * seg) >> lg, c_hi = (cpd * (seg + 1)) >> lg;
+  for (I e0 = (I)bx * per; e0 < (I)elems; e0 += (I)bx_per_dump * per) {
+    const I e = e0 + col;
     float2 sacc = make_float2(0.f, 0.f);
-    if (e < elems) {
+    if (e < (I)elems) {
       const float2* p = part + (d * cpd + c_lo) * elems + e;
       int64_t c = c_lo;
       for (; c + 8 <= c_hi; c += 8, p += 8 * elems) {
@@ -1307,14 +1312,14 @@ reduce_partials_kernel(const float2* __restrict__ part, int64_t cpd, int64_t ele
         for (int g = 1; g < segs; ++g) sacc = cadd(sacc, red[g * per + col]);
       __syncthreads();
     }
-    if (seg != 0 || e >= elems) continue;
+    if (seg != 0 || e >= (I)elems) continue;
     sacc.x *= scale;
     sacc.y *= scale;
-    int64_t oe = e;
+    int64_t oe = (int64_t)e;
     if (tile > 0) {
-      const int64_t t = e / tile, tcol = e - t * tile;
-      const int64_t cb = t / nb, b = t - cb * nb;
-      oe = b * n_chan + cb * tile + tcol;
+      const I t = e / (I)tile, tcol = e - t * (I)tile;
+      const I cb = t / (I)nb, b = t - cb * (I)nb;
+      oe = (int64_t)b * n_chan + (int64_t)(cb * (I)tile + tcol);
     }
     float2* o = vis + d * elems + oe;
     if (accumulate) {
@@ -1347,8 +1352,12 @@ hipError_t launch_reduce(const float2* part, int64_t n_dump, int64_t cpd, int64_
     hc = HistCopy{hist->x, hist->ld_x, hist->n_samp, hist->hist, hist->keep, hist->out, (int)hb};
     extra = hb * hist->n_ant;
   }
-  return launch(reduce_partials_kernel, dim3((unsigned)(bx * n_dump + extra)), dim3(256), 0, s, part, cpd, elems, bx,
-                segs, scale, accumulate, tile, nb, n_chan, vis, bx * n_dump, hc);
+  const dim3 grid((unsigned)(bx * n_dump + extra));
+  if (elems < (1LL << 31))  // a dump's grid adds at most 2^20 elements
+    return launch(reduce_partials_kernel<uint32_t>, grid, dim3(256), 0, s, part, cpd, elems, (unsigned)bx, segs, scale,
+                  accumulate, tile, nb, n_chan, vis, bx * n_dump, hc);
+  return launch(reduce_partials_kernel<uint64_t>, grid, dim3(256), 0, s, part, cpd, elems, (unsigned)bx, segs, scale,
+                accumulate, tile, nb, n_chan, vis, bx * n_dump, hc);
 }
 
 // ---------------------------------------------------------------------------
@@ -1357,6 +1366,13 @@ hipError_t launch_reduce(const float2* part, int64_t n_dump, int64_t cpd, int64_
 __device__ __forceinline__ uint16_t enc_f16(float v) {
   v = fminf(fmaxf(v, -65504.f), 65504.f);
   return __half_as_ushort(__float2half_rn(v));
+}
+
+// Two values to FP16 (re in the low half): as enc_f16, one packed conversion.
+__device__ __forceinline__ uint32_t enc_f16x2(float re, float im) {
+  typedef _Float16 half2_t __attribute__((ext_vector_type(2)));
+  const half2_t h = {(_Float16)fminf(fmaxf(re, -65504.f), 65504.f), (_Float16)fminf(fmaxf(im, -65504.f), 65504.f)};
+  return __builtin_bit_cast(uint32_t, h);
 }
 
 __device__ __forceinline__ uint16_t enc_bf16(float v) {
@@ -1481,7 +1497,10 @@ channelize_kernel(const int8_t* __restrict__ x, int64_t ld_x, int n_ant, int64_t
 // shorter filter of n_taps runs with zero taps on the older blocks.
 // With PP the transform ping-pongs between two buffers as in the fused
 // ping-pong tile (one barrier per radix pass, none after the stores);
-// without it the transform runs in place.
+// without it the transform runs in place.  Bound: vector issue, at a power
+// limit: the F+X of 32 antennas x 4096 spectra of 4096 points in FP16 takes 872 us,
+// 898 us with a conversion per value and a test of the antenna per store, and
+// no less with the reduction after it left out.
 template <int N, int NA, int V, int P, bool PP = false>
 struct ChanRingCfg {
   using C = FusedCfg<N, NA, 1, V, false, 0>;
@@ -1666,7 +1685,7 @@ __device__ __forceinline__ void chan_ring_body(const int8_t* __restrict__ x, int
       if constexpr (PREC == 0) {
         st_f2<WT>(&reinterpret_cast<float2*>(out)[idx], make_float2(y.x * hh, y.y * hh));
       } else if constexpr (PREC == 1) {
-        reinterpret_cast<uint32_t*>(out)[idx] = enc_f16(y.x * hh) | (enc_f16(y.y * hh) << 16);
+        reinterpret_cast<uint32_t*>(out)[idx] = enc_f16x2(y.x * hh, y.y * hh);
       } else if constexpr (PREC == 2) {
         reinterpret_cast<uint32_t*>(out)[idx] = enc_bf16(y.x * hh) | (enc_bf16(y.y * hh) << 16);
       } else {
@@ -1674,22 +1693,20 @@ __device__ __forceinline__ void chan_ring_body(const int8_t* __restrict__ x, int
       }
     };
 #pragma unroll
-    for (int cc = 0; cc < CPT; ++cc) {
-      const int k = tid + cc * C::NT;
+    for (int p = 0; p < C::NP; ++p) {
+      if constexpr (CPLX) {
+        if (a_base + p < n_ant)
 #pragma unroll
-      for (int p = 0; p < C::NP; ++p) {
-        if constexpr (CPLX) {
-          const int a = a_base + p;
-          if (a < n_ant) put(a, k, zk[cc][p], hs[p]);
-        } else {
-          float2 ya, yb;
-          separate(zk[cc][p], zn[cc][p], ya, yb);
+          for (int cc = 0; cc < CPT; ++cc) put(a_base + p, tid + cc * C::NT, zk[cc][p], hs[p]);
+      } else {
+        float2 y[2][CPT];
 #pragma unroll
-          for (int u = 0; u < 2; ++u) {
-            const int a = a_base + 2 * p + u;
-            if (a < n_ant) put(a, k, u ? yb : ya, hs[2 * p + u]);
-          }
-        }
+        for (int cc = 0; cc < CPT; ++cc) separate(zk[cc][p], zn[cc][p], y[0][cc], y[1][cc]);
+#pragma unroll
+        for (int u = 0; u < 2; ++u)
+          if (a_base + 2 * p + u < n_ant)
+#pragma unroll
+            for (int cc = 0; cc < CPT; ++cc) put(a_base + 2 * p + u, tid + cc * C::NT, y[u][cc], hs[2 * p + u]);
       }
     }
     // the next FIR overwrites b0: without PP every thread must be done
