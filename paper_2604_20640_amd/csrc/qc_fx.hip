@@ -769,6 +769,13 @@ fx_fused_ring_pp_kernel(const int8_t* __restrict__ x, int64_t ld_x, const int8_t
   }
 }
 
+// a * b + c into a register of its own
+__device__ __forceinline__ float fma3(float a, float b, float c) {
+  float d;
+  asm("v_fma_f32 %0, %1, %2, %3" : "=v"(d) : "v"(a), "v"(b), "v"(c));
+  return d;
+}
+
 // ---------------------------------------------------------------------------
 // Fused F+X of complex words (I, Q of 8 or 16 bits), four taps: the register
 // ring of the real tiles, one transform per antenna, all N channels.
@@ -779,17 +786,21 @@ fx_fused_ring_pp_kernel(const int8_t* __restrict__ x, int64_t ld_x, const int8_t
 // each of the two repeats the filter (a fifth of its work) and halves the rest.
 // The two of a run are eight blocks apart, on one compute die, whose L2 serves
 // the second one's samples.
-// TR: taps in registers.  Without it they are read (L1 and L2) for each
-// spectrum, all antennas at once: with 16-bit words at N = 4096 the ring takes
-// 128 and the sums 64 of the 256 registers a thread has.
+// With DEC = 2 the filter keeps, instead of the last blocks, the sums of the
+// next three spectra over the blocks so far (the halves of a block fold into the
+// same sums): a sample is converted once, not once per tap, nothing is
+// shifted, and 96 registers hold what took 128.  Its taps are read (L1 and
+// L2) for each spectrum, two samples' at a time, all antennas at once.  With
+// DEC = 1 the sums would take 32 to 64 registers more than the blocks.
 //
-// Bound: FP32 vector ALU (1646 instructions a spectrum and thread at N = 4096
-// with 16-bit words, 96 of them the ring's shift).  4 antennas x 2^26 samples,
-// N = 4096: 16-bit words 0.88 ms with the reduction, 1.38 ms through float32
-// spectra in HBM (2 GiB written and read); 4 x 2^24: 8-bit words 217 us (352),
-// N = 1024 190 us (469, 16 bits 507), N = 2048 165 us (376, 16 bits 397).
+// Bound: FP32 vector ALU (1312 instructions a spectrum and thread at N = 4096;
+// 1646 with the blocks kept, 256 of them conversions).  4 antennas x 2^26
+// samples, N = 4096: 16-bit words 0.81 ms with the reduction, 0.88 ms with the
+// blocks kept, 1.38 ms through float32 spectra in HBM (2 GiB written and read);
+// 4 x 2^24: 8-bit words 217 us (352), N = 1024 190 us (469, 16 bits 507),
+// N = 2048 165 us (376, 16 bits 397).
 // ---------------------------------------------------------------------------
-template <int N, int NA, int DEC, int ST, bool TR>
+template <int N, int NA, int DEC, int ST>
 struct CplxCfg {
   static constexpr int V = 16, P = 4;
   static constexpr int M = N / DEC;             // transform length
@@ -799,6 +810,7 @@ struct CplxCfg {
   static constexpr int CPT = M / NT;            // channels per thread
   static constexpr int BUF = lds_padded_size(NA * M);
   static constexpr bool SQ = M == 4096;         // radix-16 throughout: the shortened table
+  static constexpr bool SUMS = DEC == 2;        // filter state: sums, not blocks
   static constexpr int tw_entries() {
     if constexpr (SQ) return PpTw<M, V>::LDS_TW;
     else return M;
@@ -809,17 +821,18 @@ struct CplxCfg {
   static_assert(fft_pass_count(M, V) % 2 == 1, "odd pass count: the output lands in the second buffer");
 };
 
-template <int N, int NA, int DEC, int ST, bool TR>
-__global__ void __launch_bounds__((CplxCfg<N, NA, DEC, ST, TR>::NT))
+template <int N, int NA, int DEC, int ST>
+__global__ void __launch_bounds__((CplxCfg<N, NA, DEC, ST>::NT))
 fx_fused_cplx_kernel(const int8_t* __restrict__ x, int64_t ld_x, const int8_t* __restrict__ hist,
                      const float* __restrict__ taps, const float2* __restrict__ tw,
                      const float2* __restrict__ twp, int64_t spec_per_dump, int64_t cpd, int64_t runs,
                      float2* __restrict__ part) {
-  using C = CplxCfg<N, NA, DEC, ST, TR>;
+  using C = CplxCfg<N, NA, DEC, ST>;
   using W = RingWord<ST>;
   using T = typename W::T;
   static_assert(W::CPLX, "complex words");
   constexpr int P = C::P, GP = C::GP, M = C::M, NT = C::NT;
+  constexpr bool SUMS = C::SUMS;
   extern __shared__ float2 buf[];
   float2* b0 = buf;
   float2* b1 = buf + C::BUF;
@@ -852,19 +865,85 @@ fx_fused_cplx_kernel(const int8_t* __restrict__ x, int64_t ld_x, const int8_t* _
   auto load_next = [&](int a, int g, int nb) -> T {
     return *reinterpret_cast<const T*>(x + ((int64_t)a * ld_x + nb * N + cn0[g]) * W::BYTES);
   };
-  T ring[P][NA][GP];
-#pragma unroll
-  for (int q = 0; q < P; ++q)
-#pragma unroll
-    for (int a = 0; a < NA; ++a)
-#pragma unroll
-      for (int g = 0; g < GP; ++g) ring[q][a][g] = load_blk(a, g, m_lo - P + 1 + q);
-  float4 hr[TR ? GP : 1][P];
-  if constexpr (TR) {
+  float4 hr[SUMS ? 1 : GP][P];
+  if constexpr (!SUMS) {
 #pragma unroll
     for (int g = 0; g < GP; ++g)
 #pragma unroll
       for (int q = 0; q < P; ++q) hr[g][q] = *reinterpret_cast<const float4*>(taps + q * N + cn0[g]);
+  }
+  // filter state: the ring of the last blocks, or the sums of the next spectra
+  // over the blocks so far and the block that is due
+  constexpr int RP = SUMS ? 1 : P;
+  T ring[RP][NA][GP];
+  float2 ps[SUMS ? P - 1 : 1][NA][4];
+  const float fold = odd ? -1.f : 1.f;
+  // SUMS: sample i of the block in ring[0] joins the sums of antenna a; returns
+  // the finished one.  A sum moves on by one place with its first product: a
+  // three-address FMA, where the compiler's choice is a copy and a two-address
+  // one.
+  auto advance = [&](int a, int i, const float (&h)[GP][P]) -> float2 {
+    float2 xv[GP], y = make_float2(0.f, 0.f);
+#pragma unroll
+    for (int g = 0; g < GP; ++g)
+      xv[g] = make_float2(word_re<ST>(ring[0][a][g], i), word_im<ST>(ring[0][a][g], i));
+#pragma unroll
+    for (int kk = 0; kk < P; ++kk) {
+      float2 t;
+      if (kk < P - 1) {
+        const float2 o = ps[kk % (SUMS ? P - 1 : 1)][a][i];
+        t = make_float2(fma3(h[0][P - 1 - kk], xv[0].x, o.x), fma3(h[0][P - 1 - kk], xv[0].y, o.y));
+      } else {
+        t = make_float2(h[0][0] * xv[0].x, h[0][0] * xv[0].y);
+      }
+#pragma unroll
+      for (int g = 1; g < GP; ++g) {
+        t.x = fmaf(h[g][P - 1 - kk], xv[g].x, t.x);
+        t.y = fmaf(h[g][P - 1 - kk], xv[g].y, t.y);
+      }
+      if (kk == 0) y = t;
+      else ps[(kk + P - 2) % (SUMS ? P - 1 : 1)][a][i] = t;
+    }
+    return y;
+  };
+  // the taps of samples 2 ih and 2 ih + 1
+  auto taps2 = [&](int ih, int at0, int lt, float (&h)[2][GP][P]) {
+#pragma unroll
+    for (int g = 0; g < GP; ++g)
+#pragma unroll
+      for (int q = 0; q < P; ++q) {
+        const float2 v = *reinterpret_cast<const float2*>(taps + at0 + q * N + 4 * lt + g * 4 * NT + 2 * ih);
+        const float f = DEC == 2 && g == 1 ? fold : 1.f;
+        h[0][g][q] = f * v.x;
+        h[1][g][q] = f * v.y;
+      }
+  };
+  if constexpr (!SUMS) {
+#pragma unroll
+    for (int q = 0; q < P; ++q)
+#pragma unroll
+      for (int a = 0; a < NA; ++a)
+#pragma unroll
+        for (int g = 0; g < GP; ++g) ring[q % RP][a][g] = load_blk(a, g, m_lo - P + 1 + q);
+  } else {
+    float h[2][2][GP][P];
+    taps2(0, 0, tid, h[0]);
+    taps2(1, 0, tid, h[1]);
+#pragma unroll
+    for (int a = 0; a < NA; ++a) {
+#pragma unroll
+      for (int kk = 0; kk < P - 1; ++kk)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) ps[kk % (SUMS ? P - 1 : 1)][a][i] = make_float2(0.f, 0.f);
+      for (int q = 0; q < P - 1; ++q) {
+#pragma unroll
+        for (int g = 0; g < GP; ++g) ring[0][a][g] = load_blk(a, g, m_lo - P + 1 + q);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) advance(a, i, h[i >> 1][i & 1]);
+      }
+#pragma unroll
+      for (int g = 0; g < GP; ++g) ring[0][a][g] = load_blk(a, g, m_lo);
+    }
   }
   float2 acc[C::CPT][C::NB];
 #pragma unroll
@@ -873,58 +952,62 @@ fx_fused_cplx_kernel(const int8_t* __restrict__ x, int64_t ld_x, const int8_t* _
     for (int b = 0; b < C::NB; ++b) acc[cc][b] = make_float2(0.f, 0.f);
   __syncthreads();  // tables in LDS
 
-  settle_words<P * NA * GP * (int)(sizeof(T) / 4)>(reinterpret_cast<uint32_t*>(&ring[0][0][0]));
+  settle_words<RP * NA * GP * (int)(sizeof(T) / 4)>(reinterpret_cast<uint32_t*>(&ring[0][0][0]));
   for (int64_t m = m_lo; m < m_hi; ++m) {
     int lt = tid;
     // hidden per spectrum, so that no address is kept over the loop
-    if constexpr (!TR) asm volatile("" : "+v"(lt));
+    if constexpr (SUMS) asm volatile("" : "+v"(lt));
     // polyphase FIR; with DEC = 2 the two halves of the block fold together
     int at0 = 0;  // hidden: these loads stay inside the loop
     if constexpr (DEC == 2) asm volatile("" : "+s"(at0));
-    constexpr int YG = DEC == 2 ? 1 : GP;
-    float2 y[YG][NA][4];
+    if constexpr (SUMS) {
 #pragma unroll
-    for (int g = 0; g < YG; ++g)
+      for (int ih = 0; ih < 2; ++ih) {
+        float h[2][GP][P];
+        taps2(ih, at0, lt, h);
+        float4 wn = make_float4(1.f, 0.f, 1.f, 0.f);
+        if (odd) wn = *reinterpret_cast<const float4*>(tw + at0 + 4 * lt + 2 * ih);
 #pragma unroll
-      for (int a = 0; a < NA; ++a)
-#pragma unroll
-        for (int i = 0; i < 4; ++i) y[g][a][i] = make_float2(0.f, 0.f);
-    const float fold = odd ? -1.f : 1.f;
-#pragma unroll
-    for (int g = 0; g < GP; ++g)
-#pragma unroll
-      for (int q = 0; q < P; ++q) {
-        float4 h;
-        if constexpr (TR) h = hr[g][q];
-        else h = *reinterpret_cast<const float4*>(taps + at0 + q * N + 4 * lt + g * 4 * NT);
-        if (DEC == 2 && g == 1) h = make_float4(fold * h.x, fold * h.y, fold * h.z, fold * h.w);
-        const float hv[4] = {h.x, h.y, h.z, h.w};
-#pragma unroll
-        for (int a = 0; a < NA; ++a)
-#pragma unroll
-          for (int i = 0; i < 4; ++i) {
-            y[g % YG][a][i].x += hv[i] * word_re<ST>(ring[q][a][g], i);
-            y[g % YG][a][i].y += hv[i] * word_im<ST>(ring[q][a][g], i);
+        for (int a = 0; a < NA; ++a) {
+          float2 y0 = advance(a, 2 * ih, h[0]), y1 = advance(a, 2 * ih + 1, h[1]);
+          if (odd) {
+            y0 = cmul(y0, make_float2(wn.x, wn.y));
+            y1 = cmul(y1, make_float2(wn.z, wn.w));
           }
+          float2* const o = b0 + lds_pad(4 * lt) + lds_pad(a * M) + 2 * ih;
+          o[0] = y0;
+          o[1] = y1;
+        }
       }
-    if constexpr (DEC == 2) {
-      if (odd) {
-        const float4* wp = reinterpret_cast<const float4*>(tw + at0 + 4 * lt);
-        const float4 w0 = wp[0], w1 = wp[1];
-        const float2 wn[4] = {make_float2(w0.x, w0.y), make_float2(w0.z, w0.w), make_float2(w1.x, w1.y),
-                              make_float2(w1.z, w1.w)};
+    } else {
+      float2 y[GP][NA][4];
+#pragma unroll
+      for (int g = 0; g < GP; ++g)
 #pragma unroll
         for (int a = 0; a < NA; ++a)
 #pragma unroll
-          for (int i = 0; i < 4; ++i) y[0][a][i] = cmul(y[0][a][i], wn[i]);
-      }
+          for (int i = 0; i < 4; ++i) y[g][a][i] = make_float2(0.f, 0.f);
+#pragma unroll
+      for (int g = 0; g < GP; ++g)
+#pragma unroll
+        for (int q = 0; q < P; ++q) {
+          const float4 h = hr[g][q];
+          const float hv[4] = {h.x, h.y, h.z, h.w};
+#pragma unroll
+          for (int a = 0; a < NA; ++a)
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+              y[g][a][i].x += hv[i] * word_re<ST>(ring[q % RP][a][g], i);
+              y[g][a][i].y += hv[i] * word_im<ST>(ring[q % RP][a][g], i);
+            }
+        }
+#pragma unroll
+      for (int g = 0; g < GP; ++g)
+#pragma unroll
+        for (int a = 0; a < NA; ++a)
+#pragma unroll
+          for (int i = 0; i < 4; ++i) b0[lds_pad(4 * lt) + lds_pad(a * M + g * 4 * NT) + i] = y[g][a][i];
     }
-#pragma unroll
-    for (int g = 0; g < YG; ++g)
-#pragma unroll
-      for (int a = 0; a < NA; ++a)
-#pragma unroll
-        for (int i = 0; i < 4; ++i) b0[lds_pad(4 * lt) + lds_pad(a * M + g * 4 * NT) + i] = y[g][a][i];
     // the next block's words, in flight over the transforms
     const int nb = (int)(m + 1 < m_hi ? m + 1 : m);
 #pragma unroll
@@ -932,8 +1015,8 @@ fx_fused_cplx_kernel(const int8_t* __restrict__ x, int64_t ld_x, const int8_t* _
 #pragma unroll
       for (int g = 0; g < GP; ++g) {
 #pragma unroll
-        for (int q = 0; q + 1 < P; ++q) ring[q][a][g] = ring[q + 1][a][g];
-        ring[P - 1][a][g] = load_next(a, g, nb);
+        for (int q = 0; q + 1 < RP; ++q) ring[q][a][g] = ring[q + 1][a][g];
+        ring[RP - 1][a][g] = load_next(a, g, nb);
       }
     __syncthreads();
     if constexpr (C::SQ) fft_pp_passes<M, 1, NT, C::V, 0>(b0, b1, twl, lt);
@@ -969,11 +1052,11 @@ fx_fused_cplx_kernel(const int8_t* __restrict__ x, int64_t ld_x, const int8_t* _
     for (int b = 0; b < C::NB; ++b) out[(int64_t)b * N + DEC * (tid + cc * NT)] = acc[cc][b];
 }
 
-template <int N, int NA, int DEC, int ST, bool TR>
+template <int N, int NA, int DEC, int ST>
 static hipError_t launch_fused_cplx(const FxArgs& a, int64_t n_dump, int64_t spd, int64_t cpd, float2* part,
                                     hipStream_t s, const float2* twp) {
-  using C = CplxCfg<N, NA, DEC, ST, TR>;
-  auto kern = fx_fused_cplx_kernel<N, NA, DEC, ST, TR>;
+  using C = CplxCfg<N, NA, DEC, ST>;
+  auto kern = fx_fused_cplx_kernel<N, NA, DEC, ST>;
   hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
                                      hipFuncAttributeMaxDynamicSharedMemorySize, (int)C::LDS_BYTES);
   if (e != hipSuccess) return e;
@@ -1187,11 +1270,11 @@ int64_t fused_words_chunks(int sample, int n_fft, int n_ant, int64_t n_dump, int
 template <int ST>
 static hipError_t launch_fused_cplx_st(const FxArgs& a, int64_t n_dump, int64_t spd, int64_t cpd, float2* part,
                                        hipStream_t s, const float2* twp) {
-  if (a.n_ant == 2) return launch_fused_cplx<4096, 2, 1, ST, true>(a, n_dump, spd, cpd, part, s, twp);
+  if (a.n_ant == 2) return launch_fused_cplx<4096, 2, 1, ST>(a, n_dump, spd, cpd, part, s, twp);
   switch (a.n_fft) {
-    case 1024: return launch_fused_cplx<1024, 4, 1, ST, true>(a, n_dump, spd, cpd, part, s, twp);
-    case 2048: return launch_fused_cplx<2048, 4, 1, ST, true>(a, n_dump, spd, cpd, part, s, twp);
-    default: return launch_fused_cplx<4096, 4, 2, ST, ST == 2>(a, n_dump, spd, cpd, part, s, twp);
+    case 1024: return launch_fused_cplx<1024, 4, 1, ST>(a, n_dump, spd, cpd, part, s, twp);
+    case 2048: return launch_fused_cplx<2048, 4, 1, ST>(a, n_dump, spd, cpd, part, s, twp);
+    default: return launch_fused_cplx<4096, 4, 2, ST>(a, n_dump, spd, cpd, part, s, twp);
   }
 }
 
