@@ -274,6 +274,8 @@ __global__ void __launch_bounds__(CLEAN_MAX_WG) image_clean_claim_kernel(int* __
   }
   __syncthreads();
   if (slot_s < 0) return;
+  __syncthreads();
+  if (slot_s < 0) return;  // no area of its own
   CleanSlot& c = g_clean_slots[slot_s];
   for (int q = 0; q < 2; ++q)
     __hip_atomic_store(&c.key[q][threadIdx.x], 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -281,6 +283,12 @@ __global__ void __launch_bounds__(CLEAN_MAX_WG) image_clean_claim_kernel(int* __
     __hip_atomic_store(&c.done, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     __hip_atomic_store(&c.abort, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   }
+}
+
+// The count of a launch that ran on one workgroup for want of an area.
+__global__ void image_clean_count_kernel(int* __restrict__ n_comp) {
+  const int c = *n_comp;
+  if (c <= -2) *n_comp = -2 - c;
 }
 
 // Candidate: |v| (31 bits), 2^26 - 1 - pixel (26), sign (1), tag (6): the
@@ -440,7 +448,9 @@ image_clean_kernel(float* __restrict__ r, const float* __restrict__ psf, int log
   }
   if (t == 0) {
     if (G == 1) {
-      *n_comp = it;
+      // beside workgroups that may still have to read "no area" here: a count
+      // that stays negative for them, set right by the kernel after this one
+      *n_comp = gridDim.x > 1 ? -2 - it : it;
     } else {
       // the last workgroup to get here has seen every other past its last wait
       const int left = __hip_atomic_fetch_add(&ex->done, 1, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_AGENT);
@@ -558,6 +568,7 @@ extern "C" qc_status qc_image_clean(float* residual, const float* psf, int32_t n
     if (wgs > 1) hipLaunchKernelGGL(qc::image_clean_claim_kernel, dim3(1), dim3(qc::CLEAN_MAX_WG), 0, s, count);
     hipLaunchKernelGGL(kernel, dim3(wgs), dim3(qc::CLEAN_NT), 0, s, residual, psf, log2n, gain, threshold,
                        (int)max_iter, pix, comp_flux, count);
+    if (wgs > 1) hipLaunchKernelGGL(qc::image_clean_count_kernel, dim3(1), dim3(1), 0, s, count);
   };
   if (log2n <= 6) launch(qc::image_clean_kernel<4>, 1);
   else if (log2n == 7) launch(qc::image_clean_kernel<4>, 4);
