@@ -145,9 +145,11 @@ qc_status qc_pfb_channelize_ex(const void* x, int32_t sample, int64_t ld_x, int3
 
 /* F+X of any input word (Sec. 4.1 eq. 1; Sec. 4.2; Sec. 3.3).  As
  * qc_xcorrelate with the word conventions of qc_pfb_channelize_ex; vis is
- * [n_dump][n_base][n_chan].  QC_SAMPLE_I8 calls qc_xcorrelate; other words
- * run the F-engine of the full dumps' spectra into a stream-ordered pool
- * buffer, then qc_xcorrelate_chan.  Reduced x_prec needs n_ant <= 32 and
+ * [n_dump][n_base][n_chan].  QC_SAMPLE_I8 calls qc_xcorrelate.  Float32 F+X of
+ * four-tap filters is fused for real int16 with the built-in taps and for
+ * complex words with any taps (4 antennas at N = 1024, 2048 and 4096, 2 at
+ * 4096); other calls run the F-engine of the full dumps' spectra into a
+ * stream-ordered pool buffer, then qc_xcorrelate_chan.  Reduced x_prec needs n_ant <= 32 and
  * n_chan % 32 == 0 (else QC_EUNSUPPORTED). */
 qc_status qc_xcorrelate_ex(const void* x, int32_t sample, int64_t ld_x, int32_t n_ant, int64_t n_samp,
                            const qc_pfb_params* p, const void* hist, void* hist_out, int64_t spec_per_dump,
@@ -229,7 +231,9 @@ qc_status qc_ingest_run(const char* const* paths, const qc_ingest_config* cfg, f
  *   [max_iter]), and subtracts g * psf[((p - peak + (n/2, n/2)) mod n] from
  *   every pixel p (the dirty image of gridded data is periodic over the
  *   field), product and difference each rounded to float32.  n_comp:
- *   device int32[1] receives the number of components.  One workgroup;
+ *   device int32[1] receives the number of components, or -1 if a workgroup
+ *   waited out its bound for the others (the outputs are then unusable).  Up
+ *   to 64 workgroups, which have to be resident together.
  *   2 <= n <= 8192, 0 < gain <= 1. */
 qc_status qc_image_grid(const float* u, const float* v, const float* vis, const float* weight, int64_t n_vis,
                         int32_t n, double cell_rad, float* grid, double* wsum, void* stream);
