@@ -231,16 +231,23 @@ qc_status qc_ingest_run(const char* const* paths, const qc_ingest_config* cfg, f
  *   [max_iter]), and subtracts g * psf[((p - peak + (n/2, n/2)) mod n] from
  *   every pixel p (the dirty image of gridded data is periodic over the
  *   field), product and difference each rounded to float32.  n_comp:
- *   device int32[1] receives the number of components, or -1 if a workgroup
- *   waited out its bound for the others (the outputs are then unusable).  Up
- *   to 64 workgroups, which have to be resident together.
- *   2 <= n <= 8192, 0 < gain <= 1. */
+ *   device int32[1] receives the number of components.  Up to 64 workgroups
+ *   share the image where they get to run together, else one does it all; the
+ *   results are the same bits.  (-1: a workgroup that had started was held up
+ *   for 10 s; the outputs are then unusable.)
+ *   2 <= n <= 8192, 0 < gain <= 1.
+ * qc_image_clean_limits: for tests, process-wide: exchange areas that CLEAN
+ *   launches in flight may use (0..16, one each; 0: always one workgroup) and
+ *   how long a launch's workgroups wait for one another to start, in
+ *   microseconds (at most 10^6; 0: not at all).  Negative: the default, 16 and
+ *   20000. */
 qc_status qc_image_grid(const float* u, const float* v, const float* vis, const float* weight, int64_t n_vis,
                         int32_t n, double cell_rad, float* grid, double* wsum, void* stream);
 qc_status qc_image_invert(const float* grid, const double* wsum, int32_t n, float* work, float* image,
                           void* stream);
 qc_status qc_image_clean(float* residual, const float* psf, int32_t n, float gain, float threshold,
                          int32_t max_iter, int32_t* comp_pix, float* comp_flux, int32_t* n_comp, void* stream);
+qc_status qc_image_clean_limits(int32_t areas, int64_t gather_us);
 
 /* Prototype filters (Fig. pfb_fft compares an 8-tap Kaiser PFB, beta = 8,
  * with a plain rectangular-window FFT).  Writes P*N float taps, designed in

@@ -81,6 +81,7 @@ _SIGS = {
                       ctypes.POINTER(IngestStats)],
     "qc_image_invert": [_P, _P, _I32, _P, _P, _P],
     "qc_image_clean": [_P, _P, _I32, ctypes.c_float, ctypes.c_float, _I32, _P, _P, _P, _P],
+    "qc_image_clean_limits": [_I32, _I64],
     "qc_mad_flag": [_P, _I64, _I64, _I32, ctypes.c_float, _I32, _P, _P, _P],
     "qc_apply_delay_phase": [_P, _I64, _I32, _I32, ctypes.c_double, ctypes.c_double,
                              ctypes.POINTER(ctypes.c_double), ctypes.POINTER(ctypes.c_double), _P],
@@ -702,7 +703,7 @@ def image_clean(residual, psf, gain, threshold, max_iter):
                                 _ptr(pix), _ptr(flux), _ptr(nc), _stream()), "qc_image_clean")
     k = int(nc.item())
     if k < 0:
-        raise QCError(-3, "qc_image_clean", "the launch's workgroups could not run together")
+        raise QCError(-3, "qc_image_clean", "a workgroup was held up for 10 s")
     return pix[:k], flux[:k]
 
 

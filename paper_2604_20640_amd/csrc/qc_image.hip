@@ -26,6 +26,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <atomic>
+
 #include "qc.h"
 #include "qc_fft.h"
 #include "qc_internal.h"
@@ -246,49 +248,93 @@ hipError_t rows_fft(float2* x, int n, const float2* tw, hipStream_t s) {
 // CU took 0.65 ms per component there, bound by that CU's load path; 64
 // workgroups take 4.6 us, about half of it the exchange.
 //
-// All G workgroups have to be resident together.  G <= 64 of 1024 threads
-// leaves room for one such launch on each of the four hardware queues of a
-// process on 256 CUs; a wait is bounded in time all the same, and a launch
-// whose wait expires reports n_comp = -1 instead of a result.
+// All G workgroups have to be resident together, which other launches on the
+// GPU can prevent.  So they check in before anything is changed: the first
+// workgroup lets the others go on once it has seen all of them; if one is
+// missing after CLEAN_GATHER_US the first does the whole image alone and the
+// others leave.  Once all are resident none can keep another away; a wait is
+// bounded in time all the same, and a launch whose wait expires reports
+// n_comp = -1.
 constexpr int CLEAN_NT = 1024;
 constexpr int CLEAN_MAX_WG = 64;
 constexpr int CLEAN_SLOTS = 16;  // launches in flight with an exchange area of their own
-constexpr uint64_t CLEAN_WAIT_TICKS = 200000000ull;  // 2 s of the 100 MHz wall clock
+constexpr uint64_t CLEAN_TICKS_US = 100;                           // of the 100 MHz wall clock
+constexpr uint64_t CLEAN_WAIT_TICKS = 10000000 * CLEAN_TICKS_US;  // 10 s
+constexpr int64_t CLEAN_GATHER_US = 20000;
 
-struct CleanSlot {
-  uint64_t key[2][CLEAN_MAX_WG];
-  int busy, done, abort;
+enum { CLEAN_GATHER = 0, CLEAN_TOGETHER = 1, CLEAN_ALONE = 2 };
+// Sixteen workgroups' keys share a cache line, and the lines lie on different
+// memory channels (256 bytes apart): 64 workgroups 4.5 us a component at
+// 1024 x 1024, 4.7 with the keys in a row; 16 at 256 x 256 2.4 us, 2.7 where
+// they straddle two lines.
+constexpr int CLEAN_KEYS = 32 * (CLEAN_MAX_WG / 16);
+__device__ __forceinline__ int clean_at(int wg) { return 32 * (wg >> 4) + (wg & 15); }
+
+struct alignas(256) CleanSlot {
+  uint64_t key[2][CLEAN_KEYS];
+  int busy, verdict, abort, count, done;
 };
 __device__ CleanSlot g_clean_slots[CLEAN_SLOTS];
 
-// Claims an exchange area for the launch that follows on the stream and hands
-// its index on in n_comp (-1: all taken; the launch then runs on one workgroup).
-__global__ void __launch_bounds__(CLEAN_MAX_WG) image_clean_claim_kernel(int* __restrict__ n_comp) {
+template <class T>
+__device__ __forceinline__ T agent_load(const T* p) {
+  return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+template <class T>
+__device__ __forceinline__ void agent_store(T* p, T v) {
+  __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+// Claims one of the first `areas` exchange areas for the launch that follows on
+// the stream and hands it on in n_comp as -2 - index (-1: all taken; the launch
+// then runs on one workgroup).  Workgroups that start after the others are done
+// find the count there, which is no area either.
+__global__ void __launch_bounds__(CLEAN_MAX_WG) image_clean_claim_kernel(int* __restrict__ n_comp, int areas) {
   __shared__ int slot_s;
   if (threadIdx.x == 0) {
     int slot = -1;
-    for (int i = 0; i < CLEAN_SLOTS && slot < 0; ++i)
+    for (int i = 0; i < areas && slot < 0; ++i)
       if (atomicCAS(&g_clean_slots[i].busy, 0, 1) == 0) slot = i;
     slot_s = slot;
-    *n_comp = slot;
+    *n_comp = slot < 0 ? -1 : -2 - slot;
   }
-  __syncthreads();
-  if (slot_s < 0) return;
   __syncthreads();
   if (slot_s < 0) return;  // no area of its own
   CleanSlot& c = g_clean_slots[slot_s];
-  for (int q = 0; q < 2; ++q)
-    __hip_atomic_store(&c.key[q][threadIdx.x], 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  for (int q = 0; q < 2; ++q) agent_store(&c.key[q][clean_at(threadIdx.x)], (uint64_t)0);
   if (threadIdx.x == 0) {
-    __hip_atomic_store(&c.done, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    __hip_atomic_store(&c.abort, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    agent_store(&c.verdict, (int)CLEAN_GATHER);
+    agent_store(&c.abort, 0);
+    agent_store(&c.done, 0);
   }
 }
 
-// The count of a launch that ran on one workgroup for want of an area.
-__global__ void image_clean_count_kernel(int* __restrict__ n_comp) {
-  const int c = *n_comp;
-  if (c <= -2) *n_comp = -2 - c;
+// Check-in of workgroup wg of G, by its first wave: true if all run together.
+// The arrivals carry a tag of their own (63) in the second set of keys; one
+// word decides for all, whoever is the first to.
+__device__ __forceinline__ bool clean_gather(CleanSlot* ex, int G, int wg, uint64_t gather_ticks) {
+  const int lane = threadIdx.x & 63;
+  if (lane == 0) agent_store(&ex->key[1][clean_at(wg)], (uint64_t)63);
+  const uint64_t began = wall_clock64();
+  int verdict = CLEAN_GATHER;
+  while (verdict == CLEAN_GATHER) {
+    const bool all = wg == 0 && __all(lane >= G || agent_load(&ex->key[1][clean_at(lane < G ? lane : 0)]) == 63);
+    const bool late = wall_clock64() - began >= gather_ticks;
+    if (all || late) {
+      if (lane == 0) atomicCAS(&ex->verdict, (int)CLEAN_GATHER, (int)(all ? CLEAN_TOGETHER : CLEAN_ALONE));
+    }
+    verdict = __builtin_amdgcn_readfirstlane(agent_load(&ex->verdict));
+  }
+  return verdict == CLEAN_TOGETHER;
+}
+
+// Leaves the area: the last of G workgroups to do so, which has seen every
+// other past its last read of the area, hands out the count and gives it back.
+__device__ __forceinline__ void clean_leave(CleanSlot* ex, int G, int* n_comp) {
+  const int left = __hip_atomic_fetch_add(&ex->done, 1, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_AGENT);
+  if (left != G - 1) return;
+  *n_comp = agent_load(&ex->abort) ? -1 : agent_load(&ex->count);
+  __hip_atomic_store(&ex->busy, 0, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT);
 }
 
 // Candidate: |v| (31 bits), 2^26 - 1 - pixel (26), sign (1), tag (6): the
@@ -313,23 +359,33 @@ __device__ __forceinline__ uint64_t key_max(uint64_t a, uint64_t b) { return a >
 template <int PX>
 __global__ void __launch_bounds__(CLEAN_NT)
 image_clean_kernel(float* __restrict__ r, const float* __restrict__ psf, int log2n, float gain, float thr,
-                   int max_iter, int* __restrict__ comp_pix, float* __restrict__ comp_flux,
-                   int* __restrict__ n_comp) {
+                   int max_iter, uint64_t gather_ticks, int* __restrict__ comp_pix,
+                   float* __restrict__ comp_flux, int* __restrict__ n_comp) {
   __shared__ uint64_t wkey[CLEAN_NT / 64];
   __shared__ uint64_t all_s;
-  __shared__ int slot_s, stop_s;
+  __shared__ int slot_s, stop_s, together_s;
   const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
   const int n = 1 << log2n, mask = n - 1, h = n / 2;
   const int npix = 1 << (2 * log2n);
   int G = gridDim.x, wg = blockIdx.x;
-  if (t == 0) slot_s = G > 1 ? *n_comp : -1;
+  if (wave == 0) {
+    const int handed = G > 1 ? __builtin_amdgcn_readfirstlane(*n_comp) : -1;
+    const bool together = handed <= -2 && clean_gather(g_clean_slots + (-2 - handed), G, wg, gather_ticks);
+    if (t == 0) {
+      slot_s = handed <= -2 ? -2 - handed : -1;
+      together_s = together;
+    }
+  }
   __syncthreads();
   const int slot = __builtin_amdgcn_readfirstlane(slot_s);
-  if (G > 1 && slot < 0) {  // no exchange area: the first workgroup does it all
-    if (wg > 0) return;
+  CleanSlot* const ex = g_clean_slots + (slot < 0 ? 0 : slot);
+  if (G > 1 && !__builtin_amdgcn_readfirstlane(together_s)) {  // the first workgroup does it all
+    if (wg > 0) {
+      if (t == 0 && slot >= 0) clean_leave(ex, G, n_comp);
+      return;
+    }
     G = 1;
   }
-  CleanSlot* const ex = g_clean_slots + (slot < 0 ? 0 : slot);
   const int first = wg * CLEAN_NT + t, stride = G * CLEAN_NT;
   const bool regs = PX > 0 && G == (int)gridDim.x;
   float own[PX > 0 ? PX : 1];
@@ -396,22 +452,21 @@ image_clean_kernel(float* __restrict__ r, const float* __restrict__ psf, int log
       if (G > 1) {
         const uint64_t tag = (uint64_t)(it % 62 + 1);
         uint64_t* const at = ex->key[it & 1];
-        if (lane == 0) __hip_atomic_store(&at[wg], key | tag, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        if (lane == 0) agent_store(&at[clean_at(wg)], key | tag);
         uint64_t began = 0;
         for (unsigned spin = 0;; ++spin) {
-          key = lane < G ? __hip_atomic_load(&at[lane], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : tag;
+          key = lane < G ? agent_load(&at[clean_at(lane)]) : tag;
           if (__all((key & 63u) == tag)) break;
           if ((spin & 255u) == 255u) {
             const uint64_t now = wall_clock64();
             if (began == 0) began = now;
-            if (now - began > CLEAN_WAIT_TICKS ||
-                __hip_atomic_load(&ex->abort, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0) {
+            if (now - began > CLEAN_WAIT_TICKS || agent_load(&ex->abort) != 0) {
               stop = 1;
               break;
             }
           }
         }
-        if (stop && lane == 0) __hip_atomic_store(&ex->abort, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        if (stop && lane == 0) agent_store(&ex->abort, 1);
         key &= ~63ull;
         for (int d = 32; d >= 1; d >>= 1) key = key_max(key, __shfl_xor((unsigned long long)key, d));
       }
@@ -447,22 +502,20 @@ image_clean_kernel(float* __restrict__ r, const float* __restrict__ psf, int log
     }
   }
   if (t == 0) {
-    if (G == 1) {
-      // beside workgroups that may still have to read "no area" here: a count
-      // that stays negative for them, set right by the kernel after this one
-      *n_comp = gridDim.x > 1 ? -2 - it : it;
+    if (slot >= 0) {
+      if (wg == 0) agent_store(&ex->count, it);
+      clean_leave(ex, (int)gridDim.x, n_comp);
     } else {
-      // the last workgroup to get here has seen every other past its last wait
-      const int left = __hip_atomic_fetch_add(&ex->done, 1, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_AGENT);
-      if (left == G - 1) {
-        *n_comp = __hip_atomic_load(&ex->abort, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) ? -1 : it;
-        __hip_atomic_store(&ex->busy, 0, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT);
-      }
+      *n_comp = it;
     }
   }
 }
 
 #pragma clang fp contract(on)
+
+// What qc_image_clean_limits sets; read at each launch.
+std::atomic<int> g_clean_areas{CLEAN_SLOTS};
+std::atomic<int64_t> g_clean_gather_us{CLEAN_GATHER_US};
 
 }  // namespace
 
@@ -544,6 +597,15 @@ extern "C" qc_status qc_image_invert(const float* grid, const double* wsum, int3
   return QC_OK;
 }
 
+extern "C" qc_status qc_image_clean_limits(int32_t areas, int64_t gather_us) {
+  qc::api_clear_error();
+  if (areas > qc::CLEAN_SLOTS) return qc::api_fail(QC_EINVAL, "at most %d exchange areas", qc::CLEAN_SLOTS);
+  if (gather_us > 1000000) return qc::api_fail(QC_EINVAL, "gather_us must be at most 10^6");
+  qc::g_clean_areas = areas < 0 ? qc::CLEAN_SLOTS : areas;
+  qc::g_clean_gather_us = gather_us < 0 ? qc::CLEAN_GATHER_US : gather_us;
+  return QC_OK;
+}
+
 extern "C" qc_status qc_image_clean(float* residual, const float* psf, int32_t n, float gain, float threshold,
                                     int32_t max_iter, int32_t* comp_pix, float* comp_flux, int32_t* n_comp,
                                     void* stream) {
@@ -565,10 +627,12 @@ extern "C" qc_status qc_image_clean(float* residual, const float* psf, int32_t n
   int* const pix = reinterpret_cast<int*>(comp_pix);
   int* const count = reinterpret_cast<int*>(n_comp);
   auto launch = [&](auto kernel, int wgs) {
-    if (wgs > 1) hipLaunchKernelGGL(qc::image_clean_claim_kernel, dim3(1), dim3(qc::CLEAN_MAX_WG), 0, s, count);
+    if (wgs > 1)
+      hipLaunchKernelGGL(qc::image_clean_claim_kernel, dim3(1), dim3(qc::CLEAN_MAX_WG), 0, s, count,
+                         qc::g_clean_areas.load(std::memory_order_relaxed));
     hipLaunchKernelGGL(kernel, dim3(wgs), dim3(qc::CLEAN_NT), 0, s, residual, psf, log2n, gain, threshold,
-                       (int)max_iter, pix, comp_flux, count);
-    if (wgs > 1) hipLaunchKernelGGL(qc::image_clean_count_kernel, dim3(1), dim3(1), 0, s, count);
+                       (int)max_iter, (uint64_t)qc::g_clean_gather_us.load(std::memory_order_relaxed) * qc::CLEAN_TICKS_US,
+                       pix, comp_flux, count);
   };
   if (log2n <= 6) launch(qc::image_clean_kernel<4>, 1);
   else if (log2n == 7) launch(qc::image_clean_kernel<4>, 4);
