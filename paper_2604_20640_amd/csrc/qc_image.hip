@@ -309,16 +309,26 @@ __global__ void __launch_bounds__(CLEAN_MAX_WG) image_clean_claim_kernel(int* __
   }
 }
 
+// Candidate: |v| (31 bits), 2^26 - pixel (27), sign (1), tag (5): the largest is
+// the largest |v|, of those the smallest pixel (n <= 8192).  A NaN is no
+// candidate; 0 stands for none, which no pixel's key is.
+constexpr uint64_t CLEAN_TAG = 31;
+constexpr uint64_t CLEAN_ARRIVED = 31;  // the check-in's tag; iterations go through 1 to 30
+__device__ __forceinline__ uint64_t clean_key(float v, int p) {
+  const uint32_t bits = __float_as_uint(v);
+  return ((uint64_t)(bits & 0x7fffffffu) << 33) | ((uint64_t)((1 << 26) - p) << 6) | ((uint64_t)(bits >> 31) << 5);
+}
+
 // Check-in of workgroup wg of G, by its first wave: true if all run together.
-// The arrivals carry a tag of their own (63) in the second set of keys; one
+// The arrivals carry a tag of their own in the second set of keys; one
 // word decides for all, whoever is the first to.
 __device__ __forceinline__ bool clean_gather(CleanSlot* ex, int G, int wg, uint64_t gather_ticks) {
   const int lane = threadIdx.x & 63;
-  if (lane == 0) agent_store(&ex->key[1][clean_at(wg)], (uint64_t)63);
+  if (lane == 0) agent_store(&ex->key[1][clean_at(wg)], CLEAN_ARRIVED);
   const uint64_t began = wall_clock64();
   int verdict = CLEAN_GATHER;
   while (verdict == CLEAN_GATHER) {
-    const bool all = wg == 0 && __all(lane >= G || agent_load(&ex->key[1][clean_at(lane < G ? lane : 0)]) == 63);
+    const bool all = wg == 0 && __all(lane >= G || agent_load(&ex->key[1][clean_at(lane < G ? lane : 0)]) == CLEAN_ARRIVED);
     const bool late = wall_clock64() - began >= gather_ticks;
     if (all || late) {
       if (lane == 0) atomicCAS(&ex->verdict, (int)CLEAN_GATHER, (int)(all ? CLEAN_TOGETHER : CLEAN_ALONE));
@@ -335,15 +345,6 @@ __device__ __forceinline__ void clean_leave(CleanSlot* ex, int G, int* n_comp) {
   if (left != G - 1) return;
   *n_comp = agent_load(&ex->abort) ? -1 : agent_load(&ex->count);
   __hip_atomic_store(&ex->busy, 0, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT);
-}
-
-// Candidate: |v| (31 bits), 2^26 - 1 - pixel (26), sign (1), tag (6): the
-// largest is the largest |v|, of those the smallest pixel (n <= 8192).  A NaN
-// is no candidate; 0 stands for none.
-__device__ __forceinline__ uint64_t clean_key(float v, int p) {
-  const uint32_t bits = __float_as_uint(v);
-  return ((uint64_t)(bits & 0x7fffffffu) << 33) | ((uint64_t)((1 << 26) - 1 - p) << 7) |
-         ((uint64_t)(bits >> 31) << 6);
 }
 
 __device__ __forceinline__ uint64_t key_max(uint64_t a, uint64_t b) { return a > b ? a : b; }
@@ -450,13 +451,13 @@ image_clean_kernel(float* __restrict__ r, const float* __restrict__ psf, int log
       for (int d = 8; d >= 1; d >>= 1) key = key_max(key, __shfl_xor((unsigned long long)key, d));
       int stop = 0;
       if (G > 1) {
-        const uint64_t tag = (uint64_t)(it % 62 + 1);
+        const uint64_t tag = (uint64_t)(it % 30 + 1);
         uint64_t* const at = ex->key[it & 1];
         if (lane == 0) agent_store(&at[clean_at(wg)], key | tag);
         uint64_t began = 0;
         for (unsigned spin = 0;; ++spin) {
           key = lane < G ? agent_load(&at[clean_at(lane)]) : tag;
-          if (__all((key & 63u) == tag)) break;
+          if (__all((key & CLEAN_TAG) == tag)) break;
           if ((spin & 255u) == 255u) {
             const uint64_t now = wall_clock64();
             if (began == 0) began = now;
@@ -467,7 +468,7 @@ image_clean_kernel(float* __restrict__ r, const float* __restrict__ psf, int log
           }
         }
         if (stop && lane == 0) agent_store(&ex->abort, 1);
-        key &= ~63ull;
+        key &= ~CLEAN_TAG;
         for (int d = 32; d >= 1; d >>= 1) key = key_max(key, __shfl_xor((unsigned long long)key, d));
       }
       if (lane == 0) {
@@ -483,8 +484,8 @@ image_clean_kernel(float* __restrict__ r, const float* __restrict__ psf, int log
                          (uint32_t)__builtin_amdgcn_readfirstlane((int)all_s);
     failed = __builtin_amdgcn_readfirstlane(stop_s) != 0;
     const bool none = top == 0ull;
-    const int pi = none ? 0x7fffffff : (1 << 26) - 1 - (int)((top >> 7) & ((1u << 26) - 1));
-    const float peak = none ? 0.f : __uint_as_float((uint32_t)(top >> 33) | ((uint32_t)((top >> 6) & 1u) << 31));
+    const int pi = none ? 0x7fffffff : (1 << 26) - (int)((top >> 6) & ((1u << 27) - 1));
+    const float peak = none ? 0.f : __uint_as_float((uint32_t)(top >> 33) | ((uint32_t)((top >> 5) & 1u) << 31));
     if (failed || it >= max_iter || !(fabsf(peak) >= thr)) break;
     g = gain * peak;
     pl = pi >> log2n;

@@ -83,6 +83,19 @@ def test_launches_in_flight(qc, limits, areas, gather_us):
         one.check()
 
 
+@pytest.mark.parametrize("n", [64, 512, 8192])
+def test_zero_at_the_last_pixel(qc, n):
+    """The last pixel is a peak like any other, also where it is zero and the
+    rest of the image is no number."""
+    import torch
+    D = np.full((n, n), np.nan, np.float32)
+    D[-1, -1] = 0.0
+    res, psf = torch.from_numpy(D).cuda(), torch.zeros((n, n), device="cuda")
+    pix, flux = qc.image_clean(res, psf, 0.5, 0.0, 2)
+    assert pix.cpu().numpy().tolist() == [n * n - 1] * 2
+    assert flux.cpu().numpy().tolist() == [0.0, 0.0]
+
+
 def test_limits_reject(qc):
     assert qc.lib().qc_image_clean_limits(17, 0) == -1
     assert qc.lib().qc_image_clean_limits(0, 1000001) == -1
