@@ -308,9 +308,8 @@ qc_status qc_xcorrelate_chan(const void* v, qc_prec prec, const float* scale, in
  * Amplitudes are |V| formed in float64 and rounded once to float32; medians,
  * the MAD and T = med + (sigma*1.4826)*MAD are float64, the even-count median
  * is the mean of the two middle values, and MAD = 0 gives T = median.
- * Populations of more than 2048 values take a work buffer from the
- * stream-ordered memory pool: 4 bytes per visibility, 2 above 36864 values
- * (4 for population 1). */
+ * Populations of more than 2048 values take a work buffer of 4 bytes per
+ * visibility from the stream-ordered memory pool. */
 qc_status qc_mad_flag(const float* vis, int64_t n_time, int64_t n_base, int32_t n_chan,
                       float sigma, int32_t population, uint8_t* mask, double* thresh_out,
                       void* stream);

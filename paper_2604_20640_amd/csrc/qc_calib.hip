@@ -583,9 +583,14 @@ __global__ void mad_amp4_kernel(const float4* __restrict__ vis, int64_t n_base, 
 //      kept amplitudes at the ranks the counts leave, the threshold, the
 //      remaining flags.
 // Ranks and counts are of the whole population, so the results are the exact
-// order statistics.  A population whose rank falls outside its window (large
-// groups of equal amplitudes, or a sample that misled) or whose lists overflow
-// stays MAD_OPEN, and mad_kernel then does it from the start.
+// order statistics.  A population that the sample cannot bound (half of it
+// zero), whose rank falls outside its window (a sample that misled) or whose
+// lists would overflow (large groups of equal amplitudes) is left open:
+//   4. mad_open_amp_kernel forms the amplitudes of the open ones over their
+//      lists, and mad_kernel selects among those from the start.
+// 528 planes of 524288, all open because half of each is zero: 10.7 ms, 10.6
+// without the sample (18.1 ms with the amplitudes formed anew by every pass of
+// mad_kernel); of amplitudes that repeat: 5.2 ms (15.7).
 //
 // Bound: HBM, 8 B a visibility read and 1 B written, and the scan's vector
 // instructions beside it.  528 planes of 524288 visibilities: 0.82 ms (sample
@@ -622,9 +627,8 @@ constexpr int MAD_CHUNK = 16384;     // elements per scan workgroup
 __host__ __device__ __forceinline__ int64_t mad_cap_med(int64_t n) { return n / 8; }
 __host__ __device__ __forceinline__ int64_t mad_cap_dev(int64_t n) { return n / 4; }
 __host__ __device__ __forceinline__ int64_t mad_cap_thr(int64_t n) { return n / 16; }
-__host__ __device__ __forceinline__ int64_t mad_list_floats(int64_t n) {
-  return (mad_cap_med(n) + mad_cap_dev(n) + 2 * mad_cap_thr(n) + 3) / 4 * 4;
-}
+// The lists of one population lie in the first half of its n floats, which its
+// amplitudes take if it is left open.
 
 // The four amplitudes at elements i..i+3 of a population (i % 4 == 0).  VEC:
 // rows are multiples of four elements and 16-byte aligned.
@@ -700,11 +704,13 @@ __device__ __forceinline__ bool sample_bounds(const float (&a)[MAD_SAMPLE_PER], 
 template <bool VEC>
 __global__ void __launch_bounds__(MAD_SAMPLE_NT)
 mad_sample_kernel(const float2* __restrict__ vis, int64_t n_time, int64_t n_base, int n_chan, float sigma,
-                  int population, MadWin* __restrict__ win) {
+                  int population, int flags, MadWin* __restrict__ win) {
   __shared__ unsigned hist[2048];
   __shared__ unsigned wsum[MAD_SAMPLE_NT / 64];
   __shared__ unsigned long long sh[4];
   __shared__ unsigned sub[64];
+  __shared__ unsigned held[3];
+  if (threadIdx.x < 3) held[threadIdx.x] = 0u;
   const Pop pop = make_pop(blockIdx.x, n_time, n_base, n_chan, population);
   const int64_t n4 = pop.count / 4;
   // strata of the population in order, four neighbouring elements of each,
@@ -723,7 +729,6 @@ mad_sample_kernel(const float2* __restrict__ vis, int64_t n_time, int64_t n_base
   const float lo = __uint_as_float(k0), hi = __uint_as_float(k1);
   // the sample's deviations are from the centre of the median's window
   if (ok) ok = sample_bounds(a, 0.5f * (lo + hi), hist, wsum, sh, sub, e0, e1);
-  if (threadIdx.x != 0) return;
   MadWin w;
   w.state = MAD_OPEN;
   w.n_le = w.n_in = w.n_med = w.n_dev = w.n_thr = 0u;
@@ -754,7 +759,31 @@ mad_sample_kernel(const float2* __restrict__ vis, int64_t n_time, int64_t n_base
     w.q_t1 = sq(t1);
     // the windows in order, and every square a normal float32
     if (c0 < lo && hi < c1 && lo > 1e-15f && r1 < 1e18f && t1 < 1e18f) w.state = MAD_SCAN;
+    // what the lists would hold of the sample: no scan for one that overflows
+    unsigned n_med = 0u, n_dev = 0u, n_thr = 0u;
+#pragma unroll
+    for (int j = 0; j < MAD_SAMPLE_PER; ++j) {
+      n_med += a[j] > lo && a[j] <= hi;
+      n_dev += (a[j] >= l0 && a[j] < c0) || (a[j] > c1 && a[j] <= r1);
+      n_thr += a[j] > t0 && a[j] <= t1;
+    }
+#pragma unroll
+    for (int d = 32; d >= 1; d >>= 1) {
+      n_med += __shfl_xor(n_med, d);
+      n_dev += __shfl_xor(n_dev, d);
+      n_thr += __shfl_xor(n_thr, d);
+    }
+    if ((threadIdx.x & 63) == 0) {
+      atomicAdd(&held[0], n_med);
+      atomicAdd(&held[1], n_dev);
+      atomicAdd(&held[2], n_thr);
+    }
   }
+  __syncthreads();
+  if (threadIdx.x != 0) return;
+  if (held[0] > mad_cap_med(MAD_SAMPLE) || held[1] > mad_cap_dev(MAD_SAMPLE) ||
+      (flags && held[2] > mad_cap_thr(MAD_SAMPLE)))
+    w.state = MAD_OPEN;
   win[blockIdx.x] = w;
 }
 
@@ -774,7 +803,7 @@ mad_scan_kernel(const float2* __restrict__ vis, int64_t n_time, int64_t n_base, 
   if (w->state != MAD_SCAN) return;
   const Pop pop = make_pop(id, n_time, n_base, n_chan, population);
   const int64_t n = pop.count;
-  float* const g_med = lists + id * mad_list_floats(n);
+  float* const g_med = lists + id * n;
   float* const g_dev = g_med + mad_cap_med(n);
   float* const g_thr = g_dev + mad_cap_dev(n);
   const float q_lo = w->q_lo, q_hi = w->q_hi, q_l0 = w->q_l0, q_c0 = w->q_c0, q_c1 = w->q_c1, q_r1 = w->q_r1;
@@ -916,7 +945,7 @@ mad_finish_kernel(int64_t n_time, int64_t n_base, int n_chan, float sigma, int p
   if (uni((uint32_t)w->state) != MAD_SCAN) return;
   const Pop pop = make_pop(blockIdx.x, n_time, n_base, n_chan, population);
   const int64_t n = pop.count;
-  const float* const g_med = lists + (int64_t)blockIdx.x * mad_list_floats(n);
+  const float* const g_med = lists + (int64_t)blockIdx.x * n;
   const float* const g_dev = g_med + mad_cap_med(n);
   const float* const g_thr = g_dev + mad_cap_dev(n);
   const int64_t n_med = uni(w->n_med), n_dev = uni(w->n_dev), n_thr = uni(w->n_thr);
@@ -971,6 +1000,35 @@ mad_finish_kernel(int64_t n_time, int64_t n_base, int n_chan, float sigma, int p
       stats[2 * (int64_t)blockIdx.x] = med;
       stats[2 * (int64_t)blockIdx.x + 1] = madv;
     }
+  }
+}
+
+// The amplitudes of the populations left open, parts blocks each.  Bound: HBM,
+// 12 B an element; a block whose population is done only reads its state.
+template <bool VEC>
+__global__ void __launch_bounds__(256)
+mad_open_amp_kernel(const float2* __restrict__ vis, int64_t n_time, int64_t n_base, int n_chan, int population,
+                    int parts, const MadWin* __restrict__ win, float* __restrict__ amp) {
+  const int64_t id = blockIdx.x / (unsigned)parts;
+  if (__builtin_amdgcn_readfirstlane(win[id].state) == MAD_DONE) return;
+  const Pop pop = make_pop(id, n_time, n_base, n_chan, population);
+  const int64_t n = pop.count, step = (int64_t)parts * 256;
+  float* const o = amp + id * n;
+  const int64_t first = (int64_t)(blockIdx.x % (unsigned)parts) * 256 + threadIdx.x;
+  if constexpr (VEC) {  // n is a multiple of four
+    constexpr int U = 4;
+    const int64_t n4 = n / 4;
+    for (int64_t j0 = first; j0 < n4; j0 += U * step) {
+      float a[U][4];
+#pragma unroll
+      for (int u = 0; u < U; ++u) amp4<true>(vis, pop, 4 * (j0 + u * step < n4 ? j0 + u * step : j0), a[u]);
+#pragma unroll
+      for (int u = 0; u < U; ++u)
+        if (j0 + u * step < n4)
+          reinterpret_cast<float4*>(o)[j0 + u * step] = make_float4(a[u][0], a[u][1], a[u][2], a[u][3]);
+    }
+  } else {
+    for (int64_t i = first; i < n; i += step) o[i] = amp_f32(vis[pop.off(i)]);
   }
 }
 
@@ -1183,7 +1241,7 @@ int64_t mad_scratch_floats(int64_t n_time, int64_t n_base, int n_chan, int popul
   const int64_t npop = population == 0 ? n_base : population == 1 ? n_base * n_chan : n_time * n_base;
   const int64_t count = population == 0 ? n_time * n_chan : population == 1 ? n_time : n_chan;
   if (mad_scans(npop, count, population))
-    return npop * ((int64_t)(sizeof(MadWin) / sizeof(float)) + mad_list_floats(count));
+    return (npop * count + 1) / 2 * 2 + npop * (int64_t)(sizeof(MadWin) / sizeof(float));
   return count > MAD_CAP_SMALL ? npop * count : 0;
 }
 
@@ -1199,14 +1257,16 @@ hipError_t launch_mad(const float2* vis, int64_t n_time, int64_t n_base, int n_c
                   population, MAD_CAP_SMALL, (int64_t)0, nullptr, nullptr, mask, thresh, stats);
   } else {
     MadWin* win = nullptr;
+    const float* gamp = nullptr;
     if (amp_scratch && mad_scans(npop, count, population)) {
-      win = reinterpret_cast<MadWin*>(amp_scratch);
-      float* const lists = reinterpret_cast<float*>(win + npop);
+      float* const lists = amp_scratch;
+      win = reinterpret_cast<MadWin*>(amp_scratch + (npop * count + 1) / 2 * 2);
       const bool vec = n_chan % 4 == 0 && (reinterpret_cast<uintptr_t>(vis) & 15u) == 0 &&
                        (reinterpret_cast<uintptr_t>(mask) & 3u) == 0;
       const int chunks = (int)((count + MAD_CHUNK - 1) / MAD_CHUNK);
       hipError_t e = launch(vec ? mad_sample_kernel<true> : mad_sample_kernel<false>, dim3((unsigned)npop),
-                            dim3(MAD_SAMPLE_NT), 0, s, vis, n_time, n_base, n_chan, sigma, population, win);
+                            dim3(MAD_SAMPLE_NT), 0, s, vis, n_time, n_base, n_chan, sigma, population, (int)(mask != nullptr),
+                            win);
       if (e == hipSuccess)
         e = launch(vec ? mad_scan_kernel<true> : mad_scan_kernel<false>, dim3((unsigned)(npop * chunks)),
                    dim3(256), 0, s, vis, n_time, n_base, n_chan, population, chunks, win, lists, mask);
@@ -1216,12 +1276,16 @@ hipError_t launch_mad(const float2* vis, int64_t n_time, int64_t n_base, int n_c
                          sigma, population, win, lists, mask, thresh, stats)
                 : launch(mad_finish_kernel<512>, dim3((unsigned)npop), dim3(512), 0, s, n_time, n_base, n_chan, sigma,
                          population, win, lists, mask, thresh, stats);
+      // about 2048 blocks, should all be open
+      const int parts = (int)std::max<int64_t>(1, std::min<int64_t>(chunks, 2048 / npop));
+      if (e == hipSuccess)
+        e = launch(vec ? mad_open_amp_kernel<true> : mad_open_amp_kernel<false>, dim3((unsigned)(npop * parts)),
+                   dim3(256), 0, s, vis, n_time, n_base, n_chan, population, parts, win, lists);
       if (e != hipSuccess) return e;
-      amp_scratch = nullptr;
+      gamp = lists;
     }
     const int64_t cap = count <= MAD_CAP_BIG ? count : 0;
-    const float* gamp = nullptr;
-    if (amp_scratch) {
+    if (amp_scratch && !win) {
       // the amplitudes are formed once, by the whole GPU: the selection
       // workgroups (one per population) then load 4 contiguous bytes per
       // element instead of forming a float64 square root each, and

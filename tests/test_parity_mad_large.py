@@ -103,3 +103,22 @@ def test_normalised_input_over_its_range(qc):
     fin = np.isfinite(ref)
     assert np.array_equal(fin, np.isfinite(x))
     assert np.all(np.abs(x[fin] - ref[fin]) <= 2.0 ** -23 * np.abs(ref[fin]))
+
+
+@pytest.mark.parametrize("off", [0, 1])
+def test_open_populations_beside_closed_ones(qc, off):
+    """More populations than compute units, some left open: zero, mostly zero,
+    a few values that repeat, a group of equal amplitudes at the median and one
+    at the threshold."""
+    import torch
+    n_base = torch.cuda.get_device_properties(0).multi_processor_count + 44
+    v = _noise((37, n_base, 1000 + 4 * off), 21)
+    v[:, 1::7] = 0
+    v[:30, 2::7] = 0
+    v[:, 3::7] = np.round(2 * v[:, 3::7].real) / 2
+    a = np.abs(v[:, 4::7])
+    v[:, 4::7][(a > 0.9) & (a < 1.4)] = np.complex64(1.2)
+    med = np.median(a, axis=(0, 2), keepdims=True)
+    top = med + 3 * 1.4826 * np.median(np.abs(a - med), axis=(0, 2), keepdims=True)
+    v[:, 5::7][:, :a.shape[1], :90] = top[:, :v[:, 5::7].shape[1]].astype(np.complex64)
+    _check(qc, v, 3.0, 0, off)
