@@ -860,18 +860,41 @@ __device__ __forceinline__ double log1p_pos(double r) {
 
 // Network input of one baseline plane: A = |V| (float64, rounded to
 // float32), r = (A - med)/(1.4826 MAD), x = sign(r) log1p|r|.  A block takes
-// NORM_PER elements of one row (baseline, integration).  Bound: HBM, 12 B an
-// element: 66 planes of 524288 in 122 us, 3.4 TB/s (403 us with the library's
-// log1p and division and a thread per element).
+// NORM_PER elements of one row (baseline, integration), or, with rows of up to
+// half as many (NARROW), as many rows as it has groups of 2^lg >= n_chan / 4
+// lanes.  Bound: HBM, 12 B an element: 66 planes of 524288 in 122 us, 3.4 TB/s
+// (403 us with the library's log1p and division and a thread per element); as
+// many in rows of 64 channels 102 us, of 4 187 us (1.3 and 21.1 ms with a block
+// per row).
 constexpr int NORM_PER = 1024;
+template <bool NARROW>
 __global__ void __launch_bounds__(256)
 cnn_normalize_kernel(const float2* __restrict__ vis, const double* __restrict__ stats, int64_t n_time,
-                     int64_t n_base, int n_chan, int64_t b0, int64_t rows, unsigned row_blocks,
+                     int64_t n_base, int n_chan, int64_t b0, int64_t rows, unsigned row_blocks, int lg,
                      float* __restrict__ x) {
-  const int f0 = (int)(blockIdx.x % row_blocks) * NORM_PER;
-  // row = bl * n_time + tt; more than one only beyond 2^30 blocks
-  for (int64_t row = blockIdx.x / row_blocks; row < rows; row += gridDim.x / row_blocks) {
-    const int64_t bl = row / n_time, tt = row - bl * n_time, b = b0 + bl;
+  const int lanes = NARROW ? 1 << lg : 256;
+  const int f0 = NARROW ? 0 : (int)(blockIdx.x % row_blocks) * NORM_PER;
+  const int lane = (int)threadIdx.x & (lanes - 1);
+  // row = bl * n_time + tt: the block's first by a scalar division
+  int64_t row = NARROW ? (int64_t)blockIdx.x << (8 - lg) : (int64_t)(blockIdx.x / row_blocks);
+  int64_t bl = row / n_time, tt = row - bl * n_time;
+  if (NARROW) {
+    const int sub = (int)threadIdx.x >> lg;
+    row += sub;
+    tt += sub;
+    if (n_time > 256) {
+      if (tt >= n_time) {
+        tt -= n_time;
+        ++bl;
+      }
+    } else {
+      const uint32_t q = (uint32_t)tt / (uint32_t)n_time;
+      tt -= (int64_t)q * n_time;
+      bl += q;
+    }
+  }
+  if (row < rows) {
+    const int64_t b = b0 + bl;
     const double med = stats[2 * b], mad = stats[2 * b + 1];
     double scale = 1.4826 * mad;
     if (scale == 0.0) scale = 1.0;
@@ -881,12 +904,12 @@ cnn_normalize_kernel(const float2* __restrict__ vis, const double* __restrict__ 
     float2 in[NORM_PER / 256];
 #pragma unroll
     for (int i = 0; i < NORM_PER / 256; ++i) {
-      const int f = f0 + i * 256 + (int)threadIdx.x;
+      const int f = f0 + i * lanes + lane;
       in[i] = v[f < n_chan ? f : n_chan - 1];
     }
 #pragma unroll
     for (int i = 0; i < NORM_PER / 256; ++i) {
-      const int f = f0 + i * 256 + (int)threadIdx.x;
+      const int f = f0 + i * lanes + lane;
       const double re = (double)in[i].x, im = (double)in[i].y;
       const float A = (float)sqrt(re * re + im * im);
       const double r = ((double)A - med) * inv;
@@ -1350,10 +1373,19 @@ hipError_t cnn_normalize(const float2* vis, const double* stats, int64_t n_time,
                          int64_t b0, int64_t nb, float* x, hipStream_t s) {
   const int64_t n = nb * n_time * n_chan;
   if (n <= 0) return hipSuccess;
-  const int64_t row_blocks = (n_chan + NORM_PER - 1) / NORM_PER, rows = nb * n_time;
-  const int64_t fit = (1ll << 30) / row_blocks;
-  hipLaunchKernelGGL(cnn_normalize_kernel, dim3((unsigned)((rows < fit ? rows : fit) * row_blocks)), dim3(256), 0, s,
-                     vis, stats, n_time, n_base, n_chan, b0, rows, (unsigned)row_blocks, x);
+  // rows of up to 512 share a block: a block of its own would idle half of the
+  // lanes or more, and 2^24 blocks are more than a launch takes
+  const int64_t rows = nb * n_time;
+  if (n_chan <= NORM_PER / 2) {
+    int lg = 0;
+    while ((4 << lg) < n_chan) ++lg;
+    hipLaunchKernelGGL(cnn_normalize_kernel<true>, dim3((unsigned)ceil_div(rows, 256 >> lg)), dim3(256), 0, s, vis,
+                       stats, n_time, n_base, n_chan, b0, rows, 1u, lg, x);
+  } else {
+    const int64_t row_blocks = ceil_div(n_chan, NORM_PER);
+    hipLaunchKernelGGL(cnn_normalize_kernel<false>, dim3((unsigned)(rows * row_blocks)), dim3(256), 0, s, vis, stats,
+                       n_time, n_base, n_chan, b0, rows, (unsigned)row_blocks, 8, x);
+  }
   return hipGetLastError();
 }
 
