@@ -823,15 +823,14 @@ __global__ void cnn_adam_kernel(float* __restrict__ w, const float* __restrict__
   w[e] -= lr * (mi / c1) / (sqrtf(vi / c2) + eps);
 }
 
-// log1p(r), r >= 0, to about 1e-15 of the result: y = 1 + r = 2^e m with m in
+// log1p(r), r >= 0, to a few units of float64: y = 1 + r = 2^e m with m in
 // [sqrt(1/2), sqrt(2)), log m = 2 artanh(s), s = (m - 1)/(m + 1), by the series
 // 2 s (1 + s^2/3 + s^4/5 + ...), |s| <= 0.1716, up to s^20/21 (the next term is
-// below 1e-18 of the sum).  Below 2^-10, where 1 + r would drop bits of r, the
-// series of log1p itself up to r^6.  The library's float64 log1p and division
-// took most of the kernel below.
+// below 1e-18 of the sum).  With e = 0 the numerator is r itself, not 1 + r - 1,
+// which has lost bits of it (1.1e-13 of the result at r = 2^-10); above, what
+// 1 + r loses is below 3.3e-16 of the result.  The library's float64 log1p and
+// division took most of the kernel below.
 __device__ __forceinline__ double log1p_pos(double r) {
-  if (r < 0x1p-10)
-    return r * fma(r, fma(r, fma(r, fma(r, fma(r, -1.0 / 6.0, 1.0 / 5.0), -1.0 / 4.0), 1.0 / 3.0), -1.0 / 2.0), 1.0);
   if (!(r <= 1.7976931348623157e308)) return r;  // infinite, or not a number
   const double y = 1.0 + r;
   double m = 2.0 * __builtin_amdgcn_frexp_mant(y);  // [1, 2)
@@ -844,7 +843,7 @@ __device__ __forceinline__ double log1p_pos(double r) {
   double q = __builtin_amdgcn_rcp(d);
   q = fma(fma(-d, q, 1.0), q, q);
   q = fma(fma(-d, q, 1.0), q, q);
-  const double s = (m - 1.0) * q, z = s * s;
+  const double s = (e == 0 ? r : m - 1.0) * q, z = s * s;
   double p = 1.0 / 21.0;
   p = fma(p, z, 1.0 / 19.0);
   p = fma(p, z, 1.0 / 17.0);
@@ -862,9 +861,9 @@ __device__ __forceinline__ double log1p_pos(double r) {
 // float32), r = (A - med)/(1.4826 MAD), x = sign(r) log1p|r|.  A block takes
 // NORM_PER elements of one row (baseline, integration), or, with rows of up to
 // half as many (NARROW), as many rows as it has groups of 2^lg >= n_chan / 4
-// lanes.  Bound: HBM, 12 B an element: 66 planes of 524288 in 122 us, 3.4 TB/s
-// (403 us with the library's log1p and division and a thread per element); as
-// many in rows of 64 channels 102 us, of 4 187 us (1.3 and 21.1 ms with a block
+// lanes.  Bound: HBM, 12 B an element: 66 planes of 524288 in 116 us, 3.6 TB/s
+// (328 us with the library's log1p and division and a thread per element); as
+// many in rows of 64 channels 112 us, of 4 188 us (1.3 and 21.1 ms with a block
 // per row).
 constexpr int NORM_PER = 1024;
 template <bool NARROW>
@@ -898,7 +897,9 @@ cnn_normalize_kernel(const float2* __restrict__ vis, const double* __restrict__ 
     const double med = stats[2 * b], mad = stats[2 * b + 1];
     double scale = 1.4826 * mad;
     if (scale == 0.0) scale = 1.0;
-    const double inv = 1.0 / scale;
+    // quotients to the last bit: product with the reciprocal and one correction
+    // (none for an infinite scale, whose quotients are zeros)
+    const double inv = 1.0 / scale, by = inv == 0.0 ? 0.0 : scale;
     const float2* const v = vis + (tt * n_base + b) * n_chan;
     float* const o = x + row * n_chan;
     float2 in[NORM_PER / 256];
@@ -912,7 +913,8 @@ cnn_normalize_kernel(const float2* __restrict__ vis, const double* __restrict__ 
       const int f = f0 + i * lanes + lane;
       const double re = (double)in[i].x, im = (double)in[i].y;
       const float A = (float)sqrt(re * re + im * im);
-      const double r = ((double)A - med) * inv;
+      const double d = (double)A - med, q = d * inv, fix = fma(-q, by, d) * inv;
+      const double r = fabs(q) < 1e300 ? q + fix : q;
       const double xv = log1p_pos(fabs(r));
       if (f < n_chan) o[f] = (float)(r < 0.0 ? -xv : xv);
     }

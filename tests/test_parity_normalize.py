@@ -41,3 +41,35 @@ def test_more_rows_than_a_launch_has_blocks(qc):
         r = (a - med) / (1.4826 * 0.5 * (s[(k - 1) // 2] + s[k // 2]))
         ref = torch.sign(r) * torch.log1p(r.abs())
         assert bool(((x[b].flatten().double() - ref).abs() <= 2.0 ** -23 * ref.abs()).all())
+
+
+def test_rounding_of_small_deviations(qc):
+    """Deviations of 2^-10 to 2^-9 scales, whose bits 1 + r cannot hold: a float64
+    error of 1e-15 moves the float32 rounding of 1e7 values 0.2 times (two
+    elements of 2e7 are allowed), one of 1e-13 at 2^-10 about ten times."""
+    import torch
+    rng = np.random.default_rng(1)
+    n_base, k = 200, 49800
+    u = rng.uniform(2.0 ** -10, 2.0 ** -9, (n_base, k)) * rng.choice([-1, 1], (n_base, k)) * 1.4826
+    a = np.concatenate([np.zeros((n_base, 25050)), 1 + u, np.ones((n_base, 100)), 2 * np.ones((n_base, 25050))], 1)
+    a *= rng.uniform(0.5, 1.0, n_base)[:, None]
+    v = np.ascontiguousarray(a.astype(np.float32).reshape(n_base, 100, 1000).transpose(1, 0, 2)).astype(np.complex64)
+    x = qc.cnn_normalize(torch.from_numpy(v).cuda()).cpu().numpy()
+    assert np.sum(x != np.asarray(cnn.normalize(v)).astype(np.float32)) <= 2
+
+
+def test_scales_out_of_range(qc):
+    """Infinite medians and deviations, and amplitudes that are no number."""
+    import torch
+    rng = np.random.default_rng(2)
+    v = (rng.normal(size=(16, 4, 64)) + 1j * rng.normal(size=(16, 4, 64))).astype(np.complex64)
+    v[:6, 0] = np.inf          # finite scale
+    v[:9, 1] = np.inf          # infinite median
+    v[2, 2, 3] = np.nan
+    v[:, 3] *= np.float32(1e-38)
+    with np.errstate(invalid="ignore"):
+        ref = np.asarray(cnn.normalize(v), np.float64)
+    x = qc.cnn_normalize(torch.from_numpy(v).cuda()).cpu().numpy()
+    assert np.array_equal(np.isnan(x), np.isnan(ref)) and np.array_equal(np.isinf(x), np.isinf(ref))
+    fin = np.isfinite(ref)
+    assert np.all(np.abs(x[fin] - ref[fin]) <= 2.0 ** -23 * np.abs(ref[fin]))
