@@ -466,7 +466,8 @@ const char* qc_stream_last_error(void);
 /* Tile shape of the fused F+X kernel for one (n_fft, n_ant): an index into a
  * fixed list of shapes (spectra in flight, values per thread per FFT pass,
  * ping-pong LDS buffers).  Every shape computes the same sums; shapes differ
- * in speed only.  Index 0 is the default.  qc_fx_tile_count returns 0 when
+ * in speed only.  Index 0 is the default, and a shape may stand at a second
+ * index that saved tuning results name.  qc_fx_tile_count returns 0 when
  * no fused kernel exists for the pair.  The choice is process-wide and is
  * what the autotuner sets. */
 int32_t qc_fx_tile_count(int32_t n_fft, int32_t n_ant);

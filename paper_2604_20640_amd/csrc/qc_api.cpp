@@ -983,11 +983,16 @@ qc_status qc_fx_autotune(const int8_t* x, int64_t ld_x, int32_t n_ant, int64_t n
   double best = 1e300;
   int best_t = 0;
   int64_t best_w = 0;
+  std::vector<double> ms(n, 0.0);
   for (int t = 0; t < n && st == QC_OK; ++t) {
-    set_choice(t, 0);
-    double per = 0.0;
-    st = time_calls(&per);
-    if (st != QC_OK) break;
+    const int first = qc::fused_tile_first(p->n_fft, n_ant, t);
+    double per = ms[first];
+    if (first == t) {
+      set_choice(t, 0);
+      st = time_calls(&per);
+      if (st != QC_OK) break;
+    }
+    ms[t] = per;
     if (ms_per_tile && t < cap) ms_per_tile[t] = per;
     if (per < best) {
       best = per;
@@ -1509,7 +1514,8 @@ qc_status graph_tune(qc_plan* P, const int8_t* const* x, float* const* vis, int 
       const qc_array_desc& D = P->desc[i];
       if (G.fused) {
         std::vector<int64_t> tiles;
-        for (int t = 0; t < qc::fused_tile_count(D.n_fft, D.n_ant); ++t) tiles.push_back(t);
+        for (int t = 0; t < qc::fused_tile_count(D.n_fft, D.n_ant); ++t)
+          if (qc::fused_tile_first(D.n_fft, D.n_ant, t) == t) tiles.push_back(t);
         st = try_value([&](int64_t v) { G.tile = (int)v; }, [&] { return (int64_t)G.tile; }, tiles);
         if (st != QC_OK) break;
       }

@@ -1168,10 +1168,11 @@ static hipError_t launch_fused_p(const FxArgs& a, int64_t n_dump, int64_t spd, i
 // values per thread per FFT pass V, ping-pong LDS buffers PP.  Entry 0 is
 // the default; the others are the candidates an autotuner may time.  The
 // defaults are the fastest at one round of workgroups (16384 spectra of 4096
-// points: 4 antennas 319 us on the ping-pong ring, 366 on the in-place one, 540
-// and more on the others; 32768 spectra of 1024, 8 antennas: 561 us with 8
-// values per thread, 840 with 16).  A shape that stands twice keeps its index
-// in saved tuning results; the in-place ring of (4096, 4) is a candidate.
+// points: 4 antennas 308 us on the ping-pong ring, 358 on the in-place one, 534
+// and more on the others, 2 antennas 232, 243 and 370; 32768 spectra of 1024, 8
+// antennas: 573 us with 8 values per thread, 829 with 16).  Former defaults stand
+// at the end of their lists; a shape that became the default also keeps the index
+// it has in saved tuning results, and is timed once.
 struct FusedTile {
   int S, V;  // S = 0: ring variant (one spectrum in flight, register ring)
   bool PP;
@@ -1196,10 +1197,11 @@ QC_TILES(1024, 4, {2, 16, true, 0}, {2, 16, false, 0}, {4, 16, false, 0}, {2, 8,
 QC_TILES(2048, 4, {0, 16, false, 0}, {1, 16, true, 0}, {1, 16, false, 0}, {1, 16, false, 4},
          {1, 8, true, 0})
 QC_TILES(512, 4, {4, 16, true, 0}, {4, 16, false, 0}, {2, 16, true, 4})
-QC_TILES(1024, 8, {1, 8, true, 0}, {1, 8, true, 0})
+QC_TILES(1024, 8, {1, 8, true, 0}, {1, 8, true, 0}, {1, 16, true, 0})
 QC_TILES(2048, 8, {1, 8, true, 0}, {1, 8, false, 0})
 QC_TILES(1024, 2, {4, 16, true, 0}, {4, 16, false, 0}, {2, 16, true, 4})
-QC_TILES(4096, 2, {0, 16, true, 0}, {1, 16, true, 0}, {1, 16, false, 0}, {1, 16, false, 4}, {0, 16, true, 0})
+QC_TILES(4096, 2, {0, 16, true, 0}, {1, 16, true, 0}, {1, 16, false, 0}, {1, 16, false, 4}, {0, 16, true, 0},
+         {0, 16, false, 0})
 #undef QC_TILES
 
 template <int N, int NA, int I>
@@ -1233,14 +1235,35 @@ static int tile_count() {
   return TileList<N, NA>::count;
 }
 
+// The first index of tile t's shape.
+template <int N, int NA>
+static int tile_first(int t) {
+  for (int i = 0; i < t; ++i) {
+    const FusedTile &a = TileList<N, NA>::tiles[i], &b = TileList<N, NA>::tiles[t];
+    if (a.S == b.S && a.V == b.V && a.PP == b.PP && a.OCC == b.OCC) return i;
+  }
+  return t;
+}
+
+#define QC_CASES                                                     \
+  QC_CASE(4096, 4) QC_CASE(1024, 4) QC_CASE(2048, 4) QC_CASE(512, 4) \
+  QC_CASE(1024, 8) QC_CASE(2048, 8) QC_CASE(1024, 2) QC_CASE(4096, 2)
 int fused_tile_count(int n_fft, int n_ant) {
 #define QC_CASE(NN, NAA) \
   if (n_fft == NN && n_ant == NAA) return tile_count<NN, NAA>();
-  QC_CASE(4096, 4) QC_CASE(1024, 4) QC_CASE(2048, 4) QC_CASE(512, 4)
-  QC_CASE(1024, 8) QC_CASE(2048, 8) QC_CASE(1024, 2) QC_CASE(4096, 2)
+  QC_CASES
 #undef QC_CASE
   return 0;
 }
+
+int fused_tile_first(int n_fft, int n_ant, int tile) {
+#define QC_CASE(NN, NAA) \
+  if (n_fft == NN && n_ant == NAA && tile < tile_count<NN, NAA>()) return tile_first<NN, NAA>(tile);
+  QC_CASES
+#undef QC_CASE
+  return tile;
+}
+#undef QC_CASES
 
 bool fused_supported(int n_fft, int n_ant) { return fused_tile_count(n_fft, n_ant) > 0; }
 

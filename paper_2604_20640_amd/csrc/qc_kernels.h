@@ -30,6 +30,8 @@ struct FxArgs {
 // (n_fft, n_ant); part must hold fused_part_elems() float2.
 bool fused_supported(int n_fft, int n_ant);
 int fused_tile_count(int n_fft, int n_ant);
+// The first index with tile's shape (a shape may stand twice in a list).
+int fused_tile_first(int n_fft, int n_ant, int tile);
 // Compute units of the current device (cached per device; 256 if the query
 // fails).
 int device_cu_count();

@@ -63,7 +63,7 @@ def test_spectra(qc, word, taps):
     assert err[0] <= 1.006 * err[1]
 
 
-@pytest.mark.parametrize("n_ant,in_place", [(4, 7)])
+@pytest.mark.parametrize("n_ant,in_place", [(4, 7), (2, 5)])
 def test_fused(qc, n_ant, in_place):
     """The default tile against the in-place ring tile, all of whose twiddles come
     from the table, one spectrum a dump."""
