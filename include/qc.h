@@ -483,6 +483,13 @@ int32_t qc_fx_get_tile(int32_t n_fft, int32_t n_ant);
  * whatever the width.  Process-wide; set by the autotuner. */
 qc_status qc_fx_set_width(int32_t n_fft, int32_t n_ant, int64_t workgroups);
 int64_t qc_fx_get_width(int32_t n_fft, int32_t n_ant);
+/* How long the runs of spectra are that one workgroup takes, on the current
+ * device (for tests of the kernels' loops): qc_fx_run_spectra, the shortest of a
+ * fused F+X launch of four taps (0 where the shape has no fused kernel);
+ * qc_channelize_run_spectra, the longest of the register-ring F-engine. */
+int64_t qc_fx_run_spectra(int32_t sample, int32_t n_fft, int32_t n_ant, int64_t n_dump, int64_t spec_per_dump);
+int64_t qc_channelize_run_spectra(int32_t sample, int32_t n_fft, int32_t n_ant, int64_t n_spec);
+
 /* Autotuner for the fused kernel: times every tile shape of (n_fft, n_ant) on
  * the caller's input (reps calls of qc_xcorrelate each, after one untimed
  * call) with HIP events on `stream` at the default width, then the fastest

@@ -169,6 +169,10 @@ def lib() -> ctypes.CDLL:
             fn = getattr(L, name)
             fn.argtypes = args
             fn.restype = ctypes.c_int32
+        L.qc_fx_run_spectra.argtypes = [_I32, _I32, _I32, _I64, _I64]
+        L.qc_fx_run_spectra.restype = _I64
+        L.qc_channelize_run_spectra.argtypes = [_I32, _I32, _I32, _I64]
+        L.qc_channelize_run_spectra.restype = _I64
         L.qc_channelize_set_variant.argtypes = [_I32]
         L.qc_channelize_set_variant.restype = ctypes.c_int32
         L.qc_channelize_get_variant.argtypes = []

@@ -929,6 +929,20 @@ qc_status qc_fx_set_width(int32_t n_fft, int32_t n_ant, int64_t workgroups) {
 
 int64_t qc_fx_get_width(int32_t n_fft, int32_t n_ant) { return fused_width_for(n_fft, n_ant); }
 
+int64_t qc_fx_run_spectra(int32_t sample, int32_t n_fft, int32_t n_ant, int64_t n_dump, int64_t spec_per_dump) {
+  if (n_dump < 1 || spec_per_dump < 1) return 0;
+  int64_t cpd = 0;
+  if (sample == QC_SAMPLE_I8 && qc::fused_supported(n_fft, n_ant))
+    cpd = qc::fused_chunks_per_dump(n_fft, n_ant, n_dump, spec_per_dump, fused_width_for(n_fft, n_ant));
+  else if (qc::fused_words_supported(sample, n_fft, n_ant, 4, true))
+    cpd = qc::fused_words_chunks(sample, n_fft, n_ant, n_dump, spec_per_dump);
+  return cpd > 0 ? spec_per_dump / cpd : 0;
+}
+
+int64_t qc_channelize_run_spectra(int32_t sample, int32_t n_fft, int32_t n_ant, int64_t n_spec) {
+  return n_ant < 1 ? 0 : qc::channelize_run(sample, n_fft, n_ant, n_spec);
+}
+
 qc_status qc_fx_autotune(const int8_t* x, int64_t ld_x, int32_t n_ant, int64_t n_samp,
                          const qc_pfb_params* p, int64_t spec_per_dump, int32_t reps, float* vis,
                          double* ms_per_tile, int32_t cap, int32_t* best_out, void* stream) {

@@ -1883,6 +1883,13 @@ chan_ring_kernel(const int8_t* __restrict__ x, int64_t ld_x, int n_ant, const in
                                             out, buf, twp, n_taps, mirrored != 0);
 }
 
+// Spectra per run of the ring F-engine: runs that fill rounds of workgroups of
+// nt threads, 512 threads per CU (what the registers allow).
+static int64_t chan_ring_run(int nt, int groups, int64_t n_spec) {
+  const int64_t chunks = chunks_of_rounds((int64_t)device_cu_count() * (512 / nt), groups, n_spec);
+  return (n_spec + chunks - 1) / chunks;
+}
+
 // The ring F-engine over n_ant rows of ST words.  Four real antennas (two
 // packed transforms) per workgroup up to N = 4096 and two at N = 8192;
 // complex words take half as many antennas, one transform each.  Ping-pong
@@ -1899,11 +1906,7 @@ static hipError_t launch_chan_ring_w(const ChanxArgs& a, void* out, const float*
   if (PP && !a.twp) return hipErrorInvalidValue;
   const int64_t n_spec = a.n_samp / N;
   const int groups = (a.n_ant + NA - 1) / NA;
-  // runs that fill rounds of workgroups, 512 threads per CU (what the
-  // registers allow)
-  int64_t chunks = chunks_of_rounds((int64_t)device_cu_count() * (512 / C::NT), groups, n_spec);
-  const int64_t spb = (n_spec + chunks - 1) / chunks;
-  chunks = (n_spec + spb - 1) / spb;
+  const int64_t spb = chan_ring_run(C::NT, groups, n_spec), chunks = (n_spec + spb - 1) / spb;
   if ((int64_t)groups * chunks > 0x7fffffffLL) return hipErrorInvalidValue;
   auto kern = chan_ring_kernel<N, NA, V, P, PREC, PP, ST>;
   hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
@@ -2000,6 +2003,12 @@ hipError_t launch_channelize_ring_any(const ChanxArgs& a, int sample, int prec, 
     case 8192: return launch_chan_ring_n<8192>(a, sample, prec, out, scale, s);
   }
   return hipErrorNotSupported;
+}
+
+int64_t channelize_run(int sample, int n_fft, int n_ant, int64_t n_spec) {
+  if (n_fft < 1024 || n_fft > 8192 || n_spec < 1) return 0;
+  const int na = (n_fft == 8192 ? 2 : 4) / (sample >= 2 ? 2 : 1);
+  return chan_ring_run(n_fft >= 4096 ? 512 : n_fft / 8, (n_ant + na - 1) / na, n_spec);
 }
 
 hipError_t launch_channelize(const FxArgs& a, int prec, void* out, const float* scale,

@@ -102,6 +102,8 @@ hipError_t launch_fused_words(const FxArgs& a, int sample, int64_t n_dump, int64
 // output with P <= 4, or P <= 8 with int8 words up to N = 4096; requantised
 // output with the built-in P = 4; ring variant selected); hipErrorNotSupported
 // otherwise.
+// (channelize_run: its spectra per workgroup.)
+int64_t channelize_run(int sample, int n_fft, int n_ant, int64_t n_spec);
 hipError_t launch_channelize_ring_any(const ChanxArgs& a, int sample, int prec, void* out, const float* scale,
                                       hipStream_t s);
 hipError_t launch_channelize_any(const ChanxArgs& a, int sample, int prec, void* out, const float* scale,
