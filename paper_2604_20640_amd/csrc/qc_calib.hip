@@ -583,11 +583,12 @@ __global__ void mad_amp4_kernel(const float4* __restrict__ vis, int64_t n_base, 
 //      kept amplitudes at the ranks the counts leave, the threshold, the
 //      remaining flags.
 // Ranks and counts are of the whole population, so the results are the exact
-// order statistics.  A population that the sample cannot bound (half of it
-// zero), whose rank falls outside its window (a sample that misled) or whose
-// lists would overflow (large groups of equal amplitudes) is left open:
-//   4. mad_open_amp_kernel forms the amplitudes of the open ones over their
-//      lists, and mad_kernel selects among those from the start.
+// order statistics.  A population that the sample cannot bound (half of it zero)
+// or whose lists would overflow (large groups of equal amplitudes) is open from
+// step 1: step 2 then forms its amplitudes, over its lists, and mad_kernel
+// selects among those from the start.  One whose rank falls outside its window
+// all the same (a sample that misled) stays at MAD_SCAN; mad_kernel forms the
+// amplitudes on its first pass.
 // 528 planes of 524288, all open because half of each is zero: 10.7 ms, 10.6
 // without the sample (18.1 ms with the amplitudes formed anew by every pass of
 // mad_kernel); of amplitudes that repeat: 5.2 ms (15.7).
@@ -648,10 +649,10 @@ __device__ __forceinline__ void amp4(const float2* __restrict__ vis, const Pop& 
 // Bounds of the sample's order statistics of ranks MAD_SAMPLE/2 -+ MAD_SLACK
 // over keys kv[] (16 per thread): the edges of their bins in a histogram over
 // the middle three quarters of a 64-key subsample.  False when a rank falls
-// outside it.
+// outside it, or when more than `most` of the sample lie within the bounds.
 __device__ __forceinline__ bool sample_bounds(const float (&a)[MAD_SAMPLE_PER], float centre, unsigned* hist,
-                                              unsigned* wsum, unsigned long long* sh, unsigned* sub, uint32_t& klo,
-                                              uint32_t& khi) {
+                                              unsigned* wsum, unsigned long long* sh, unsigned* sub, unsigned most,
+                                              uint32_t& klo, uint32_t& khi) {
   constexpr int NT = MAD_SAMPLE_NT, NBINS = 2048;
   const int t = threadIdx.x;
   auto key = [&](int j) -> uint32_t { return __float_as_uint(fabsf(a[j] - centre)); };
@@ -691,11 +692,14 @@ __device__ __forceinline__ bool sample_bounds(const float (&a)[MAD_SAMPLE_PER], 
   __syncthreads();
   find_digit<NT, NBINS>(hist, MAD_SAMPLE / 2 - MAD_SLACK, wsum, sh);
   const unsigned b0 = (unsigned)__builtin_amdgcn_readfirstlane((int)sh[0]);
+  const unsigned in0 = (unsigned)__builtin_amdgcn_readfirstlane((int)sh[1]);  // of its bin, before the rank
   __syncthreads();
   find_digit<NT, NBINS>(hist, MAD_SAMPLE / 2 + MAD_SLACK, wsum, sh);
   const unsigned b1 = (unsigned)__builtin_amdgcn_readfirstlane((int)sh[0]);
+  const unsigned in1 = (unsigned)__builtin_amdgcn_readfirstlane((int)sh[1]);
+  const unsigned inside = in0 + 2 * MAD_SLACK + ((unsigned)__builtin_amdgcn_readfirstlane((int)hist[b1]) - in1);
   __syncthreads();
-  if (b0 == 0u || b1 == (unsigned)(NBINS - 1)) return false;
+  if (b0 == 0u || b1 == (unsigned)(NBINS - 1) || inside > most) return false;
   klo = lo + ((b0 - 1u) << s);
   khi = lo + (b1 << s);
   return true;
@@ -704,13 +708,11 @@ __device__ __forceinline__ bool sample_bounds(const float (&a)[MAD_SAMPLE_PER], 
 template <bool VEC>
 __global__ void __launch_bounds__(MAD_SAMPLE_NT)
 mad_sample_kernel(const float2* __restrict__ vis, int64_t n_time, int64_t n_base, int n_chan, float sigma,
-                  int population, int flags, MadWin* __restrict__ win) {
+                  int population, MadWin* __restrict__ win) {
   __shared__ unsigned hist[2048];
   __shared__ unsigned wsum[MAD_SAMPLE_NT / 64];
   __shared__ unsigned long long sh[4];
   __shared__ unsigned sub[64];
-  __shared__ unsigned held[3];
-  if (threadIdx.x < 3) held[threadIdx.x] = 0u;
   const Pop pop = make_pop(blockIdx.x, n_time, n_base, n_chan, population);
   const int64_t n4 = pop.count / 4;
   // strata of the population in order, four neighbouring elements of each,
@@ -725,10 +727,13 @@ mad_sample_kernel(const float2* __restrict__ vis, int64_t n_time, int64_t n_base
     amp4<VEC>(vis, pop, 4 * (g0 + (int64_t)(h % (uint32_t)(g1 - g0))), a + 4 * q);
   }
   uint32_t k0 = 0u, k1 = 0u, e0 = 0u, e1 = 0u;
-  bool ok = sample_bounds(a, 0.f, hist, wsum, sh, sub, k0, k1);
+  // the median's list takes an eighth of the population; the deviations' a
+  // quarter, of which the slack added below takes about 8 %
+  bool ok = sample_bounds(a, 0.f, hist, wsum, sh, sub, MAD_SAMPLE / 8, k0, k1);
   const float lo = __uint_as_float(k0), hi = __uint_as_float(k1);
   // the sample's deviations are from the centre of the median's window
-  if (ok) ok = sample_bounds(a, 0.5f * (lo + hi), hist, wsum, sh, sub, e0, e1);
+  if (ok) ok = sample_bounds(a, 0.5f * (lo + hi), hist, wsum, sh, sub, MAD_SAMPLE / 6, e0, e1);
+  if (threadIdx.x != 0) return;
   MadWin w;
   w.state = MAD_OPEN;
   w.n_le = w.n_in = w.n_med = w.n_dev = w.n_thr = 0u;
@@ -759,31 +764,7 @@ mad_sample_kernel(const float2* __restrict__ vis, int64_t n_time, int64_t n_base
     w.q_t1 = sq(t1);
     // the windows in order, and every square a normal float32
     if (c0 < lo && hi < c1 && lo > 1e-15f && r1 < 1e18f && t1 < 1e18f) w.state = MAD_SCAN;
-    // what the lists would hold of the sample: no scan for one that overflows
-    unsigned n_med = 0u, n_dev = 0u, n_thr = 0u;
-#pragma unroll
-    for (int j = 0; j < MAD_SAMPLE_PER; ++j) {
-      n_med += a[j] > lo && a[j] <= hi;
-      n_dev += (a[j] >= l0 && a[j] < c0) || (a[j] > c1 && a[j] <= r1);
-      n_thr += a[j] > t0 && a[j] <= t1;
-    }
-#pragma unroll
-    for (int d = 32; d >= 1; d >>= 1) {
-      n_med += __shfl_xor(n_med, d);
-      n_dev += __shfl_xor(n_dev, d);
-      n_thr += __shfl_xor(n_thr, d);
-    }
-    if ((threadIdx.x & 63) == 0) {
-      atomicAdd(&held[0], n_med);
-      atomicAdd(&held[1], n_dev);
-      atomicAdd(&held[2], n_thr);
-    }
   }
-  __syncthreads();
-  if (threadIdx.x != 0) return;
-  if (held[0] > mad_cap_med(MAD_SAMPLE) || held[1] > mad_cap_dev(MAD_SAMPLE) ||
-      (flags && held[2] > mad_cap_thr(MAD_SAMPLE)))
-    w.state = MAD_OPEN;
   win[blockIdx.x] = w;
 }
 
@@ -800,9 +781,38 @@ mad_scan_kernel(const float2* __restrict__ vis, int64_t n_time, int64_t n_base, 
   const int64_t id = blockIdx.x / (unsigned)chunks;
   const int64_t i0 = (int64_t)(blockIdx.x % (unsigned)chunks) * MAD_CHUNK;
   MadWin* const w = win + id;
-  if (w->state != MAD_SCAN) return;
   const Pop pop = make_pop(id, n_time, n_base, n_chan, population);
   const int64_t n = pop.count;
+  if (w->state != MAD_SCAN) {  // open: the chunk's amplitudes
+    constexpr int U = 4;
+    float* const o = lists + id * n;
+    const int64_t end = i0 + MAD_CHUNK < n ? i0 + MAD_CHUNK : n;
+    for (int64_t k0 = i0 + 4 * (int)threadIdx.x; k0 < end; k0 += 4 * U * NT) {
+      float a[U][4];
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        const int64_t k = k0 + 4 * u * NT;
+        if (VEC) {
+          amp4<true>(vis, pop, k < end ? k : k0, a[u]);
+        } else {
+#pragma unroll
+          for (int j = 0; j < 4; ++j) a[u][j] = amp_f32(vis[pop.off(k + j < end ? k + j : k0)]);
+        }
+      }
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        const int64_t k = k0 + 4 * u * NT;
+        if (VEC) {
+          if (k < end) *reinterpret_cast<float4*>(o + k) = make_float4(a[u][0], a[u][1], a[u][2], a[u][3]);
+        } else {
+#pragma unroll
+          for (int j = 0; j < 4; ++j)
+            if (k + j < end) o[k + j] = a[u][j];
+        }
+      }
+    }
+    return;
+  }
   float* const g_med = lists + id * n;
   float* const g_dev = g_med + mad_cap_med(n);
   float* const g_thr = g_dev + mad_cap_dev(n);
@@ -1003,42 +1013,16 @@ mad_finish_kernel(int64_t n_time, int64_t n_base, int n_chan, float sigma, int p
   }
 }
 
-// The amplitudes of the populations left open, parts blocks each.  Bound: HBM,
-// 12 B an element; a block whose population is done only reads its state.
-template <bool VEC>
-__global__ void __launch_bounds__(256)
-mad_open_amp_kernel(const float2* __restrict__ vis, int64_t n_time, int64_t n_base, int n_chan, int population,
-                    int parts, const MadWin* __restrict__ win, float* __restrict__ amp) {
-  const int64_t id = blockIdx.x / (unsigned)parts;
-  if (__builtin_amdgcn_readfirstlane(win[id].state) == MAD_DONE) return;
-  const Pop pop = make_pop(id, n_time, n_base, n_chan, population);
-  const int64_t n = pop.count, step = (int64_t)parts * 256;
-  float* const o = amp + id * n;
-  const int64_t first = (int64_t)(blockIdx.x % (unsigned)parts) * 256 + threadIdx.x;
-  if constexpr (VEC) {  // n is a multiple of four
-    constexpr int U = 4;
-    const int64_t n4 = n / 4;
-    for (int64_t j0 = first; j0 < n4; j0 += U * step) {
-      float a[U][4];
-#pragma unroll
-      for (int u = 0; u < U; ++u) amp4<true>(vis, pop, 4 * (j0 + u * step < n4 ? j0 + u * step : j0), a[u]);
-#pragma unroll
-      for (int u = 0; u < U; ++u)
-        if (j0 + u * step < n4)
-          reinterpret_cast<float4*>(o)[j0 + u * step] = make_float4(a[u][0], a[u][1], a[u][2], a[u][3]);
-    }
-  } else {
-    for (int64_t i = first; i < n; i += step) o[i] = amp_f32(vis[pop.off(i)]);
-  }
-}
-
 template <int NT, int DB>
 __global__ void __launch_bounds__(NT)
 mad_kernel(const float2* __restrict__ vis, int64_t n_time, int64_t n_base, int n_chan, float sigma,
-           int population, int64_t cap, int64_t comp_cap, const float* __restrict__ gamp,
-           const MadWin* __restrict__ done, uint8_t* __restrict__ mask, double* __restrict__ thresh,
+           int population, int64_t cap, int64_t comp_cap, float* __restrict__ gamp,
+           const MadWin* __restrict__ win, uint8_t* __restrict__ mask, double* __restrict__ thresh,
            double* __restrict__ stats) {
-  if (done && __builtin_amdgcn_readfirstlane(done[blockIdx.x].state) == MAD_DONE) return;
+  // the amplitudes are in gamp, or (MAD_SCAN) go there on the first pass
+  const int state = win ? __builtin_amdgcn_readfirstlane(win[blockIdx.x].state) : MAD_OPEN;
+  if (state == MAD_DONE) return;
+  const bool formed = gamp && state == MAD_OPEN;
   __shared__ unsigned hist[1 << DB];
   __shared__ unsigned wsum[NT / 64];
   __shared__ unsigned long long sh[4];
@@ -1089,7 +1073,7 @@ mad_kernel(const float2* __restrict__ vis, int64_t n_time, int64_t n_base, int n
     constexpr int U = 8;
     for (int64_t i0 = threadIdx.x; i0 < n; i0 += (int64_t)U * NT) {
       float a[U];
-      if (gamp) {
+      if (formed) {
 #pragma unroll
         for (int u = 0; u < U; ++u) {
           const int64_t i = i0 + (int64_t)u * NT;
@@ -1110,6 +1094,7 @@ mad_kernel(const float2* __restrict__ vis, int64_t n_time, int64_t n_base, int n
         const int64_t i = i0 + (int64_t)u * NT;
         if (i < n) {
           if (cached) acache[i] = a[u];
+          else if (gamp && !formed) gamp[id * n + i] = a[u];
           const uint32_t kv = __float_as_uint(a[u]);
           amin = kv < amin ? kv : amin;
           amax = kv > amax ? kv : amax;
@@ -1257,16 +1242,15 @@ hipError_t launch_mad(const float2* vis, int64_t n_time, int64_t n_base, int n_c
                   population, MAD_CAP_SMALL, (int64_t)0, nullptr, nullptr, mask, thresh, stats);
   } else {
     MadWin* win = nullptr;
-    const float* gamp = nullptr;
+    float* gamp = nullptr;
+    const bool vec = n_chan % 4 == 0 && (reinterpret_cast<uintptr_t>(vis) & 15u) == 0 &&
+                     (reinterpret_cast<uintptr_t>(mask) & 3u) == 0;
     if (amp_scratch && mad_scans(npop, count, population)) {
       float* const lists = amp_scratch;
       win = reinterpret_cast<MadWin*>(amp_scratch + (npop * count + 1) / 2 * 2);
-      const bool vec = n_chan % 4 == 0 && (reinterpret_cast<uintptr_t>(vis) & 15u) == 0 &&
-                       (reinterpret_cast<uintptr_t>(mask) & 3u) == 0;
       const int chunks = (int)((count + MAD_CHUNK - 1) / MAD_CHUNK);
       hipError_t e = launch(vec ? mad_sample_kernel<true> : mad_sample_kernel<false>, dim3((unsigned)npop),
-                            dim3(MAD_SAMPLE_NT), 0, s, vis, n_time, n_base, n_chan, sigma, population, (int)(mask != nullptr),
-                            win);
+                            dim3(MAD_SAMPLE_NT), 0, s, vis, n_time, n_base, n_chan, sigma, population, win);
       if (e == hipSuccess)
         e = launch(vec ? mad_scan_kernel<true> : mad_scan_kernel<false>, dim3((unsigned)(npop * chunks)),
                    dim3(256), 0, s, vis, n_time, n_base, n_chan, population, chunks, win, lists, mask);
@@ -1276,11 +1260,6 @@ hipError_t launch_mad(const float2* vis, int64_t n_time, int64_t n_base, int n_c
                          sigma, population, win, lists, mask, thresh, stats)
                 : launch(mad_finish_kernel<512>, dim3((unsigned)npop), dim3(512), 0, s, n_time, n_base, n_chan, sigma,
                          population, win, lists, mask, thresh, stats);
-      // about 2048 blocks, should all be open
-      const int parts = (int)std::max<int64_t>(1, std::min<int64_t>(chunks, 2048 / npop));
-      if (e == hipSuccess)
-        e = launch(vec ? mad_open_amp_kernel<true> : mad_open_amp_kernel<false>, dim3((unsigned)(npop * parts)),
-                   dim3(256), 0, s, vis, n_time, n_base, n_chan, population, parts, win, lists);
       if (e != hipSuccess) return e;
       gamp = lists;
     }

@@ -122,3 +122,19 @@ def test_open_populations_beside_closed_ones(qc, off):
     top = med + 3 * 1.4826 * np.median(np.abs(a - med), axis=(0, 2), keepdims=True)
     v[:, 5::7][:, :a.shape[1], :90] = top[:, :v[:, 5::7].shape[1]].astype(np.complex64)
     _check(qc, v, 3.0, 0, off)
+
+
+def test_a_sample_that_misled(qc):
+    """Windows that miss: the sample takes elements of one pattern, the rest of the
+    population differs, so the amplitudes are formed by the last step."""
+    n = 65536
+    n4, strata = n // 4, 3072
+    g = np.arange(strata, dtype=np.int64)
+    g0, g1 = g * n4 // strata, (g + 1) * n4 // strata
+    h = (g.astype(np.uint32) * np.uint32(2654435761)) >> np.uint32(8)
+    at = g0 + h.astype(np.int64) % (g1 - g0)
+    v = _noise((1, 2, n), 17)
+    v[0, 0] *= np.float32(50)
+    quads = v[0, 0].reshape(n4, 4)
+    quads[at] /= np.float32(50)
+    _check(qc, v, 5.0, 0)
