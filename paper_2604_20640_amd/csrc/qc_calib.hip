@@ -1216,16 +1216,23 @@ constexpr int64_t MAD_COMP_MAX = 32768;
 // The one-pass route takes populations of contiguous rows (all but the
 // per-channel ones) that do not fit the LDS of one workgroup.  Below, mad_kernel
 // alone takes 44 us for ten populations of 32768 with their amplitude pass
-// (its selection passes read LDS), the three steps and the check 59 us.
-bool mad_scans(int64_t npop, int64_t count, int population) {
-  return population != 1 && count > MAD_CAP_BIG && count <= 0x7fffffffLL &&
+// (its selection passes read LDS), the three steps and the check 59 us.  Of
+// populations no more than the compute units, whose time is that of one
+// workgroup without the route, they have to be somewhat larger, the more so
+// where elements are read one by one (vec false): one to 66 populations of
+// 37000 take 61 to 74 us without and 64 to 76 with it (77 to 92 one by one), of
+// 48000 74 to 84 and 65 to 77 (80 to 98), of 64000 85 to 101 and 68 to 80 (82 to
+// 102).
+bool mad_scans(int64_t npop, int64_t count, int population, bool vec) {
+  const int64_t least = npop > device_cu_count() ? MAD_CAP_BIG + 1 : vec ? 42000 : 60000;
+  return population != 1 && count >= least && count <= 0x7fffffffLL &&
          npop * ((count + MAD_CHUNK - 1) / MAD_CHUNK) <= 0x7fffffffLL;
 }
 
 int64_t mad_scratch_floats(int64_t n_time, int64_t n_base, int n_chan, int population) {
   const int64_t npop = population == 0 ? n_base : population == 1 ? n_base * n_chan : n_time * n_base;
   const int64_t count = population == 0 ? n_time * n_chan : population == 1 ? n_time : n_chan;
-  if (mad_scans(npop, count, population))
+  if (population != 1 && count > MAD_CAP_BIG)
     return (npop * count + 1) / 2 * 2 + npop * (int64_t)(sizeof(MadWin) / sizeof(float));
   return count > MAD_CAP_SMALL ? npop * count : 0;
 }
@@ -1245,7 +1252,7 @@ hipError_t launch_mad(const float2* vis, int64_t n_time, int64_t n_base, int n_c
     float* gamp = nullptr;
     const bool vec = n_chan % 4 == 0 && (reinterpret_cast<uintptr_t>(vis) & 15u) == 0 &&
                      (reinterpret_cast<uintptr_t>(mask) & 3u) == 0;
-    if (amp_scratch && mad_scans(npop, count, population)) {
+    if (amp_scratch && mad_scans(npop, count, population, vec)) {
       float* const lists = amp_scratch;
       win = reinterpret_cast<MadWin*>(amp_scratch + (npop * count + 1) / 2 * 2);
       const int chunks = (int)((count + MAD_CHUNK - 1) / MAD_CHUNK);

@@ -124,6 +124,17 @@ def test_open_populations_beside_closed_ones(qc, off):
     _check(qc, v, 3.0, 0, off)
 
 
+@pytest.mark.parametrize("shape,pop,off", [
+    ((1, 3, 41996), 0, 0), ((42, 2, 1000), 0, 0), ((59, 2, 1001), 0, 0), ((60, 2, 1001), 0, 0), ((30, 3, 2048), 0, 1),
+    ((1, 2, 59999), 2, 0), ((2, 1, 60003), 2, 0), ((2, 130, 36865), 2, 1), ((2, 150, 36868), 2, 0),
+    ((28, 3, 2048), 0, 0), ((28, 300, 1336), 0, 0),
+])
+def test_edges_of_the_route(qc, shape, pop, off):
+    """Few populations from 42000 elements, read one by one from 60000, and more
+    populations than compute units from 36865."""
+    _check(qc, _noise(shape, sum(shape)), 4.0, pop, off)
+
+
 def test_a_sample_that_misled(qc):
     """Windows that miss: the sample takes elements of one pattern, the rest of the
     population differs, so the amplitudes are formed by the last step."""
