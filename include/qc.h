@@ -538,13 +538,17 @@ qc_status qc_timing_enable(int32_t on);
 qc_status qc_timing_read(int32_t kernel, double* total_ms, int64_t* launches);
 
 /* F-engine kernel choice (process-wide; not thread-safe against concurrent
- * calls): 0 (default) uses the register-ring kernel where it applies (n_fft
+ * calls): 0 (default) uses the register-ring kernel where it applies and, for
+ * filters other than the built-in P = 4, is the faster one by the sizes (n_fft
  * 1024..8192; float32 output with any taps, P <= 4, or P <= 8 for int8 words up
  * to n_fft 4096; requantised output with the built-in P = 4: the fused ring
  * tile's FIR and transform, writing spectra out), 1 always the plain kernel.  Both compute the same
  * sums (Sec. 4.2 F-engine); the choice only affects speed.  Used by
- * qc_pfb_channelize and the two-pass paths of qc_xcorrelate. */
+ * qc_pfb_channelize and the two-pass paths of qc_xcorrelate.
+ * qc_channelize_ring_always (for tests): with variant 0, the ring wherever it
+ * applies. */
 qc_status qc_channelize_set_variant(int32_t variant);
+void qc_channelize_ring_always(int32_t on);
 int32_t qc_channelize_get_variant(void);
 
 /* Float32 X-engine kernel choice (process-wide; not thread-safe against

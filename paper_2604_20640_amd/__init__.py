@@ -175,6 +175,8 @@ def lib() -> ctypes.CDLL:
         L.qc_channelize_run_spectra.restype = _I64
         L.qc_channelize_set_variant.argtypes = [_I32]
         L.qc_channelize_set_variant.restype = ctypes.c_int32
+        L.qc_channelize_ring_always.argtypes = [_I32]
+        L.qc_channelize_ring_always.restype = None
         L.qc_channelize_get_variant.argtypes = []
         L.qc_channelize_get_variant.restype = ctypes.c_int32
         L.qc_xengine_set_variant.argtypes = [_I32]

@@ -1878,6 +1878,8 @@ qc_status qc_channelize_set_variant(int32_t variant) {
   return QC_OK;
 }
 
+void qc_channelize_ring_always(int32_t on) { qc::set_ring_always(on != 0); }
+
 int32_t qc_channelize_get_variant(void) { return qc::get_channelize_variant(); }
 
 qc_status qc_xengine_set_variant(int32_t variant) {

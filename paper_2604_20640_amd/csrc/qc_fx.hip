@@ -1961,10 +1961,12 @@ static hipError_t launch_chan_t(const FxArgs& a, int prec, void* out, const floa
 #undef QC_CHAN_LAUNCH
 }
 
-static int g_chan_variant = 0;  // 0: ring variant where it applies, 1: always the plain kernel
+static int g_chan_variant = 0;  // 0: ring variant where it pays, 1: always the plain kernel
+static bool g_ring_always = false;  // with 0: wherever it applies
 
 void set_channelize_variant(int v) { g_chan_variant = v; }
 int get_channelize_variant() { return g_chan_variant; }
+void set_ring_always(bool on) { g_ring_always = on; }
 
 template <int N>
 static hipError_t launch_chan_ring_n(const ChanxArgs& a, int sample, int prec, void* out, const float* scale,
@@ -1978,6 +1980,46 @@ static hipError_t launch_chan_ring_n(const ChanxArgs& a, int sample, int prec, v
     case 3: return launch_chan_ring_st<N, 4, 3>(a, prec, out, scale, s);
   }
   return hipErrorInvalidValue;
+}
+
+int64_t channelize_run(int sample, int n_fft, int n_ant, int64_t n_spec) {
+  if (n_fft < 1024 || n_fft > 8192 || n_spec < 1) return 0;
+  const int na = (n_fft == 8192 ? 2 : 4) / (sample >= 2 ? 2 : 1);
+  return chan_ring_run(n_fft >= 4096 ? 512 : n_fft / 8, (n_ant + na - 1) / na, n_spec);
+}
+
+// Whether the ring F-engine is the faster of the two for float32 output of a
+// prototype other than the built-in four taps (which it takes always): by the
+// times in microseconds that the two come to, fitted to 4832 sizes (1 to 32
+// antennas, 2^15 to 2^24 samples, 1 to 8 taps).  The ring reads each sample once
+// but works on groups of four antennas (two of complex words) and takes its time
+// by the spectrum of a run, with a start of several spectra; the plain kernel
+// reads each sample once per tap, for pairs of antennas (one of complex words),
+// and is short where it does not fill the GPU (about 1.5 Mi values).  4 antennas,
+// N = 4096, 4 taps: ring 10 and plain 12 us at 8 spectra, 30 and 77 at 1024; N =
+// 1024: 11 and 10 at 64, 31 and 51 at 4096; one antenna, N = 1024, one tap: 73 and
+// 42 at 16384.  Over the sizes fitted the choice is within 1 % of the faster one on
+// average (the ring throughout would be 12 % off, the plain kernel 13), and 2 % of
+// them lose more than 5 % by it.
+static bool ring_pays(int sample, int n_fft, int n_ant, int64_t n_spec, int n_taps) {
+  struct Cost {
+    double ring, spectrum[2];                 // start; a spectrum of a run (real, complex words)
+    double plain, sample[2], value[2], full[2];  // start; a Mi sample and tap; a Mi value, and beyond 1.5 of them
+  };
+  static constexpr Cost costs[] = {{8.7, {2.6, 1.4}, 6.3, {0.67, 0.55}, {0.24, 1.2}, {2.4, 1.35}},
+                                   {8.8, {3.3, 2.4}, 6.7, {0.86, 0.70}, {0.1, 0.8}, {3.75, 2.7}},
+                                   {6.3, {3.3, 2.8}, 7.5, {1.1, 0.85}, {0.0, 0.4}, {4.3, 3.4}},
+                                   {18.2, {4.4, 2.85}, 12.5, {1.07, 0.74}, {-1.3, -1.0}, {7.2, 6.7}}};
+  const int cplx = sample >= 2;
+  const Cost& c = costs[n_fft == 1024 ? 0 : n_fft == 2048 ? 1 : n_fft == 4096 ? 2 : 3];
+  const double mi = (double)n_spec * n_fft / (1 << 20);                // Mi samples of one antenna
+  const double out = 8.0 * n_ant * mi / (cplx ? 1 : 2);                // MiB of spectra
+  const double values = mi * (cplx ? n_ant : (n_ant + 1) / 2);         // what the plain kernel transforms
+  const double run = (double)channelize_run(sample, n_fft, n_ant, n_spec);
+  const double ring = c.ring + c.spectrum[cplx] * run + 0.22 * out + (n_taps > 4 ? 1.1 + 1.15 * run : 0.0);
+  const double plain = c.plain + 0.8 * n_taps + c.sample[cplx] * n_taps * n_ant * mi / (cplx ? 1 : 2) +
+                       c.value[cplx] * values + c.full[cplx] * (values > 1.5 ? values - 1.5 : 0.0);
+  return ring < 0.97 * plain;
 }
 
 // The ring takes every prototype whose taps and samples fit a thread's
@@ -1996,6 +2038,10 @@ hipError_t launch_channelize_ring_any(const ChanxArgs& a, int sample, int prec, 
   // 16-bit words at N = 8192 (four distinct tap positions per thread and a
   // ring twice as wide) would spill inside the loop: the plain kernel
   if (a.n_fft == 8192 && (sample == 1 || sample == 3)) return hipErrorNotSupported;
+  if (a.n_fft < 1024) return hipErrorNotSupported;
+  if (!g_ring_always && !(a.n_taps == 4 && a.taps_symmetric) &&
+      !ring_pays(sample, a.n_fft, a.n_ant, a.n_samp / a.n_fft, a.n_taps))
+    return hipErrorNotSupported;
   switch (a.n_fft) {
     case 1024: return launch_chan_ring_n<1024>(a, sample, prec, out, scale, s);
     case 2048: return launch_chan_ring_n<2048>(a, sample, prec, out, scale, s);
@@ -2003,12 +2049,6 @@ hipError_t launch_channelize_ring_any(const ChanxArgs& a, int sample, int prec, 
     case 8192: return launch_chan_ring_n<8192>(a, sample, prec, out, scale, s);
   }
   return hipErrorNotSupported;
-}
-
-int64_t channelize_run(int sample, int n_fft, int n_ant, int64_t n_spec) {
-  if (n_fft < 1024 || n_fft > 8192 || n_spec < 1) return 0;
-  const int na = (n_fft == 8192 ? 2 : 4) / (sample >= 2 ? 2 : 1);
-  return chan_ring_run(n_fft >= 4096 ? 512 : n_fft / 8, (n_ant + na - 1) / na, n_spec);
 }
 
 hipError_t launch_channelize(const FxArgs& a, int prec, void* out, const float* scale,

@@ -64,8 +64,10 @@ hipError_t launch_reduce(const float2* part, int64_t n_dump, int64_t cpd, int64_
                          int64_t nb = 0, const HistArgs* hist = nullptr);
 
 // Standalone F-engine.  out layout [n_ant][n_spec][n_chan]; prec 0..3 as qc_prec.
-// Variant 0 uses the ring kernel where it applies (launch_channelize_ring_any),
-// 1 always the plain kernel.
+// Variant 0 uses the ring kernel where it applies and pays
+// (launch_channelize_ring_any), 1 always the plain kernel.  set_ring_always: the
+// ring wherever it applies, with variant 0.
+void set_ring_always(bool on);
 void set_channelize_variant(int v);
 int get_channelize_variant();
 hipError_t launch_channelize(const FxArgs& a, int prec, void* out, const float* scale,
@@ -100,7 +102,8 @@ hipError_t launch_fused_words(const FxArgs& a, int sample, int64_t n_dump, int64
                               float2* part, hipStream_t s, const float2* twp);
 // The ring F-engine for any word where it applies (N = 1024..8192; float32
 // output with P <= 4, or P <= 8 with int8 words up to N = 4096; requantised
-// output with the built-in P = 4; ring variant selected); hipErrorNotSupported
+// output with the built-in P = 4; ring variant selected; where it is the faster
+// kernel, unless with the built-in P = 4); hipErrorNotSupported
 // otherwise.
 // (channelize_run: its spectra per workgroup.)
 int64_t channelize_run(int sample, int n_fft, int n_ant, int64_t n_spec);

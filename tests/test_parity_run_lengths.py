@@ -40,6 +40,13 @@ def _oracle(word, x, N, P, chans, hist=None, taps=None):
     return np.concatenate(out)
 
 
+@pytest.fixture
+def ring_always(qc):
+    qc.lib().qc_channelize_ring_always(1)
+    yield
+    qc.lib().qc_channelize_ring_always(0)
+
+
 FUSED = [("i8", 4, 4096), ("i8", 2, 4096), ("i8", 4, 1024), ("i8", 8, 1024), ("i8", 4, 2048)] + [
     (w, a, n) for w in ("i16", "ci8", "ci16") for a, n in ((4, 4096), (2, 4096), (4, 1024), (4, 2048))]
 
@@ -69,8 +76,8 @@ def test_fused(qc, word, n_ant, N, run):
     ("i16", 4, 1024, 4), ("i16", 6, 4096, 3), ("ci8", 3, 2048, 4), ("ci8", 2, 8192, 2), ("ci16", 3, 1024, 3),
     ("ci16", 2, 4096, 4),
 ])
-@pytest.mark.parametrize("run", [2, 3, 9])
-def test_ring(qc, word, n_ant, N, P, run):
+@pytest.mark.parametrize("run", [1, 2, 3, 9])
+def test_ring(qc, ring_always, word, n_ant, N, P, run):
     import torch
     s = SAMPLE[word]
     length = qc.lib().qc_channelize_run_spectra
@@ -86,3 +93,27 @@ def test_ring(qc, word, n_ant, N, P, run):
     out, _ = qc.pfb_channelize_ex(torch.from_numpy(x).cuda(), N, P, taps=torch.from_numpy(taps).cuda(), hist=hd)
     got = out[:, :, torch.from_numpy(chans).cuda()].cpu().numpy()
     assert np.max(np.abs(got - ref)) <= 1e-5 * np.sqrt(np.mean(np.abs(ref) ** 2))
+
+
+@pytest.mark.parametrize("word,n_ant,N,P,n_spec,ring", [
+    ("i8", 4, 4096, 4, 1024, True), ("i8", 1, 1024, 1, 16384, False), ("i8", 4, 1024, 1, 64, False),
+    ("i8", 13, 2048, 8, 1531, True), ("ci16", 4, 4096, 4, 1024, True), ("ci16", 13, 1024, 1, 157, False),
+    ("i8", 2, 8192, 1, 256, False),
+])
+def test_the_choice_of_kernel(qc, word, n_ant, N, P, n_spec, ring):
+    """By default the kernel that is the faster one by a clear margin runs: the
+    spectra are that kernel's, to the bit."""
+    import torch
+    x = torch.from_numpy(_words(word, n_ant, N * n_spec, 5)).cuda()
+    t = torch.from_numpy(np.random.default_rng(P).normal(size=P * N).astype(np.float32)).cuda()
+    got, _ = qc.pfb_channelize_ex(x, N, P, taps=t)
+    try:
+        if ring:
+            qc.lib().qc_channelize_ring_always(1)
+        else:
+            qc.channelize_variant(1)
+        ref, _ = qc.pfb_channelize_ex(x, N, P, taps=t)
+    finally:
+        qc.lib().qc_channelize_ring_always(0)
+        qc.channelize_variant(0)
+    assert torch.equal(got, ref)
