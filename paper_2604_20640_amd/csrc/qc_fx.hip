@@ -1804,7 +1804,9 @@ __device__ __forceinline__ void chan_ring_body(const int8_t* __restrict__ x, int
     __syncthreads();
     if constexpr (PP)
       fft_pp_passes<N, 1, C::NT, V, 0, PpTw<N, V, C::BUF>::ROWS, 0, PREC != 0>(
-          b0, b1, twl, P > 4 ? in_place(twp) : twp, tid);
+          // kept over the loop for 16-bit words: 13 antennas x 1024 spectra 90 us, 94 in
+          // place; read in place for 8-bit ones: 83 us, 86 kept, complex 93 and 103
+          b0, b1, twl, ST == 1 || ST == 3 ? twp : in_place(twp), tid);
     else F::run(b0, b0, twl, tid);
     // The FIR of spectrum m is done: shift the ring here, before the
     // stores, so the wait for the prefetch does not also wait for them.
