@@ -1016,13 +1016,19 @@ mad_finish_kernel(int64_t n_time, int64_t n_base, int n_chan, float sigma, int p
 template <int NT, int DB>
 __global__ void __launch_bounds__(NT)
 mad_kernel(const float2* __restrict__ vis, int64_t n_time, int64_t n_base, int n_chan, float sigma,
-           int population, int64_t cap, int64_t comp_cap, float* __restrict__ gamp,
+           int population, int64_t cap, int64_t comp_cap, float* __restrict__ gamp_big,
            const MadWin* __restrict__ win, uint8_t* __restrict__ mask, double* __restrict__ thresh,
            double* __restrict__ stats) {
-  // the amplitudes are in gamp, or (MAD_SCAN) go there on the first pass
-  const int state = win ? __builtin_amdgcn_readfirstlane(win[blockIdx.x].state) : MAD_OPEN;
-  if (state == MAD_DONE) return;
-  const bool formed = gamp && state == MAD_OPEN;
+  // the amplitudes are in gamp, or (MAD_SCAN) go there on the first pass; small
+  // populations have neither
+  constexpr bool BIG = NT >= 1024;
+  float* const gamp = BIG ? gamp_big : nullptr;
+  bool formed = BIG && gamp != nullptr;
+  if (BIG && win) {
+    const int state = __builtin_amdgcn_readfirstlane(win[blockIdx.x].state);
+    if (state == MAD_DONE) return;
+    formed = formed && state == MAD_OPEN;
+  }
   __shared__ unsigned hist[1 << DB];
   __shared__ unsigned wsum[NT / 64];
   __shared__ unsigned long long sh[4];
@@ -1088,13 +1094,16 @@ mad_kernel(const float2* __restrict__ vis, int64_t n_time, int64_t n_base, int n
         }
 #pragma unroll
         for (int u = 0; u < U; ++u) a[u] = amp_f32(v[u]);
+        if (BIG && gamp)
+#pragma unroll
+          for (int u = 0; u < U; ++u)
+            if (i0 + (int64_t)u * NT < n) gamp[id * n + i0 + (int64_t)u * NT] = a[u];
       }
 #pragma unroll
       for (int u = 0; u < U; ++u) {
         const int64_t i = i0 + (int64_t)u * NT;
         if (i < n) {
           if (cached) acache[i] = a[u];
-          else if (gamp && !formed) gamp[id * n + i] = a[u];
           const uint32_t kv = __float_as_uint(a[u]);
           amin = kv < amin ? kv : amin;
           amax = kv > amax ? kv : amax;
