@@ -43,10 +43,12 @@ namespace {
 // conjugates follow from the finished sums (image_mirror_kernel).  Bound: the
 // atomics: 8.1 M samples of 32 antennas onto 1024 x 1024 took 2.3 ms with four
 // per sample (14 G/s); runs leave about one sample in nine and the conjugates
-// none, 62 us and 6 us for the mirror pass (2.1 TB/s of samples).
+// none, 62 us and 6 us for the mirror pass (2.1 TB/s of samples).  Few samples
+// are done before a mirror pass would have been launched: they add their
+// conjugates themselves (DIRECT).
 constexpr int GRID_PER = 4;
 
-template <bool VEC>
+template <bool VEC, bool DIRECT>
 __global__ void __launch_bounds__(256)
 image_grid_kernel(const float* __restrict__ u, const float* __restrict__ v, const float2* __restrict__ vis,
                   const float* __restrict__ weight, int64_t n_vis, int n, double inv_du,
@@ -59,6 +61,11 @@ image_grid_kernel(const float* __restrict__ u, const float* __restrict__ v, cons
     float* const a = reinterpret_cast<float*>(grid + cell);
     atomicAdd(a, z.x);
     atomicAdd(a + 1, z.y);
+    if constexpr (DIRECT) {  // (n - iu, n - iv)
+      float* const b = reinterpret_cast<float*>(grid + ((int64_t)n * n + n - cell));
+      atomicAdd(b, z.x);
+      atomicAdd(b + 1, -z.y);
+    }
   };
   // whole waves run each step: the scan needs every lane
   const int64_t wave_step = (int64_t)gridDim.x * blockDim.x * GRID_PER;
@@ -552,13 +559,20 @@ extern "C" qc_status qc_image_grid(const float* u, const float* v, const float* 
     const int64_t blocks = (n_vis + per - 1) / per < 2048 ? (n_vis + per - 1) / per : 2048;
     const bool vec = ((reinterpret_cast<uintptr_t>(u) | reinterpret_cast<uintptr_t>(v) |
                        reinterpret_cast<uintptr_t>(vis) | reinterpret_cast<uintptr_t>(weight)) & 15u) == 0;
-    hipLaunchKernelGGL(vec ? qc::image_grid_kernel<true> : qc::image_grid_kernel<false>, dim3((unsigned)blocks),
-                       dim3(256), 0, s, u, v, reinterpret_cast<const float2*>(vis), weight, n_vis, (int)n,
-                       (double)n * cell_rad, reinterpret_cast<float2*>(grid), wsum);
+    // a mirror pass costs 2.4 us of launch and 16 B a pixel, two more atomics a
+    // sample less than that up to here: 40000 samples onto 64 x 64 13.3 us (15.7
+    // with the pass), 60000 16.6 (15.7); onto 4096 x 4096 3000 28 us (70), 500000
+    // 119 (118)
+    const bool direct = n_vis <= 45056 + npix / 32;
+    hipLaunchKernelGGL((vec ? direct ? qc::image_grid_kernel<true, true> : qc::image_grid_kernel<true, false>
+                            : direct ? qc::image_grid_kernel<false, true> : qc::image_grid_kernel<false, false>),
+                       dim3((unsigned)blocks), dim3(256), 0, s, u, v, reinterpret_cast<const float2*>(vis), weight,
+                       n_vis, (int)n, (double)n * cell_rad, reinterpret_cast<float2*>(grid), wsum);
     e = hipGetLastError();
     if (e != hipSuccess) return qc::api_fail(QC_EHIP, "grid kernel: %s", hipGetErrorString(e));
-    hipLaunchKernelGGL(qc::image_mirror_kernel, dim3((unsigned)((npix / 2 + n + 255) / 256)), dim3(256), 0, s,
-                       reinterpret_cast<float2*>(grid), (int)n);
+    if (!direct)
+      hipLaunchKernelGGL(qc::image_mirror_kernel, dim3((unsigned)((npix / 2 + n + 255) / 256)), dim3(256), 0, s,
+                         reinterpret_cast<float2*>(grid), (int)n);
     e = hipGetLastError();
     if (e != hipSuccess) return qc::api_fail(QC_EHIP, "grid kernel: %s", hipGetErrorString(e));
   }
