@@ -435,6 +435,12 @@ int64_t fused_width_for(int n_fft, int n_ant) {
   return it == g_width.end() ? 0 : it->second;
 }
 
+// Tuners run their first candidate this long before they time any: a GPU that
+// was idle needs some milliseconds to its clock (the default tile of 4096 points
+// and 4 antennas, timed first, took 1.38 ms instead of 1.13, and lost to one of
+// 1.35).
+constexpr double TUNE_WARM_MS = 40.0;
+
 qc_status channelize_impl(const Resolved& r, qc_prec out_prec, void* out, float* scale_out,
                           hipStream_t s) {
   const qc::FxArgs& a = r.args;
@@ -998,6 +1004,9 @@ qc_status qc_fx_autotune(const int8_t* x, int64_t ld_x, int32_t n_ant, int64_t n
   int best_t = 0;
   int64_t best_w = 0;
   std::vector<double> ms(n, 0.0);
+  set_choice(0, 0);
+  for (double spent = 0.0, per = 0.0; st == QC_OK && spent < TUNE_WARM_MS; spent += (reps + 1) * std::max(per, 1e-3))
+    st = time_calls(&per);
   for (int t = 0; t < n && st == QC_OK; ++t) {
     const int first = qc::fused_tile_first(p->n_fft, n_ant, t);
     double per = ms[first];
@@ -1499,7 +1508,9 @@ qc_status plan_time(qc_plan* P, const int8_t* const* x, float* const* vis, int r
 qc_status graph_tune(qc_plan* P, const int8_t* const* x, float* const* vis, int reps, hipStream_t s,
                      hipEvent_t a, hipEvent_t b) {
   double best = 0.0;
-  qc_status st = plan_time(P, x, vis, reps, s, a, b, &best);
+  qc_status st = QC_OK;
+  for (double spent = 0.0; st == QC_OK && spent < TUNE_WARM_MS; spent += (reps + 1) * std::max(best, 1e-3))
+    st = plan_time(P, x, vis, reps, s, a, b, &best);
   auto try_value = [&](auto set, auto get, const std::vector<int64_t>& cand) -> qc_status {
     const int64_t keep = get();
     int64_t bestv = keep;
