@@ -116,7 +116,7 @@ __device__ __forceinline__ auto ring_word(const T& w) {
 // The same for four real samples by the bytes: a byte plus 128 below the
 // exponent of 1024 is the half 1152 + b, and taking off 1152 is exact.  Five
 // instructions where the conversions, shifts and merges are ten; in the fused
-// ping-pong tile 1128 -> 1117 us for 4 x 2^28 samples, in the ring F-engine,
+// ping-pong tile 11 us less for 4 x 2^28 samples, in the ring F-engine,
 // whose stores overlap its conversions, 2 % slower.
 __device__ __forceinline__ uint64_t halves_of(uint32_t w) {
   typedef _Float16 half2_t __attribute__((ext_vector_type(2)));
@@ -1650,9 +1650,9 @@ channelize_kernel(const int8_t* __restrict__ x, int64_t ld_x, int n_ant, int64_t
 // With PP the transform ping-pongs between two buffers as in the fused
 // ping-pong tile (one barrier per radix pass, none after the stores);
 // without it the transform runs in place.  Bound: vector issue, at a power
-// limit: the F+X of 32 antennas x 4096 spectra of 4096 points in FP16 takes 872 us,
-// 898 us with a conversion per value and a test of the antenna per store, and
-// no less with the reduction after it left out.
+// limit: the F+X of 32 antennas x 4096 spectra of 4096 points in FP16 takes 872 us
+// (885 with a conversion per value and a test of the antenna per store), and no
+// less with the reduction after it left out.
 template <int N, int NA, int V, int P, bool PP = false>
 struct ChanRingCfg {
   using C = FusedCfg<N, NA, 1, V, false, 0>;
