@@ -99,3 +99,28 @@ def test_zero_at_the_last_pixel(qc, n):
 def test_limits_reject(qc):
     assert qc.lib().qc_image_clean_limits(17, 0) == -1
     assert qc.lib().qc_image_clean_limits(0, 1000001) == -1
+
+
+@pytest.mark.parametrize("n", [64, 512])
+def test_in_a_graph(qc, n):
+    """A captured CLEAN claims and gives back an area on each replay; eager work and
+    a CLEAN outside the graph run in between."""
+    import torch
+    one, other = (_Launch(qc, *_input(n, n + q), 0.3, 0.0, 12) for q in (1, 2))
+    D, E = one.res.clone(), other.res.clone()
+    one.go()                                     # first use outside the capture
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    one.stream.wait_stream(torch.cuda.current_stream())
+    with torch.cuda.graph(graph, stream=one.stream):
+        one.go()
+    for _ in range(20):
+        one.res.copy_(D)
+        other.res.copy_(E)
+        one.count.fill_(-7)
+        torch.cuda.synchronize()
+        graph.replay()
+        other.go()
+        torch.cuda.synchronize()
+        one.check()
+        other.check()
