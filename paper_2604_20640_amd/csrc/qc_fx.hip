@@ -548,17 +548,18 @@ fx_fused_ring_kernel(const int8_t* __restrict__ x, int64_t ld_x, const int8_t* _
 // barrier instead of two: four per spectrum (after the FIR and after each of
 // the three passes; the next spectrum's FIR writes the buffer the last pass
 // read, and its first pass writes the buffer the X step read, each behind a
-// barrier).  Beside the two buffers, LDS holds the per-pass twiddles: all of them
-// with one transform, up to the last pass's r = 8 with two of 4096 points, which
-// keeps the whole working set within 160 KiB.  The last pass then reads its
-// r = 9..15 from the table in global memory (14 KiB, the same seven places of it
-// per thread and spectrum): 4 antennas x 2^28 samples 1144 us, 1120 with the seven
-// formed as products, which are less exact (below); no less with the reads ahead
-// of the barrier before them, with r = 9..11 in what is left of the LDS, or in
-// registers (1575: the kernel has none left).
+// barrier).  Beside the two buffers, LDS holds the per-pass twiddle table up
+// to the last pass's r = 8 (a prefix of the per-pass layout), which keeps the
+// whole working set within 160 KiB.  The last pass reads its r = 9..15 from the
+// table in global memory (14 KiB, the same seven places of it per thread and
+// spectrum): 4 antennas x 2^28 samples 1128 us, 1120 with the seven formed as
+// products, which are less exact (below); 1148 with 64-bit addresses in vector
+// registers.  No less with the reads ahead of the barrier before them, with r =
+// 9..11 in what is left of the LDS, or in registers (1575: the kernel has none
+// left); 2 antennas, whose whole table fits the LDS, 867 us, 888 from there.
 // The taps of a thread's chunk positions are read from global memory into
 // registers once (any P = 4 prototype).
-template <int N, int V, int BUF>
+template <int N, int V>
 struct PpTw {
   static constexpr int PASSES = fft_pass_count(N, V);
   static constexpr int last_ns() {
@@ -569,20 +570,19 @@ struct PpTw {
   static constexpr int NSL = last_ns();
   static constexpr int RLAST = N / NSL;
   static_assert(RLAST == 16, "the last pass has radix 16");
-  // a prefix of the per-pass table: the passes before the last, then the last
-  // pass's r = 1..ROWS
+  // per-pass entries before the last pass, then the last pass's r = 1..8
   static constexpr int EARLY = (N - 1) - (RLAST - 1) * NSL;
-  static constexpr int ROWS = sizeof(float2) * (2 * (size_t)BUF + N - 1) <= 160 * 1024 ? RLAST - 1 : 8;
-  static constexpr int LDS_TW = EARLY + ROWS * NSL;
+  static constexpr int LDS_TW = EARLY + 8 * NSL;
 };
 
 // Last pass (stride NS, radix 16, one butterfly per thread) with the
-// twiddles of r = 1..ROWS from the LDS table and the others from twp, the
-// per-pass table it is a prefix of.  PROD: r = 9..15 as products W^{jm q} W^{8 jm}
-// instead, whose rounding adds 6 % to the rms error of a 4096-point transform
-// (7.5e-8 of the spectrum's rms, 7.1e-8 with the table); kept for requantised
-// spectra, whose bits it decides now and then.
-template <int N, int NS, int NT, int ROWS, bool PROD>
+// twiddles of r = 1..8 from the LDS table and r = 9..15 from twp, the per-pass
+// table it is a prefix of (one scalar base a row and one 32-bit offset).
+// PROD: r = 9..15 as products W^{jm q} W^{8 jm} instead, whose rounding adds 6 %
+// to the rms error of a 4096-point transform (7.5e-8 of the spectrum's rms,
+// 7.1e-8 with the table); kept for requantised spectra, whose bits it decides
+// now and then.
+template <int N, int NS, int NT, bool PROD>
 __device__ __forceinline__ void stockham_last_pass_half(const float2* src, float2* dst, const float2* twl,
                                                         const float2* __restrict__ twp, int tid) {
   constexpr int R = 16;
@@ -593,12 +593,15 @@ __device__ __forceinline__ void stockham_last_pass_half(const float2* src, float
   float2 w[R];
   if constexpr (!PROD)  // on their way while the LDS is read
 #pragma unroll
-    for (int r = ROWS + 1; r < R; ++r) w[r] = twp[(NS - 1) + (r - 1) * NS + jm];
+    for (int r = 9; r < R; ++r) {
+      const char* const row = reinterpret_cast<const char*>(twp + (NS - 1) + (r - 1) * NS);
+      w[r] = *reinterpret_cast<const float2*>(row + (uint32_t)jm * (uint32_t)sizeof(float2));
+    }
   float2 v[R];
 #pragma unroll
   for (int r = 0; r < R; ++r) v[r] = src[lds_at<NB>(f * N + j, p0, r)];
 #pragma unroll
-  for (int r = 1; r <= (PROD ? 8 : ROWS); ++r) w[r] = twl[(NS - 1) + (r - 1) * NS + jm];
+  for (int r = 1; r <= 8; ++r) w[r] = twl[(NS - 1) + (r - 1) * NS + jm];
   if constexpr (PROD)
 #pragma unroll
     for (int q = 1; q < 8; ++q) w[8 + q] = cmul(w[q], w[8]);
@@ -613,7 +616,7 @@ __device__ __forceinline__ void stockham_last_pass_half(const float2* src, float
 
 // TWG: table twiddles read in groups of TWG, 0 for one wait per read (see
 // stockham_pass).
-template <int N, int NS, int NT, int V, int PASS, int ROWS, int TWG = 4, bool PROD = false>
+template <int N, int NS, int NT, int V, int PASS, int TWG = 4, bool PROD = false>
 __device__ __forceinline__ void fft_pp_passes(float2* b0, float2* b1, const float2* twl,
                                               const float2* __restrict__ twp, int tid) {
   constexpr int REM = N / NS;
@@ -622,10 +625,10 @@ __device__ __forceinline__ void fft_pp_passes(float2* b0, float2* b1, const floa
     float2* src = (PASS % 2 == 0) ? b0 : b1;
     float2* dst = (PASS % 2 == 0) ? b1 : b0;
     if constexpr (NS * R == N)
-      stockham_last_pass_half<N, NS, NT, ROWS, PROD>(src, dst, twl, twp, tid);
+      stockham_last_pass_half<N, NS, NT, PROD>(src, dst, twl, twp, tid);
     else
       stockham_pass<N, R, NS, NT, V, false, false, true, TWG>(src, dst, twl, tid);
-    fft_pp_passes<N, NS * R, NT, V, PASS + 1, ROWS, TWG, PROD>(b0, b1, twl, twp, tid);
+    fft_pp_passes<N, NS * R, NT, V, PASS + 1, TWG, PROD>(b0, b1, twl, twp, tid);
   }
 }
 
@@ -641,8 +644,7 @@ template <int N, int NA, int V, int P>
 struct RingPpCfg {
   using C = FusedCfg<N, NA, 1, V, false, 0>;
   static constexpr int BUF = C::BUF;  // padded buffer
-  using TW = PpTw<N, V, BUF>;
-  static constexpr size_t LDS_BYTES = sizeof(float2) * (2 * (size_t)BUF + TW::LDS_TW);
+  static constexpr size_t LDS_BYTES = sizeof(float2) * (2 * (size_t)BUF + PpTw<N, V>::LDS_TW);
 };
 
 template <int N, int NA, int V, int P>
@@ -664,7 +666,7 @@ fx_fused_ring_pp_kernel(const int8_t* __restrict__ x, int64_t ld_x, const int8_t
   const int64_t m_lo = d * spec_per_dump + (c * spec_per_dump) / cpd;
   const int64_t m_hi = d * spec_per_dump + ((c + 1) * spec_per_dump) / cpd;
 
-  for (int i = tid; i < RC::TW::LDS_TW; i += C::NT) twl[i] = twp[i];
+  for (int i = tid; i < PpTw<N, V>::LDS_TW; i += C::NT) twl[i] = twp[i];
 
   constexpr int GP = G / C::NP;
   static_assert(GP * C::NP == G && GP * C::NT * 4 == N, "ring chunk mapping");
@@ -756,7 +758,7 @@ fx_fused_ring_pp_kernel(const int8_t* __restrict__ x, int64_t ld_x, const int8_t
       for (int i = 0; i < 4; ++i) b0[lds_pad((g / GP) * N + cn0[g] + i)] = make_float2(y0[i], y1[i]);
     }
     __syncthreads();
-    fft_pp_passes<N, 1, C::NT, V, 0, RC::TW::ROWS>(b0, b1, twl, in_place(twp), tid);
+    fft_pp_passes<N, 1, C::NT, V, 0>(b0, b1, twl, in_place(twp), tid);
     static_assert(C::NCH % C::NT == 0, "every thread has CPT channels");
     // all of the thread's transform outputs are read before any is used, so
     // the reads overlap instead of each waiting for the one before
@@ -858,7 +860,7 @@ struct CplxCfg {
   static constexpr bool SQ = M == 4096;         // radix-16 throughout: the shortened table
   static constexpr bool SUMS = DEC == 2;        // filter state: sums, not blocks
   static constexpr int tw_entries() {
-    if constexpr (SQ) return PpTw<M, V, BUF>::LDS_TW;
+    if constexpr (SQ) return PpTw<M, V>::LDS_TW;
     else return M;
   }
   static constexpr size_t LDS_BYTES = sizeof(float2) * (2 * (size_t)BUF + tw_entries());
@@ -1065,7 +1067,7 @@ fx_fused_cplx_kernel(const int8_t* __restrict__ x, int64_t ld_x, const int8_t* _
         ring[RP - 1][a][g] = load_next(a, g, nb);
       }
     __syncthreads();
-    if constexpr (C::SQ) fft_pp_passes<M, 1, NT, C::V, 0, PpTw<M, C::V, C::BUF>::ROWS>(b0, b1, twl, in_place(twp), lt);
+    if constexpr (C::SQ) fft_pp_passes<M, 1, NT, C::V, 0>(b0, b1, twl, in_place(twp), lt);
     else Fft<M, NT, C::V, true, false, true>::run(b0, b1, twl, lt);
     float2 z[C::CPT][NA];
 #pragma unroll
@@ -1708,7 +1710,7 @@ __device__ __forceinline__ void chan_ring_body(const int8_t* __restrict__ x, int
   const int64_t m_hi = m_lo + spb < n_spec ? m_lo + spb : n_spec;
 
   if constexpr (PP) {
-    for (int i = tid; i < PpTw<N, V, C::BUF>::LDS_TW; i += C::NT) twl[i] = twp[i];
+    for (int i = tid; i < PpTw<N, V>::LDS_TW; i += C::NT) twl[i] = twp[i];
   } else {
     build_pass_twiddles<N, V>(twl, tw, tid, C::NT);
   }
@@ -1803,7 +1805,7 @@ __device__ __forceinline__ void chan_ring_body(const int8_t* __restrict__ x, int
     }
     __syncthreads();
     if constexpr (PP)
-      fft_pp_passes<N, 1, C::NT, V, 0, PpTw<N, V, C::BUF>::ROWS, 0, PREC != 0>(
+      fft_pp_passes<N, 1, C::NT, V, 0, 0, PREC != 0>(
           // kept over the loop for 16-bit words: 13 antennas x 1024 spectra 90 us, 94 in
           // place; read in place for 8-bit ones: 83 us, 86 kept, complex 93 and 103
           b0, b1, twl, ST == 1 || ST == 3 ? twp : in_place(twp), tid);
